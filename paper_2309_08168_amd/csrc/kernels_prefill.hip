@@ -3,22 +3,21 @@
 // long forwards in general.  With hundreds of rows the linear layers are
 // dense contractions, 2 M N K flops per N K weight bytes, so they run on
 // matrix cores:
-//   - k_pf_gemm: C = A W^T with the float32 activations split into X_TERMS
-//     bfloat16 terms (exact for float32 values), 256 x 128 output tiles,
-//     stages of 32 k staged through double-buffered LDS in MFMA fragment
-//     order, v_mfma 16x16x32 bf16; tiles are ordered so the work-groups one
-//     XCD runs together share their weight and activation slices in that
-//     XCD's L2; narrow residual updates split the reduction into partials;
-//   - k_pf_gemm_wide: the same product on 256 x 256 (or 256 x 224) tiles
-//     with the operands loaded straight into LDS, for the layers with
-//     enough tiles to fill the CUs, and for split residual updates that do;
+//   - k_pf_gemm: C = A W^T with the float32 activations as two float16 terms
+//     and the weights turned into float16 on the way, v_mfma 16x16x32 f16 on
+//     tiles of 256 x 256 down to 128 x 64, every operand loaded straight into
+//     LDS in MFMA fragment order; tiles are ordered so the work-groups one XCD
+//     runs together share their weight and activation slices in that XCD's
+//     L2; residual updates split the reduction into partials;
+//   - k_pf_thin: the same products for up to 64 rows, bound by the weight
+//     stream, with the rotary embedding and KV append in the QKV epilogue;
 //   - k_pf_attn: causal attention, one wave per 16 query rows of a head,
 //     scores and the weighted sum of values on matrix cores with an online
 //     softmax over 32-key blocks, the longest row blocks dispatched first and
 //     spread evenly over the XCDs;
-//   - small row kernels between them: embedding, RMSNorm + split (adding a
-//     split residual update's partials first), rotary embedding + KV
-//     append, SwiGLU + split.
+//   - small row kernels between them: embedding, RMSNorm into terms (adding a
+//     residual update's partials first), rotary embedding + KV append, and
+//     the terms of the attention output and of the MLP activation.
 #include "sd_internal.h"
 
 #include <algorithm>
@@ -27,6 +26,8 @@ namespace sdk {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -36,6 +37,16 @@ typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 __device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                    c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4_t mfma16h(u32x4_t a, u32x4_t b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0,
+                                                  0, 0);
+}
+
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a),
+                                                                  __builtin_bit_cast(u16x2_t, b)));
 }
 
 __device__ __forceinline__ float bf_to_f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
@@ -59,307 +70,195 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4_t (&t)[X_TERMS
 }
 
 // ---------------------------------------------------------------------------
+// GEMM inputs as float16 terms
+//
+// A float32 activation row x is held as PF_TERMS = 2 float16 planes of the row
+// times a power of two: x 2^sa = hi + lo, hi = rne(x 2^sa), lo = rne(x 2^sa - hi),
+// with the row's largest magnitude in [2^14, 2^15), and rs[row] = 2^-sa undoes
+// the scale in the GEMM's epilogue.  hi and lo carry 22 bits of every element
+// down to 2^-18 of the row's largest and are within 2^-40 of the largest below
+// that: an activation smaller than 2^-18 of its row keeps fewer bits (three
+// bfloat16 terms kept them all), which shows in an output only if the larger
+// ones meet weights that much smaller.  The outlier channels of trained models
+// are about 2^12 times the rest.
+// Weights become float16 on their way into LDS, times WSCALE: exact for
+// bfloat16 values from 2^-17 / WSCALE up, and to 2^-24 / WSCALE absolutely
+// below that.  A tile whose rows do not fit that window (wide_ok) runs again
+// with a power of two per weight row.  Products of the terms are exact, only
+// the float32 accumulation rounds, as with three bfloat16 terms, in two
+// thirds of the matrix instructions and so of the accumulation steps: against
+// float64 the outputs are nearer.
+
+constexpr float WSCALE = 1024.0f;
+// magnitudes (bf16 bits) a weight row's largest may have at WSCALE: 2^-14 up to 2^5 (2^15 scaled)
+constexpr uint32_t WROW_MIN = (127 - 14) << 7, WROW_MAX = (127 + 5) << 7;
+
+__device__ __forceinline__ bool wide_ok(uint32_t m) { return m == 0 || (m >= WROW_MIN && m <= WROW_MAX); }
+
+// 2^sa for a row whose largest magnitude is amax, and 2^-sa
+__device__ __forceinline__ float row_scale(float amax, float *inv) {
+    const int e = (int)((__float_as_uint(amax) >> 23) & 255u);
+    int sa = e == 255 || e == 0 ? 0 : 141 - e;  // inf, NaN and (sub)zero rows as they are
+    sa = sa < -100 ? -100 : (sa > 100 ? 100 : sa);
+    *inv = __uint_as_float((uint32_t)(127 - sa) << 23);
+    return __uint_as_float((uint32_t)(127 + sa) << 23);
+}
+
+// The terms of eight consecutive scaled values, each packed as 8 halves.
+__device__ __forceinline__ void split_f16x8(const float (&x)[8], u32x4_t &hi, u32x4_t &lo) {
+    f16x8_t h, l;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        h[u] = (_Float16)x[u];
+        l[u] = (_Float16)(x[u] - (float)h[u]);
+    }
+    hi = __builtin_bit_cast(u32x4_t, h);
+    lo = __builtin_bit_cast(u32x4_t, l);
+}
+
+// ---------------------------------------------------------------------------
 // GEMM
 //
-// Work-group tile: 256 weight rows (output columns) x 128 activation rows,
-// 8 waves (2 per SIMD, so one wave's MFMAs run while the other waits).
-// Each 32-k stage is staged through LDS in fragment order: every 16 x 32
-// MFMA operand block is 1 KB with lane l's 16 bytes at offset 16 l, so a
-// fragment read is one contiguous 1 KB read and the staging writes of each
-// 8-lane group are 128 contiguous bytes (bank-conflict free both ways).
-// The weight tile is read once per 128 rows; each activation term block
-// once per 256 columns.
+// C = A W^T on tiles of BM activation rows x BN weight rows, NWN x NWM waves,
+// 32-k stages through LDS.  Every 16 x 32 MFMA operand block is 1 KB of LDS
+// with lane l's 16 bytes at 16 l, so a fragment read is one contiguous 1 KB
+// read.  All operands go from global memory straight into LDS
+// (global_load_lds_dwordx4: lane l's 16 bytes to 16 l), P stages ahead: the
+// activation terms as they are, the weights as bfloat16 into a block of the
+// wave that loads them, which turns them into float16 one stage before they
+// are multiplied.  The barrier is a bare s_barrier: a release fence before it
+// would also wait for the loads of the coming stages.
 
-constexpr int GB_N = 256;  // weight rows (output columns) per work-group
-constexpr int GB_M = 128;  // activation rows per work-group
-constexpr int GB_K = 32;   // k per stage: one MFMA k-step
-constexpr int G_THREADS = 512;
+// s_waitcnt immediate (gfx9 layout: vmcnt bits 3:0 and 15:14, expcnt 6:4,
+// lgkmcnt 11:8) that waits for vmcnt n and leaves the other counters alone
+constexpr int wait_vmcnt(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-// Offset (bf16 elements) of the 16-byte chunk kc of row r in a stage buffer.
-__device__ __forceinline__ int frag_off(int r, int kc) { return (r >> 4) * 512 + ((r & 15) + 16 * kc) * 8; }
+// Sixteen bytes per lane from g to LDS at l + 16 lane (l the same in every
+// lane).  The compiler does not see these loads: it would wait for all of them
+// before it reads or writes LDS anywhere, as they might overlap.  The kernel
+// counts them itself (wait_vmcnt).  They have no register result; M0 holds the
+// LDS address and needs one wait state before the load.
+__device__ __forceinline__ void load_to_lds16(const uint16_t *g, uint16_t *l) {
+    const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)l;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(
+                     __builtin_amdgcn_readfirstlane(off)),
+                 "v"(g)
+                 : "memory", "m0");
+}
 
-// NWN x NWM waves (NWN along the weight rows); DEPTH stages of operands in
-// flight in registers; EPI_PARTIAL writes the split's partial tile to
-// part[blockIdx split][m][n].
-template <int EPI, int NWN, int NWM, int DEPTH>
-__global__ __launch_bounds__(G_THREADS, 2) void k_pf_gemm(PfGemmArgs a) {
-    constexpr int T = X_TERMS;
-    constexpr int WN = GB_N / NWN, WM = GB_M / NWM;  // a wave's share
-    constexpr int NT = WN / 16, MT = WM / 16;        // 16 x 16 output tiles per wave
-    constexpr int W_PT = GB_N * 4 / G_THREADS;       // staging chunks per thread: weights
-    constexpr int A_PT = T * GB_M * 4 / G_THREADS;   // staging chunks per thread: activation terms
-    static_assert(NWN * NWM * 64 == G_THREADS && W_PT * G_THREADS == GB_N * 4 && A_PT * G_THREADS == T * GB_M * 4,
-                  "tile split");
-    static_assert(DEPTH == 1 || DEPTH == 2, "stages in flight");
-    __shared__ __attribute__((aligned(16))) uint16_t ws[2][GB_N * GB_K];
-    __shared__ __attribute__((aligned(16))) uint16_t as[2][T * GB_M * GB_K];
+template <int EPI, int BN, int BM, int NWN, int NWM, int P, int WPS>
+__global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
+    constexpr int T = PF_TERMS, NW = NWN * NWM;
+    constexpr int WN = BN / NWN, WM = BM / NWM;          // a wave's share
+    constexpr int NT = WN / 16, MT = WM / 16;            // 16 x 16 output tiles per wave
+    constexpr int NBW = BN / 16, NBA = T * BM / 16;      // weight and activation blocks per stage
+    constexpr int WPW = (NBW + NW - 1) / NW, APW = (NBA + NW - 1) / NW;  // load instructions per wave and stage
+    static_assert(NT * 16 == WN && MT * 16 == WM, "tile split");
+    static_assert(EPI == EPI_STORE || EPI == EPI_PARTIAL || EPI == EPI_SWIGLU, "epilogue");
+    constexpr bool SWI = EPI == EPI_SWIGLU;
+    // float16 weights, activation terms, bfloat16 weights (a block per wave and load)
+    constexpr int LW = 2 * NBW * 512, LA = (P + 1) * NBA * 512, LR = P * WPW * NW * 512;
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[LW + LA + LR];
+    uint16_t *const lw = lds, *const la = lds + LW, *const lr = lds + LW + LA;
+    // after the main loop: 1 / scale of each weight row, and row maxima
+    float *const wsc = reinterpret_cast<float *>(lds);
+    uint32_t *const ymax = reinterpret_cast<uint32_t *>(lds) + BN;
+    static_assert(LW * 2 >= (BN + BM + 1) * 4, "epilogue scratch");
 
-    const int M = a.M, N = a.N, K = a.K;
+    constexpr int BC = SWI ? BN / 2 : BN;                // output columns per tile
+    const int M = a.M, N = a.N, K = a.K, F = N / 2;
+    const int NC = SWI ? F : N;                          // output columns
     // Tile and k-split of this work-group.  Work-groups are dealt to the 8
     // XCDs in turn, so each XCD gets a contiguous range of tile indices, and
     // the range is walked in groups of 4 row tiles: the tiles one XCD runs
     // at a time form a compact block whose operand slices its L2 holds.
-    const int TM = (M + GB_M - 1) / GB_M, TN = (N + GB_N - 1) / GB_N, TT = TM * TN * a.splits;
+    const int TM = (M + BM - 1) / BM, TN = (NC + BC - 1) / BC, TT = TM * TN * a.splits;
     const int per = (TT + 7) / 8;
     int L = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if (L >= TT)
+    if ((int)(blockIdx.x >> 3) >= per || L >= TT)
         return;  // uniform over the work-group
     const int split = L % a.splits;
     L /= a.splits;
     const int GM = TM < 4 ? TM : 4;
     const int grp_i = L / (GM * TN), first = grp_i * GM, gm = min(TM - first, GM);
     const int in = L - grp_i * GM * TN;
-    const int m0 = (first + in % gm) * GB_M, n0 = (in / gm) * GB_N;
-    const int S_all = (K + GB_K - 1) / GB_K, S_per = (S_all + a.splits - 1) / a.splits;
-    const int s_begin = split * S_per, S = max(0, min(S_all - s_begin, S_per));
-
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int wn = wave % NWN, wm = wave / NWN;
-
-    // staging chunk c: row 8 (c / 32) + c % 8, k chunk (c / 8) % 4.  Every
-    // load is unconditional (clamped rows, clamped k, stages past the end
-    // reload the last one); chunks past K become zeros on the way into LDS.
-    u32x4_t wr[DEPTH][W_PT], ar[DEPTH][A_PT];
-    auto gload = [&](u32x4_t(&w)[W_PT], u32x4_t(&x)[A_PT], int stage) {
-        const int k0 = (s_begin + min(stage, max(S - 1, 0))) * GB_K;
-#pragma unroll
-        for (int i = 0; i < W_PT; ++i) {
-            const int c = tid + G_THREADS * i, row = 8 * (c >> 5) + (c & 7), k = k0 + 8 * ((c >> 3) & 3);
-            w[i] = *reinterpret_cast<const u32x4_t *>(a.W + (int64_t)min(n0 + row, N - 1) * K + min(k, K - 8));
-        }
-#pragma unroll
-        for (int i = 0; i < A_PT; ++i) {
-            const int c = tid + G_THREADS * i, t = c / (GB_M * 4), rem = c - t * GB_M * 4;
-            const int row = 8 * (rem >> 5) + (rem & 7), k = k0 + 8 * ((rem >> 3) & 3);
-            x[i] = *reinterpret_cast<const u32x4_t *>(a.A + t * a.a_term + (int64_t)min(m0 + row, M - 1) * a.lda +
-                                                      min(k, K - 8));
-        }
-    };
-    auto lstore = [&](int buf, const u32x4_t(&w)[W_PT], const u32x4_t(&x)[A_PT], int stage) {
-        const int k0 = (s_begin + stage) * GB_K;
-        const u32x4_t zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < W_PT; ++i) {
-            const int c = tid + G_THREADS * i, row = 8 * (c >> 5) + (c & 7), kc = (c >> 3) & 3;
-            *reinterpret_cast<u32x4_t *>(&ws[buf][frag_off(row, kc)]) = k0 + 8 * kc < K ? w[i] : zero;
-        }
-#pragma unroll
-        for (int i = 0; i < A_PT; ++i) {
-            const int c = tid + G_THREADS * i, t = c / (GB_M * 4), rem = c - t * GB_M * 4;
-            const int row = 8 * (rem >> 5) + (rem & 7), kc = (rem >> 3) & 3;
-            *reinterpret_cast<u32x4_t *>(&as[buf][frag_off(t * GB_M + row, kc)]) = k0 + 8 * kc < K ? x[i] : zero;
-        }
-    };
-
-    f32x4_t acc[NT][MT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-            acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    auto compute = [&](int buf) {
-        u32x4_t wf[NT], af[MT][T];
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-            wf[i] = *reinterpret_cast<const u32x4_t *>(&ws[buf][(wn * NT + i) * 512 + lane * 8]);
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-                af[j][t] =
-                    *reinterpret_cast<const u32x4_t *>(&as[buf][(t * (GB_M / 16) + wm * MT + j) * 512 + lane * 8]);
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int i = 0; i < NT; ++i)
-#pragma unroll
-                for (int j = 0; j < MT; ++j)
-                    acc[i][j] = mfma16(wf[i], af[j][t], acc[i][j]);
-    };
-
-    // step s: issue the loads of stage s + DEPTH into the set stage s came
-    // from, multiply stage s (LDS buffer s % 2), move stage s + 1 from its
-    // register set into the other buffer, barrier
-    if (S > 0) {
-        gload(wr[0], ar[0], 0);
-        if constexpr (DEPTH == 2)
-            gload(wr[DEPTH - 1], ar[DEPTH - 1], 1);
-        lstore(0, wr[0], ar[0], 0);
-    }
-    __syncthreads();
-    if constexpr (DEPTH == 1) {
-        for (int s = 0; s < S; ++s) {
-            gload(wr[0], ar[0], s + 1);
-            compute(s & 1);
-            if (s + 1 < S)
-                lstore((s & 1) ^ 1, wr[0], ar[0], s + 1);
-            __syncthreads();
-        }
-    } else {
-        for (int s = 0; s < S; s += 2) {
-            gload(wr[0], ar[0], s + 2);
-            compute(0);
-            if (s + 1 < S)
-                lstore(1, wr[DEPTH - 1], ar[DEPTH - 1], s + 1);
-            __syncthreads();
-            if (s + 1 >= S)
-                break;
-            gload(wr[DEPTH - 1], ar[DEPTH - 1], s + 3);
-            compute(1);
-            if (s + 2 < S)
-                lstore(0, wr[0], ar[0], s + 2);
-            __syncthreads();
-        }
-    }
-
-    // lane holds C^T[n0 + wn WN + 16 i + 4 grp + v][m0 + wm WM + 16 j + col]
-    const int col = lane & 15, grp = lane >> 4;
-    float *C = EPI == EPI_PARTIAL ? a.part + (int64_t)split * M * a.ldc : a.C;
-    const bool vec = (a.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-        const int n = n0 + wn * WN + 16 * i + 4 * grp;
-#pragma unroll
-        for (int j = 0; j < MT; ++j) {
-            const int m = m0 + wm * WM + 16 * j + col;
-            if (m >= M || n >= N)
-                continue;
-            float *c = C + (int64_t)m * a.ldc + n;
-            if (vec && n + 3 < N) {
-                f32x4_t v = acc[i][j];
-                if constexpr (EPI == EPI_RESID)
-                    v += *reinterpret_cast<const f32x4_t *>(c);
-                *reinterpret_cast<f32x4_t *>(c) = v;
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (n + v < N)
-                        c[v] = EPI == EPI_RESID ? c[v] + acc[i][j][v] : acc[i][j][v];
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Wide GEMM with direct-to-LDS operand loads
-//
-// The same product and accumulation order as k_pf_gemm (bit-identical
-// results; plain stores) for layers with at least 128 tiles of 256 x 256:
-// 256 activation rows x 256 (or 224) weight rows per work-group as 16 waves
-// (four per SIMD; eight waves of 128 x 64 were 1-4% slower), 32-k stages.
-// Operands go from global memory straight into LDS with
-// global_load_lds_dwordx4: one instruction fills one 1 KB fragment block
-// (lane l's 16 bytes at 16 l), so no registers stage them and no second
-// pass writes LDS.  Two 64 KB stage buffers: the loads of stage s + 1 are
-// issued right after the barrier that ends stage s - 1.  The barrier is a
-// bare s_barrier: a release fence before it would also wait for the next
-// stage's loads.  K must be a multiple of 32.
-
-constexpr int GW_M = 256;                                        // activation rows per work-group
-constexpr int GW_WAVES = 16;                                     // waves per work-group
-constexpr int GW_THREADS = 64 * GW_WAVES;
-constexpr int GW_MIN_TILES = 128;                                // tiles that make a launch "wide"
-constexpr int GW_MIN_SPLIT_GROUPS = 160;                         // work-groups of a wide split reduction
-constexpr int GW_BLOCKS = GB_N / 16 + X_TERMS * GW_M / 16;       // 1 KB fragment blocks per stage (at most)
-constexpr int GW_PER = GW_BLOCKS / GW_WAVES;                     // load instructions per wave per stage
-static_assert(GW_BLOCKS % GW_WAVES == 0, "blocks per wave");
-
-// s_waitcnt immediate (gfx9 layout: vmcnt bits 3:0 and 15:14, expcnt 6:4,
-// lgkmcnt 11:8) that waits for vmcnt 0 and leaves the other counters alone
-constexpr int WAIT_VMCNT0 = (7 << 4) | (15 << 8);
-
-__device__ __forceinline__ void load_to_lds16(const uint16_t *g, uint16_t *l) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
-                                     (__attribute__((address_space(3))) void *)l, 16, 0, 0);
-}
-
-// BN: weight rows per tile, 256 (4 x 4 waves of 64 x 64) or 224 (2 x 8
-// waves of 112 x 32, 14 weight blocks per stage, the last two load slots of
-// a stage idle).  EPI_SWIGLU (W = [gate; up], N = 2 F): a tile takes the
-// gate and the up rows of the same BN / 2 columns f of the MLP, the waves
-// holding up pass their sums to the waves holding gate through LDS, and
-// those write silu(gate) * up as terms.
-template <int EPI, int BN>
-__global__ __launch_bounds__(GW_THREADS, 4) void k_pf_gemm_wide(PfGemmArgs a) {
-    static_assert(BN == 256 || BN == 224, "tile width");
-    constexpr int T = X_TERMS, NWN = BN == 256 ? 4 : 2, NWM = GW_WAVES / NWN;
-    constexpr int WN = BN / NWN, WM = GW_M / NWM;
-    constexpr int NT = WN / 16, MT = WM / 16;
-    constexpr int NBW = BN / 16;                       // weight blocks per stage
-    constexpr int NB = NBW + X_TERMS * GW_M / 16;      // blocks per stage
-    static_assert(NB <= GW_BLOCKS && NT * 16 == WN && MT * 16 == WM, "tile split");
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * GW_BLOCKS * 512];
-
-    constexpr bool SWI = EPI == EPI_SWIGLU;
-    constexpr int BC = SWI ? BN / 2 : BN;              // output columns per tile
-    const int M = a.M, N = a.N, K = a.K, F = N / 2;
-    const int NC = SWI ? F : N;                        // output columns
-    // tile and k-split order as in k_pf_gemm: each XCD a contiguous range,
-    // walked in groups of up to 4 row tiles
-    const int TM = (M + GW_M - 1) / GW_M, TN = (NC + BC - 1) / BC, TT = TM * TN * a.splits;
-    const int per = (TT + 7) / 8;
-    int L = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if (L >= TT)
-        return;  // uniform over the work-group
-    const int split = L % a.splits;
-    L /= a.splits;
-    const int GM = TM < 4 ? TM : 4;
-    const int grp_i = L / (GM * TN), first = grp_i * GM, gm = min(TM - first, GM);
-    const int in = L - grp_i * GM * TN;
-    const int m0 = (first + in % gm) * GW_M, n0 = (in / gm) * BC;  // SWI: n0 is the first f
+    const int m0 = (first + in % gm) * BM, tn = in / gm, n0 = tn * BC;  // SWI: n0 is the first f
     // the split's stages (possibly none: its partial tile is then zeros)
-    const int S_all = K / GB_K, S_per = (S_all + a.splits - 1) / a.splits;
+    const int S_all = (K + 31) / 32, S_per = (S_all + a.splits - 1) / a.splits;
     const int s_begin = split * S_per, S = max(0, min(S_all - s_begin, S_per));
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int wn = wave % NWN, wm = wave / NWN;
+    const int wn = wave % NWN, wm = wave / NWN, col = lane & 15, grp = lane >> 4;
 
-    // block b of a stage: b < NBW the weight rows n0 + 16 b .., else term t
-    // of activation rows m0 + 16 rg ..; lane l loads row 16 b + l % 16,
-    // k chunk l / 16 (rows past the end read the last row: never stored)
-    const uint16_t *src[GW_PER];
+    // Weight block b holds rows n0 + 16 b .., or with SWI eight gate rows
+    // f = n0 + 8 b .. and then the up rows of the same f; lane l loads row
+    // l % 16, k chunk l / 16 (rows past the end read the last one: never
+    // stored).  The lane keeps the largest magnitude of what it loads.
+    const uint16_t *wsrc[WPW];
+    uint32_t wmax[WPW];
+    float wscale[WPW], winv[WPW];
 #pragma unroll
-    for (int i = 0; i < GW_PER; ++i) {
-        const int b = min(wave + GW_WAVES * i, NB - 1);  // slots past NB load nothing (below)
-        if (b < NBW) {
-            int row;
-            if constexpr (SWI)  // gate rows f, then up rows F + f
-                row = (b < NBW / 2 ? 0 : F) + min(n0 + 16 * (b % (NBW / 2)) + (lane & 15), F - 1);
-            else
-                row = min(n0 + 16 * b + (lane & 15), N - 1);
-            src[i] = a.W + (int64_t)row * K + 8 * (lane >> 4);
-        } else {
-            const int c = b - NBW, t = c / (GW_M / 16), rg = c % (GW_M / 16);
-            src[i] = a.A + t * a.a_term + (int64_t)min(m0 + 16 * rg + (lane & 15), M - 1) * a.lda + 8 * (lane >> 4);
-        }
+    for (int i = 0; i < WPW; ++i) {
+        const int b = min(wave + NW * i, NBW - 1);
+        int row;
+        if constexpr (SWI)
+            row = (col < 8 ? 0 : F) + min(n0 + 8 * b + (col & 7), F - 1);
+        else
+            row = min(n0 + 16 * b + col, N - 1);
+        wsrc[i] = a.W + (int64_t)row * K;
+        wmax[i] = 0;
+        wscale[i] = WSCALE;
+        winv[i] = 1.0f / WSCALE;
     }
-    auto issue = [&](int stage) {
-        uint16_t *dst = lds + (stage & 1) * GW_BLOCKS * 512;
+    const uint16_t *asrc[APW];
 #pragma unroll
-        for (int i = 0; i < GW_PER; ++i)
-            if (NB % GW_WAVES == 0 || wave + GW_WAVES * i < NB)  // uniform over the wave
-                load_to_lds16(src[i] + (s_begin + stage) * GB_K, dst + (wave + GW_WAVES * i) * 512);
+    for (int i = 0; i < APW; ++i) {
+        const int c = min(wave + NW * i, NBA - 1), t = c / (BM / 16), rg = c % (BM / 16);
+        asrc[i] = a.A + t * a.a_term + (int64_t)min(m0 + 16 * rg + col, M - 1) * a.lda + 8 * grp;
+    }
+    // stages past the end load the last one again (into buffers no one reads),
+    // so every wave has the same number of loads in flight
+    auto aload = [&](int stage) {
+        uint16_t *dst = la + (stage % (P + 1)) * NBA * 512;
+        const int k0 = (s_begin + min(stage, S - 1)) * 32;
+#pragma unroll
+        for (int i = 0; i < APW; ++i)
+            load_to_lds16(asrc[i] + k0, dst + min(wave + NW * i, NBA - 1) * 512);
+    };
+    auto wload = [&](int stage) {
+        uint16_t *dst = lr + (stage % P) * WPW * NW * 512;
+        const int k = (s_begin + min(stage, S - 1)) * 32 + 8 * grp;
+#pragma unroll
+        for (int i = 0; i < WPW; ++i)
+            load_to_lds16(wsrc[i] + min(k, K - 8), dst + (wave + NW * i) * 512);
+    };
+    // this wave's weights of a stage: zero past K, largest magnitude, float16
+    auto wconvert = [&](int stage) {
+        const uint16_t *src = lr + (stage % P) * WPW * NW * 512;
+        uint16_t *dst = lw + (stage & 1) * NBW * 512;
+        const bool ok = (s_begin + stage) * 32 + 8 * grp < K;
+#pragma unroll
+        for (int i = 0; i < WPW; ++i) {
+            if (NBW % NW != 0 && wave + NW * i >= NBW)  // uniform over the wave
+                break;
+            const int o = (wave + NW * i) * 512 + lane * 8;
+            const u32x4_t w = *reinterpret_cast<const u32x4_t *>(src + o);
+            u32x4_t h;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t v = ok ? w[j] : 0u;
+                wmax[i] = pk_max_u16(wmax[i], v & 0x7fff7fffu);
+                h[j] = __builtin_bit_cast(
+                    uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(v << 16) * wscale[i],
+                                                         __uint_as_float(v & 0xffff0000u) * wscale[i]));
+            }
+            *reinterpret_cast<u32x4_t *>(dst + o) = h;
+        }
     };
 
     f32x4_t acc[NT][MT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-            acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-
-    if (S > 0)
-        issue(0);
-    for (int s = 0; s < S; ++s) {
-        // this wave's stage-s blocks have landed (nothing else is in flight)
-        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
-        // all waves' blocks have landed and every wave's reads of the other
-        // buffer (stage s - 1) have returned
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (s + 1 < S)
-            issue(s + 1);
-        const uint16_t *ws = lds + (s & 1) * GW_BLOCKS * 512, *as = ws + NBW * 512;
-        u32x4_t wf[NT], af[MT][T];
+    auto fread = [&](int stage, u32x4_t(&wf)[NT], u32x4_t(&af)[MT][T]) {
+        const uint16_t *ws = lw + (stage & 1) * NBW * 512, *as = la + (stage % (P + 1)) * NBA * 512;
 #pragma unroll
         for (int i = 0; i < NT; ++i)
             wf[i] = *reinterpret_cast<const u32x4_t *>(&ws[(wn * NT + i) * 512 + lane * 8]);
@@ -367,107 +266,406 @@ __global__ __launch_bounds__(GW_THREADS, 4) void k_pf_gemm_wide(PfGemmArgs a) {
         for (int j = 0; j < MT; ++j)
 #pragma unroll
             for (int t = 0; t < T; ++t)
-                af[j][t] = *reinterpret_cast<const u32x4_t *>(&as[(t * (GW_M / 16) + wm * MT + j) * 512 + lane * 8]);
+                af[j][t] = *reinterpret_cast<const u32x4_t *>(&as[(t * (BM / 16) + wm * MT + j) * 512 + lane * 8]);
+    };
+    auto multiply = [&](const u32x4_t(&wf)[NT], const u32x4_t(&af)[MT][T]) {
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
             for (int i = 0; i < NT; ++i)
 #pragma unroll
                 for (int j = 0; j < MT; ++j)
-                    acc[i][j] = mfma16(wf[i], af[j][t], acc[i][j]);
-    }
+                    acc[i][j] = mfma16h(wf[i], af[j][t], acc[i][j]);
+    };
 
-    // lane holds C^T[n0 + wn WN + 16 i + 4 grp + v][m0 + wm WM + 16 j + col]
-    // (EPI_PARTIAL: of the split's partial sum, part[split][m][n])
-    static_assert(EPI == EPI_STORE || EPI == EPI_PARTIAL || EPI == EPI_SWIGLU, "stores only");
-    const int col = lane & 15, grp = lane >> 4;
-    if constexpr (SWI) {
-        // wave column wn < NWN / 2 holds gate, wn + NWN / 2 up of the same f
-        constexpr int HALF = NWN / 2, SLOT = NT * MT * 64;  // f32x4 per up wave
-        static_assert(NWM * HALF * SLOT * 16 <= (int)sizeof(lds), "exchange fits the stage buffers");
-        f32x4_t *xl = reinterpret_cast<f32x4_t *>(lds);
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // all reads of the stages done
-        if (wn >= HALF) {
+    for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+        for (int i = 0; i < NT; ++i)
 #pragma unroll
-                for (int j = 0; j < MT; ++j)
-                    xl[(wm * HALF + wn - HALF) * SLOT + (i * MT + j) * 64 + lane] = acc[i][j];
+            for (int j = 0; j < MT; ++j)
+                acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        if (S > 0) {
+            wload(0);
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+            wconvert(0);
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                aload(p);
+                wload(p + 1);
+            }
+            for (int s = 0; s < S; ++s) {
+                // This wave's activations of stage s and weights of stage s + 1
+                // have landed: at most the loads issued after them are in
+                // flight.  Then everyone's activations have, and the float16
+                // weights are there; every read of stage s - 1 has returned.
+                __builtin_amdgcn_s_waitcnt(wait_vmcnt((P - 1) * (APW + WPW)));
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                aload(s + P);
+                u32x4_t wf[NT], af[MT][T];
+                fread(s, wf, af);
+                wconvert(s + 1);
+                wload(s + 1 + P);  // into the block just converted
+                multiply(wf, af);
+            }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (wn >= HALF)
-            return;
-        const bool vec = (F & 3) == 0 && (a.x_term & 3) == 0 && (reinterpret_cast<uintptr_t>(a.xout) & 7) == 0;
+        __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+        __syncthreads();  // every wave is done with the stage buffers
+        if (pass)
+            break;
+        // weight rows outside the window of WSCALE: again with their own scales
+        uint32_t *flag = ymax + BM;
+        if (tid == 0)
+            *flag = 0;
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const int f = n0 + wn * WN + 16 * i + 4 * grp;
+        for (int i = 0; i < WPW; ++i) {
+            uint32_t m = max(wmax[i] & 0xffffu, wmax[i] >> 16);
+            m = max(m, (uint32_t)__shfl_xor((int)m, 16, 64));
+            m = max(m, (uint32_t)__shfl_xor((int)m, 32, 64));
+            wmax[i] = m;
+            if (!wide_ok(m))
+                *flag = 1;
+        }
+        __syncthreads();
+        const bool again = *flag;
+        __syncthreads();
+        if (!again)
+            break;
+#pragma unroll
+        for (int i = 0; i < WPW; ++i)
+            wscale[i] = row_scale(__uint_as_float(wmax[i] << 16), &winv[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < WPW; ++i)
+        if (grp == 0 && wave + NW * i < NBW)
+            wsc[(wave + NW * i) * 16 + col] = winv[i];
+    if constexpr (SWI)
+        for (int i = tid; i < BM; i += 64 * NW)
+            ymax[i] = 0;
+    __syncthreads();
+
+    // lane holds (C 2^..)^T[n0 + wn WN + 16 i + 4 grp + v][m0 + wm WM + 16 j + col]
+    // (EPI_PARTIAL: of the split's partial sum, part[split][m][n])
+    float rs[MT];
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
+        rs[j] = a.rs[min(m0 + wm * WM + 16 * j + col, M - 1)];
+    if constexpr (SWI) {
+        // Block rows 0-7 are gate, 8-15 up: lanes 0-31 hold gate, lanes 32-63
+        // up of the same eight f.  Swapping the lane halves of two tiles
+        // leaves gate and up of the first tile in lanes 0-31 and of the
+        // second in lanes 32-63.
+        float mx[MT];
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+            mx[j] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NT; i += 2) {
+            const int i2 = i + 1 < NT ? i + 1 : i;
+            const int ti = lane < 32 ? i : i2;
+            const int fl = wn * NT * 8 + 8 * ti + 4 * (grp & 1), f = n0 + fl;
+            const bool own = lane < 32 || i2 != i;
+            f32x4_t sg, su;
+            const int rb = (wn * NT + ti) * 16 + 4 * (grp & 1);
+            sg = *reinterpret_cast<const f32x4_t *>(&wsc[rb]);
+            su = *reinterpret_cast<const f32x4_t *>(&wsc[rb + 8]);
 #pragma unroll
             for (int j = 0; j < MT; ++j) {
                 const int m = m0 + wm * WM + 16 * j + col;
-                const f32x4_t up = xl[(wm * HALF + wn) * SLOT + (i * MT + j) * 64 + lane];
-                if (m >= M || f >= F)
-                    continue;
-                uint16_t t4[T][4];
+                f32x4_t y;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const float g = acc[i][j][v];
-                    uint16_t t3[T];
-                    split3(g / (1.0f + expf(-g)) * up[v], t3);
-#pragma unroll
-                    for (int q = 0; q < T; ++q)
-                        t4[q][v] = t3[q];
+                    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][j][v]),
+                                                                    __float_as_uint(acc[i2][j][v]), false, false);
+                    const float g = __uint_as_float(r[0]) * (rs[j] * sg[v]);
+                    const float up = __uint_as_float(r[1]) * (rs[j] * su[v]);
+                    y[v] = g / (1.0f + expf(-g)) * up;
                 }
-                uint16_t *o = a.xout + (int64_t)m * F + f;
-                if (vec && f + 3 < F) {
+                if (m >= M || f >= F || !own)
+                    continue;
 #pragma unroll
-                    for (int q = 0; q < T; ++q) {
-                        const u32x2_t w = {(uint32_t)t4[q][0] | ((uint32_t)t4[q][1] << 16),
-                                           (uint32_t)t4[q][2] | ((uint32_t)t4[q][3] << 16)};
-                        *reinterpret_cast<u32x2_t *>(o + q * a.x_term) = w;
-                    }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (f + v < F)
-#pragma unroll
-                            for (int q = 0; q < T; ++q)
-                                o[q * a.x_term + v] = t4[q][v];
-                }
+                for (int v = 0; v < 4; ++v)
+                    mx[j] = fmaxf(mx[j], fabsf(y[v]));
+                *reinterpret_cast<f32x4_t *>(a.C + (int64_t)m * F + f) = y;  // F % 8 == 0
             }
         }
+        // the tile's largest |y| of every row into slot tn of ymax
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+            atomicMax(&ymax[wm * WM + 16 * j + col], __float_as_uint(mx[j]));
+        __syncthreads();
+        for (int i = tid; i < BM; i += 64 * NW)
+            if (m0 + i < M)
+                a.amax[(int64_t)(m0 + i) * a.amax_ld + tn] = __uint_as_float(ymax[i]);
         return;
     }
     float *C = EPI == EPI_PARTIAL ? a.part + (int64_t)split * M * a.ldc : a.C;
     const bool vec = (a.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-        const int n = n0 + wn * WN + 16 * i + 4 * grp;
+        const int nl = wn * WN + 16 * i + 4 * grp, n = n0 + nl;
+        const f32x4_t sw = *reinterpret_cast<const f32x4_t *>(&wsc[nl]);
 #pragma unroll
         for (int j = 0; j < MT; ++j) {
             const int m = m0 + wm * WM + 16 * j + col;
             if (m >= M || n >= N)
                 continue;
+            f32x4_t v = acc[i][j] * (sw * rs[j]);
             float *c = C + (int64_t)m * a.ldc + n;
             if (vec && n + 3 < N) {
-                *reinterpret_cast<f32x4_t *>(c) = acc[i][j];
+                *reinterpret_cast<f32x4_t *>(c) = v;
             } else {
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (n + v < N)
-                        c[v] = acc[i][j][v];
+                for (int u = 0; u < 4; ++u)
+                    if (n + u < N)
+                        c[u] = v[u];
             }
         }
     }
 }
 
-// C[m][n] += part[0][m][n] + part[1][m][n] + ..., in split order.
-__global__ __launch_bounds__(256) void k_pf_split_sum(const float *part, int splits, int64_t stride, float *C,
-                                                      int64_t n_elems) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_elems; i += (int64_t)gridDim.x * 256) {
-        float v = part[i];
-        for (int s = 1; s < splits; ++s)
-            v += part[(int64_t)s * stride + i];
-        C[i] += v;
+// ---------------------------------------------------------------------------
+// GEMM for few rows (17 to 64): bound by the weight stream, with 2 M flops per
+// weight byte on top.  A work-group owns four tiles of 16 weight rows, over all
+// MB blocks of 16 activation rows; its NW waves take every NW-th 64-element
+// k-step and meet in LDS at the end, so nothing is shared and no wave waits
+// for another inside the loop (the tile kernel above spends 0.4 us per 32-k
+// stage on its barrier chain at these sizes, whatever the tile).  A wave loads
+// its weights coalesced (eight lanes per 128-byte row slice), transposes them
+// through a private LDS tile whose 16-byte chunks are XOR-swizzled by row,
+// and turns the fragments into float16.  The activation terms come in fragment
+// order (thin_off), each operand one contiguous 1 KB load.
+
+template <int EPI>
+__device__ __forceinline__ int thin_row(int t, int i, const PfThinArgs &a) {
+    if constexpr (EPI == EPI_QKV) {  // eight rotary pairs of one head
+        const int half = a.head_dim >> 1, per_head = half >> 3;
+        const int head = t / per_head, p = (t - head * per_head) * 8 + (i & 7);
+        return head * a.head_dim + (i < 8 ? p : half + p);
+    } else if constexpr (EPI == EPI_SWIGLU) {  // eight gate rows and their up rows
+        const int f = min(t * 8 + (i & 7), (a.N >> 1) - 1);
+        return i < 8 ? f : (a.N >> 1) + f;
+    } else {
+        return min(t * 16 + i, a.N - 1);
+    }
+}
+
+template <int EPI, int MB, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
+    constexpr int TN = 4, T = PF_TERMS;
+    constexpr int WL = TN * 16 * 64;          // halves of a wave's staging tile
+    constexpr int RC = MB * 16 + 1;           // pitch of the reduction rows
+    constexpr size_t SMEM_W = (size_t)NW * WL * 2, SMEM_R = (size_t)NW * 16 * RC * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_W > SMEM_R ? SMEM_W : SMEM_R];
+    __shared__ uint32_t rmax[TN * 16];
+    __shared__ float wsc[TN * 16];
+    __shared__ float fin[EPI == EPI_QKV || EPI == EPI_SWIGLU ? 16 * RC : 1];
+    __shared__ uint32_t ymax[EPI == EPI_SWIGLU ? MB * 16 : 1];
+    const int S = EPI == EPI_PARTIAL ? a.splits : 1;
+    const int grp = blockIdx.x / S, sp = blockIdx.x - grp * S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, kg = lane >> 4;
+    const int M = a.M, n_tiles = a.n_tiles;
+    uint16_t *wl = reinterpret_cast<uint16_t *>(smem) + wave * WL;
+    // load instruction ii of tile j reads rows 8 ii + lane / 8, 16-byte chunk
+    // lane % 8 of the k-step's 128-byte slice
+    const int lrow = lane >> 3, lch = lane & 7;
+    uint32_t woff[TN][2];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int ii = 0; ii < 2; ++ii)
+            woff[j][ii] = ((uint32_t)thin_row<EPI>(min(grp * TN + j, n_tiles - 1), 8 * ii + lrow, a) * (uint32_t)a.K +
+                           lch * 8) * 2;  // bytes (below 2^32: checked by the launcher)
+    const int KS_all = a.K >> 6;
+    const int ks0 = (int)(((int64_t)KS_all * sp) / S), ks1 = (int)(((int64_t)KS_all * (sp + 1)) / S);
+
+    f32x4_t acc[TN][MB];
+    float wscale[TN];
+    uint32_t wmax[TN];
+    u32x4_t wv[TN][2], xv[2][MB][T];
+    // (a uniform base and a 32-bit offset per lane)
+    auto load_w = [&](int q) {
+        const char *base = reinterpret_cast<const char *>(a.W) + ((int64_t)q << 7);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii)
+                wv[j][ii] =
+                    __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(base + woff[j][ii]));
+    };
+    const uint32_t xoff = lane * 16;
+    auto load_x = [&](int q, int i) {
+        const char *base = reinterpret_cast<const char *>(a.X) + (int64_t)(2 * q + i) * (T * MB * 1024);
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                xv[i][b][t] = *reinterpret_cast<const u32x4_t *>(base + (t * MB + b) * 1024 + xoff);
+    };
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+        wscale[j] = WSCALE;
+    for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            wmax[j] = 0;
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+                acc[j][b] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        int q = ks0 + wave;
+        if (q < ks1) {
+            load_w(q);
+            load_x(q, 0);
+            load_x(q, 1);
+        }
+        for (; q < ks1; q += NW) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int ii = 0; ii < 2; ++ii) {
+                    const int row = 8 * ii + lrow;
+                    *reinterpret_cast<u32x4_t *>(wl + j * 1024 + row * 64 + ((lch ^ (row & 7)) << 3)) = wv[j][ii];
+                }
+            const bool more = q + NW < ks1;
+            if (more)
+                load_w(q + NW);
+            // the staging tile is private to this wave, whose LDS accesses run
+            // in program order; the fences only keep the compiler from
+            // reordering them
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                u32x4_t wf[TN];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(wl + j * 1024 + r16 * 64 +
+                                                                         (((4 * i + kg) ^ (r16 & 7)) << 3));
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        wmax[j] = pk_max_u16(wmax[j], v[u] & 0x7fff7fffu);
+                        wf[j][u] = __builtin_bit_cast(
+                            uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(v[u] << 16) * wscale[j],
+                                                                 __uint_as_float(v[u] & 0xffff0000u) * wscale[j]));
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int b = 0; b < MB; ++b)
+                            acc[j][b] = mfma16h(wf[j], xv[i][b][t], acc[j][b]);
+                // one set of registers per half step: its next activations
+                // (cache hits) are requested once its MFMAs have read these
+                __builtin_amdgcn_sched_barrier(0);
+                if (more)
+                    load_x(q + NW, i);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        if (pass)
+            break;
+        // largest magnitude of every weight row over the waves
+        if (tid < TN * 16)
+            rmax[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            atomicMax(&rmax[16 * j + r16], max(wmax[j] & 0xffffu, wmax[j] >> 16));
+        __syncthreads();
+        const bool again = __syncthreads_or(tid < TN * 16 && !wide_ok(rmax[tid]));
+        if (tid < TN * 16) {
+            float inv = 1.0f / WSCALE;
+            if (again)
+                (void)row_scale(__uint_as_float(rmax[tid] << 16), &inv);
+            wsc[tid] = inv;
+        }
+        if (!again)
+            break;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            float inv;
+            wscale[j] = row_scale(__uint_as_float(rmax[16 * j + r16] << 16), &inv);
+        }
+    }
+    if constexpr (EPI == EPI_SWIGLU)
+        if (tid < MB * 16)
+            ymax[tid] = 0;
+
+    // acc: lane holds rows 4 kg + v of tile j, activation row 16 b + r16.
+    // Tile by tile the waves' sums meet in LDS and are added in wave order.
+    float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int t = grp * TN + j;
+        if (t >= n_tiles)
+            break;  // uniform over the work-group
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                red[(wave * 16 + 4 * kg + v) * RC + 16 * b + r16] = acc[j][b][v];
+        __syncthreads();
+        // consecutive threads take consecutive weight rows of one activation row
+        for (int o = tid; o < 16 * M; o += 64 * NW) {
+            const int ni = o & 15, m = o >> 4;
+            float v = red[ni * RC + m];
+#pragma unroll
+            for (int w = 1; w < NW; ++w)
+                v += red[(w * 16 + ni) * RC + m];
+            v = v * wsc[16 * j + ni] * a.rs[m];
+            if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
+                fin[ni * RC + m] = v;
+            } else {
+                const int n = t * 16 + ni;
+                float *C = EPI == EPI_PARTIAL ? a.C + (int64_t)sp * M * a.ldc : a.C;
+                if (n < a.N)
+                    C[(int64_t)m * a.ldc + n] = v;
+            }
+        }
+        if constexpr (EPI == EPI_SWIGLU) {
+            __syncthreads();
+            for (int o = tid; o < 8 * M; o += 64 * NW) {
+                const int i = o & 7, m = o >> 3, f = t * 8 + i;
+                const float g = fin[i * RC + m], y = g / (1.0f + expf(-g)) * fin[(i + 8) * RC + m];
+                a.C[(int64_t)m * a.ldc + f] = y;  // F is a multiple of 8
+                atomicMax(&ymax[m], __float_as_uint(fabsf(y)));
+            }
+        } else if constexpr (EPI == EPI_QKV) {
+            __syncthreads();
+            const int dh = a.head_dim, half = dh >> 1, per_head = half >> 3;
+            const int head = t / per_head, p0 = (t - head * per_head) * 8;
+            for (int o = tid; o < 8 * M; o += 64 * NW) {
+                const int i = o & 7, m = o >> 3, e = p0 + i, pos = a.start + m;
+                float y0 = fin[i * RC + m], y1 = fin[(i + 8) * RC + m];
+                if (head < a.n_heads + a.n_kv_heads) {
+                    const float2 cs = a.rope[(int64_t)pos * half + e];
+                    const float r0 = y0 * cs.x - y1 * cs.y;
+                    const float r1 = y1 * cs.x + y0 * cs.y;
+                    y0 = r0;
+                    y1 = r1;
+                }
+                if (head < a.n_heads) {
+                    float *qo = a.C + (int64_t)m * a.ldc + head * dh + e;
+                    qo[0] = y0;
+                    qo[half] = y1;
+                } else {
+                    const bool is_k = head < a.n_heads + a.n_kv_heads;
+                    const int g = head - a.n_heads - (is_k ? 0 : a.n_kv_heads);
+                    uint16_t *c = (is_k ? a.kcache : a.vcache) + (int64_t)g * a.kv_head_stride + (int64_t)pos * dh + e;
+                    c[0] = bf16_rne_bits(y0);
+                    c[half] = bf16_rne_bits(y1);
+                }
+            }
+        }
+    }
+    if constexpr (EPI == EPI_SWIGLU) {
+        __syncthreads();
+        if (tid < M)
+            a.amax[(int64_t)tid * a.amax_ld + grp] = __uint_as_float(ymax[tid]);
     }
 }
 
@@ -624,30 +822,23 @@ __global__ __launch_bounds__(256) void k_pf_attn(PfAttnArgs a) {
         }
     }
 
-    // lane holds O^T[16 et + 4 grp + v][query col]; the terms of 4
-    // consecutive elements go out as one 8-byte store per term
-    if (qok) {
-        const float inv = 1.0f / l_run;
+    // lane holds O^T[16 et + 4 grp + v][query col]
+    const float inv = 1.0f / l_run;
+    float mx = 0.0f;
 #pragma unroll
-        for (int et = 0; et < ET; ++et) {
-            uint16_t t4[T][4];
+    for (int et = 0; et < ET; ++et) {
+        oacc[et] *= inv;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                uint16_t s[T];
-                split3(oacc[et][v] * inv, s);
-#pragma unroll
-                for (int i = 0; i < T; ++i)
-                    t4[i][v] = s[i];
-            }
-            const int64_t e = (int64_t)rq * a.ldo + (int64_t)head * DH + 16 * et + 4 * grp;
-#pragma unroll
-            for (int i = 0; i < T; ++i) {
-                const u32x2_t w = {(uint32_t)t4[i][0] | ((uint32_t)t4[i][1] << 16),
-                                   (uint32_t)t4[i][2] | ((uint32_t)t4[i][3] << 16)};
-                *reinterpret_cast<u32x2_t *>(a.out + i * a.out_term + e) = w;
-            }
-        }
+        for (int v = 0; v < 4; ++v)
+            mx = fmaxf(mx, fabsf(oacc[et][v]));
+        if (qok)
+            *reinterpret_cast<f32x4_t *>(a.out + (int64_t)rq * a.ldo + (int64_t)head * DH + 16 * et + 4 * grp) =
+                oacc[et];
     }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (qok && grp == 0)
+        a.amax[(int64_t)rq * a.amax_ld + head] = mx;
 }
 
 // ---------------------------------------------------------------------------
@@ -661,80 +852,129 @@ __global__ __launch_bounds__(256) void k_pf_embed(const uint16_t *E, int d, cons
         o[k] = bf_to_f(e[k]);
 }
 
-__global__ __launch_bounds__(256) void k_pf_norm_split(const float *h, int K, const uint16_t *gain, float eps,
-                                                       uint16_t *out, int64_t out_term) {
-    __shared__ float red[4];
-    const int m = blockIdx.x, tid = threadIdx.x;
-    const float *x = h + (int64_t)m * K;
-    float ss = 0.0f;
-    for (int k = 4 * tid; k < K; k += 4 * 256) {
-        const f32x4_t v = *reinterpret_cast<const f32x4_t *>(x + k);
+__device__ __forceinline__ void load8bf(const uint16_t *p, float (&x)[8]) {
+    const u32x4_t w = *reinterpret_cast<const u32x4_t *>(p);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            ss = fmaf(v[j], v[j], ss);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        ss += __shfl_xor(ss, o, 64);
-    if ((tid & 63) == 0)
-        red[tid >> 6] = ss;
-    __syncthreads();
-    const float inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)K + eps);
-    for (int k = 8 * tid; k < K; k += 8 * 256) {
-        float u[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            u[j] = bf_to_f(gain[k + j]) * (x[k + j] * inv);
-        u32x4_t t[X_TERMS];
-        split8(u, t);
-#pragma unroll
-        for (int i = 0; i < X_TERMS; ++i)
-            *reinterpret_cast<u32x4_t *>(out + i * out_term + (int64_t)m * K + k) = t[i];
+    for (int j = 0; j < 4; ++j) {
+        x[2 * j] = __uint_as_float(w[j] << 16);
+        x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
     }
 }
 
-// h[m] += the split partials (in split order), then g * h / rms(h) as terms:
-// the sums of k_pf_split_sum and the norm of k_pf_norm_split in one kernel
-// (the second pass re-reads elements the work-group wrote before the
-// barrier).
-__global__ __launch_bounds__(256) void k_pf_fold_norm_split(float *h, const float *part, int splits, int64_t stride,
-                                                            int K, const uint16_t *gain, float eps, uint16_t *out,
-                                                            int64_t out_term) {
-    __shared__ float red[4];
+// The terms of row m, x[0..K) (K a multiple of 8; x(k) gives elements k .. k + 7
+// times the row's scale): row-major, zero up to the next multiple of 32
+// (blocks 0), or in fragment order.
+template <typename F>
+__device__ __forceinline__ void store_terms(int m, int K, uint16_t *out, int64_t out_term, int blocks, F x) {
+    const int ldk = pf_pitch(K);
+    for (int k = 8 * threadIdx.x; k < ldk; k += 8 * 256) {
+        u32x4_t h = {0u, 0u, 0u, 0u}, l = h;
+        if (k < K) {
+            float u[8];
+            x(k, u);
+            split_f16x8(u, h, l);
+        }
+        uint16_t *o = out + (blocks ? thin_off(0, m, k, blocks) : (int64_t)m * ldk + k);
+        *reinterpret_cast<u32x4_t *>(o) = h;
+        *reinterpret_cast<u32x4_t *>(o + (blocks ? (int64_t)blocks << 9 : out_term)) = l;
+    }
+}
+
+__device__ __forceinline__ void load8f(const float *p, float (&x)[8]) {
+    const f32x4_t a = reinterpret_cast<const f32x4_t *>(p)[0], b = reinterpret_cast<const f32x4_t *>(p)[1];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        x[j] = a[j];
+        x[4 + j] = b[j];
+    }
+}
+
+// g * h / rms(h) of every row as float16 terms, with the row's scale.  With
+// splits > 0 the partials of a split residual update are added into h first,
+// in split order: h[m] += part[0][m] + part[1][m] + ...
+__global__ __launch_bounds__(256) void k_pf_norm_split(float *h, const float *part, int splits, int64_t stride, int K,
+                                                       const uint16_t *gain, float eps, uint16_t *out, int64_t out_term,
+                                                       int blocks, float *rs) {
+    __shared__ float red[2][4];
     const int m = blockIdx.x, tid = threadIdx.x;
     float *x = h + (int64_t)m * K;
     const float *p = part + (int64_t)m * K;
-    float ss = 0.0f;
+    float ss = 0.0f, mx = 0.0f;
     // 16-byte loads (K is a multiple of 8): with 4-byte loads this pass over
     // the row and three partial planes took 40 us per 13B call
-    for (int k = 4 * tid; k < K; k += 4 * 256) {
-        f32x4_t v = *reinterpret_cast<const f32x4_t *>(p + k);
-        for (int s = 1; s < splits; ++s)
-            v += *reinterpret_cast<const f32x4_t *>(p + (int64_t)s * stride + k);
-        const f32x4_t hn = *reinterpret_cast<const f32x4_t *>(x + k) + v;
-        *reinterpret_cast<f32x4_t *>(x + k) = hn;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            ss = fmaf(hn[j], hn[j], ss);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        ss += __shfl_xor(ss, o, 64);
-    if ((tid & 63) == 0)
-        red[tid >> 6] = ss;
-    __syncthreads();
-    const float inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)K + eps);
     for (int k = 8 * tid; k < K; k += 8 * 256) {
-        float u[8];
+        float v[8], g[8];
+        load8f(x + k, v);
+        if (splits) {
+            float w[8];
+            load8f(p + k, w);
+            for (int s = 1; s < splits; ++s) {
+                float w2[8];
+                load8f(p + (int64_t)s * stride + k, w2);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    w[j] += w2[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                v[j] += w[j];
+            reinterpret_cast<f32x4_t *>(x + k)[0] = f32x4_t{v[0], v[1], v[2], v[3]};
+            reinterpret_cast<f32x4_t *>(x + k)[1] = f32x4_t{v[4], v[5], v[6], v[7]};
+        }
+        load8bf(gain + k, g);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            ss = fmaf(v[j], v[j], ss);
+            mx = fmaxf(mx, fabsf(g[j] * v[j]));
+        }
+    }
+    ss = wave_sum_all(ss);
+    mx = wave_max_all(mx);
+    if ((tid & 63) == 0) {
+        red[0][tid >> 6] = ss;
+        red[1][tid >> 6] = mx;
+    }
+    __syncthreads();
+    const float inv = 1.0f / sqrtf((red[0][0] + red[0][1] + red[0][2] + red[0][3]) / (float)K + eps);
+    const float amax = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3])) * inv;
+    float rinv;
+    const float sc = row_scale(amax, &rinv);
+    if (tid == 0)
+        rs[m] = rinv;
+    // (re-reads what this thread wrote or read above)
+    store_terms(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
+        float v[8], g[8];
+        load8f(x + k, v);
+        load8bf(gain + k, g);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            u[j] = bf_to_f(gain[k + j]) * (x[k + j] * inv);
-        u32x4_t t[X_TERMS];
-        split8(u, t);
+            u[j] = g[j] * (v[j] * inv) * sc;
+    });
+}
+
+// The terms of every row of x [M][K] (the attention output or the MLP
+// activation), whose largest magnitude is the largest of its amax slots.
+__global__ __launch_bounds__(256) void k_pf_split(const float *x, int K, const float *amax, int slots, int amax_ld,
+                                                  uint16_t *out, int64_t out_term, int blocks, float *rs) {
+    __shared__ float red[4];
+    const int m = blockIdx.x, tid = threadIdx.x;
+    float mx = 0.0f;
+    for (int i = tid; i < slots; i += 256)
+        mx = fmaxf(mx, amax[(int64_t)m * amax_ld + i]);
+    mx = wave_max_all(mx);
+    if ((tid & 63) == 0)
+        red[tid >> 6] = mx;
+    __syncthreads();
+    float rinv;
+    const float sc = row_scale(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), &rinv);
+    if (tid == 0)
+        rs[m] = rinv;
+    store_terms(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
+        load8f(x + (int64_t)m * K + k, u);
 #pragma unroll
-        for (int i = 0; i < X_TERMS; ++i)
-            *reinterpret_cast<u32x4_t *>(out + i * out_term + (int64_t)m * K + k) = t[i];
-    }
+        for (int j = 0; j < 8; ++j)
+            u[j] *= sc;
+    });
 }
 
 __global__ __launch_bounds__(256) void k_pf_rope_kv(const float *qkv, int start, const float2 *rope, int H, int KVH,
@@ -780,24 +1020,6 @@ __global__ __launch_bounds__(256) void k_pf_rope_kv(const float *qkv, int start,
     }
 }
 
-__global__ __launch_bounds__(256) void k_pf_swiglu_split(const float *gu, int F, uint16_t *out, int64_t out_term) {
-    const int m = blockIdx.x;
-    const float *x = gu + (int64_t)m * 2 * F;
-    for (int f = 8 * threadIdx.x; f < F; f += 8 * 256) {
-        float y[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float g = x[f + j], u = x[F + f + j];
-            y[j] = g / (1.0f + expf(-g)) * u;
-        }
-        u32x4_t t[X_TERMS];
-        split8(y, t);
-#pragma unroll
-        for (int i = 0; i < X_TERMS; ++i)
-            *reinterpret_cast<u32x4_t *>(out + i * out_term + (int64_t)m * F + f) = t[i];
-    }
-}
-
 }  // namespace
 
 hipError_t launch_pf_embed(const uint16_t *emb, int d, const int32_t *tokens, int M, float *h, hipStream_t s) {
@@ -805,152 +1027,176 @@ hipError_t launch_pf_embed(const uint16_t *emb, int d, const int32_t *tokens, in
     return hipGetLastError();
 }
 
-hipError_t launch_pf_norm_split(const float *h, int K, int M, const uint16_t *gain, float eps, uint16_t *out,
-                                int64_t out_term, hipStream_t s) {
-    if (K % 8)
+hipError_t launch_pf_norm_split(float *h, const float *part, int splits, int K, int M, const uint16_t *gain, float eps,
+                                const PfTerms &t, hipStream_t s) {
+    if (K % 8 || (t.blocks && K % 32) || splits < 0 || splits > PF_MAX_SPLITS)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_norm_split, dim3(M), dim3(256), 0, s, h, K, gain, eps, out, out_term);
+    hipLaunchKernelGGL(k_pf_norm_split, dim3(M), dim3(256), 0, s, h, part, splits, (int64_t)M * K, K, gain, eps, t.x,
+                       t.term, t.blocks, t.rs);
     return hipGetLastError();
 }
 
-hipError_t launch_pf_fold_norm_split(float *h, const float *part, int splits, int K, int M, const uint16_t *gain,
-                                     float eps, uint16_t *out, int64_t out_term, hipStream_t s) {
-    if (K % 8 || splits < 1 || splits > PF_MAX_SPLITS)
+hipError_t launch_pf_split(const float *x, int K, int M, const float *amax, int slots, int amax_ld, const PfTerms &t,
+                           hipStream_t s) {
+    if (K % 8 || (t.blocks && K % 32))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_fold_norm_split, dim3(M), dim3(256), 0, s, h, part, splits, (int64_t)M * K, K, gain, eps,
-                       out, out_term);
+    hipLaunchKernelGGL(k_pf_split, dim3(M), dim3(256), 0, s, x, K, amax, slots, amax_ld, t.x, t.term, t.blocks, t.rs);
     return hipGetLastError();
 }
 
-hipError_t launch_pf_split_sum(const float *part, int splits, int64_t n, float *C, hipStream_t s) {
-    if (splits < 1 || splits > PF_MAX_SPLITS || n < 1)
+namespace {
+
+template <int BN, int BM, int NWN, int NWM, int P, int WPS>
+hipError_t launch_tile(const PfGemmArgs &a, int epi, hipStream_t s) {
+    const int bc = epi == EPI_SWIGLU ? BN / 2 : BN, nc = epi == EPI_SWIGLU ? a.N / 2 : a.N;
+    const int tiles = ((nc + bc - 1) / bc) * ((a.M + BM - 1) / BM) * a.splits;
+    const dim3 grid(8 * ((tiles + 7) / 8)), block(64 * NWN * NWM);
+    if (epi == EPI_STORE)
+        hipLaunchKernelGGL((k_pf_gemm<EPI_STORE, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
+    else if (epi == EPI_PARTIAL)
+        hipLaunchKernelGGL((k_pf_gemm<EPI_PARTIAL, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
+    else if (epi == EPI_SWIGLU)
+        hipLaunchKernelGGL((k_pf_gemm<EPI_SWIGLU, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
+    else
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_split_sum, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)), dim3(256), 0, s, part,
-                       splits, n, C, n);
     return hipGetLastError();
 }
 
-hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *fold) {
-    if (fold)
-        *fold = 0;
-    if (a.M < 1 || a.N < 1 || a.K < 8 || a.K % 8 || a.lda % 8 || a.M > PF_ROWS)
+template <int EPI, int NW>
+hipError_t launch_thin_mb(const PfThinArgs &a, hipStream_t s) {
+    const dim3 grid((a.n_tiles + 3) / 4 * (EPI == EPI_PARTIAL ? a.splits : 1)), block(64 * NW);
+    switch ((a.M + 15) / 16) {
+    case 1:
+    case 2:
+        hipLaunchKernelGGL((k_pf_thin<EPI, 2, NW>), grid, block, 0, s, a);
+        break;
+    case 3:
+        hipLaunchKernelGGL((k_pf_thin<EPI, 3, NW>), grid, block, 0, s, a);
+        break;
+    case 4:
+        hipLaunchKernelGGL((k_pf_thin<EPI, 4, NW>), grid, block, 0, s, a);
+        break;
+    default:
         return hipErrorInvalidValue;
-    if (epi == EPI_SWIGLU) {
-        // gate/up: the SwiGLU in the wide kernel's epilogue when the launch
-        // is wide (xout must not overlap A: other work-groups still read
-        // it), else the product into C and a separate SwiGLU kernel.  Same
-        // box, 13B prefill: 72.9 -> 72.4 ms.
-        const int F = a.N / 2;
-        if (a.N % 2 || F % 8 || !a.xout)
-            return hipErrorInvalidValue;
-        const int TMw = (a.M + GW_M - 1) / GW_M;
-        const int t256 = TMw * ((F + 127) / 128), t224 = TMw * ((F + 111) / 112);
-        if (t256 >= GW_MIN_TILES && a.K % GB_K == 0) {
-            PfGemmArgs b = a;
-            b.splits = 1;
-            if ((int64_t)((t224 + 255) / 256) * 224 < (int64_t)((t256 + 255) / 256) * 256)
-                hipLaunchKernelGGL((k_pf_gemm_wide<EPI_SWIGLU, 224>), dim3(8 * ((t224 + 7) / 8)), dim3(GW_THREADS), 0, s,
-                                   b);
-            else
-                hipLaunchKernelGGL((k_pf_gemm_wide<EPI_SWIGLU, 256>), dim3(8 * ((t256 + 7) / 8)), dim3(GW_THREADS), 0, s,
-                                   b);
-            return hipGetLastError();
-        }
-        const hipError_t e = launch_pf_gemm(a, EPI_STORE, s);
-        if (e != hipSuccess)
-            return e;
-        return launch_pf_swiglu_split(a.C, F, a.M, a.xout, a.x_term, s);
     }
-    const int tiles = ((a.N + GB_N - 1) / GB_N) * ((a.M + GB_M - 1) / GB_M);
-    // Wide layers (at least 128 tiles of 256 x 256) take the direct-to-LDS
-    // kernel.  Both kernels fill the same fraction of the last round (one
-    // 256 x 256 work-group per CU against two of 256 x 128); measured with
-    // the 256 x 128 kernel's time first (us): 1023 rows, 13B QKV 509 -> 448,
-    // gate/up 959 -> 857, 7B QKV 368 -> 335, 70B QKV 653 -> 599; 511 rows,
-    // 7B gate/up 353 -> 311, 70B gate/up 1426 -> 1307.  With fewer tiles
-    // (the QKV layers at 511 rows: 80-120 tiles) the 256 x 128 kernel stays
-    // faster (13B 334 against 354).
-    const int wide_tiles = ((a.N + GB_N - 1) / GB_N) * ((a.M + GW_M - 1) / GW_M);
-    if (wide_tiles >= GW_MIN_TILES && a.K % GB_K == 0 && epi == EPI_STORE) {
-        PfGemmArgs b = a;
-        b.splits = 1;
-        // Tiles 224 wide when that takes fewer tile-widths of rounds on 256
-        // CUs: a round lasts about as long as a tile is wide, and 13B gate/up
-        // (1023 rows) is 432 tiles of 256 (1.7 rounds) or 496 of 224 (1.9).
-        const int tiles224 = ((a.N + 223) / 224) * ((a.M + GW_M - 1) / GW_M);
-        const int64_t cost256 = (int64_t)((wide_tiles + 255) / 256) * 256;
-        const int64_t cost224 = (int64_t)((tiles224 + 255) / 256) * 224;
-        if (cost224 < cost256)
-            hipLaunchKernelGGL((k_pf_gemm_wide<EPI_STORE, 224>), dim3(8 * ((tiles224 + 7) / 8)), dim3(GW_THREADS), 0, s,
-                               b);
-        else
-            hipLaunchKernelGGL((k_pf_gemm_wide<EPI_STORE, 256>), dim3(8 * ((wide_tiles + 7) / 8)), dim3(GW_THREADS), 0,
-                               s, b);
-        return hipGetLastError();
+    return hipGetLastError();
+}
+
+template <int NW>
+hipError_t launch_thin_nw(const PfThinArgs &a, int epi, hipStream_t s) {
+    switch (epi) {
+    case EPI_STORE:
+        return launch_thin_mb<EPI_STORE, NW>(a, s);
+    case EPI_PARTIAL:
+        return launch_thin_mb<EPI_PARTIAL, NW>(a, s);
+    case EPI_SWIGLU:
+        return launch_thin_mb<EPI_SWIGLU, NW>(a, s);
+    case EPI_QKV:
+        return launch_thin_mb<EPI_QKV, NW>(a, s);
+    default:
+        return hipErrorInvalidValue;
     }
-    // wide layers (at least one tile per CU): 4 x 2 waves, one stage in
-    // flight; narrow ones: split residual updates (below), else 2 x 4 waves
-    // with two stages in flight
-    if (tiles >= 256) {
-        PfGemmArgs b = a;
-        b.splits = 1;
-        const dim3 grid(8 * ((tiles + 7) / 8)), block(G_THREADS);
-        if (epi == EPI_STORE)
-            hipLaunchKernelGGL((k_pf_gemm<EPI_STORE, 4, 2, 1>), grid, block, 0, s, b);
-        else if (epi == EPI_RESID)
-            hipLaunchKernelGGL((k_pf_gemm<EPI_RESID, 4, 2, 1>), grid, block, 0, s, b);
-        else
-            return hipErrorInvalidValue;
-        return hipGetLastError();
-    }
-    // Residual updates split the reduction over as many work-groups as fit
-    // in one round: the 4 x 2-wave kernel runs two work-groups per CU, so up
-    // to 512 (13B output and down projections: 160 tiles, 3 splits; at
-    // least 16 stages per split).  Other narrow layers run unsplit.
-    int splits = 1;
-    bool wide_split = false;
-    if (epi == EPI_RESID && a.part) {
-        splits = std::min(PF_MAX_SPLITS, 512 / tiles);
-        while (splits > 1 && a.K < splits * GB_K * 16)
-            --splits;
-        // The same split on 256 x 256 tiles (one work-group per CU) when it
-        // keeps at least 160 CUs busy: 1023 rows, 13B O 185 -> 168 us, down
-        // 462 -> 436; 511 rows, 70B O 221 -> 197, down 775 -> 684.  At the
-        // 7B shape (511 rows, 128 work-groups) the 256 x 128 tiles stay
-        // faster (O 76 against 86 us).
-        int ws = std::min(PF_MAX_SPLITS, 256 / std::max(wide_tiles, 1));
-        while (ws > 1 && a.K < ws * GB_K * 16)
-            --ws;
-        if (a.K % GB_K == 0 && ws > 1 && wide_tiles * ws >= GW_MIN_SPLIT_GROUPS) {
-            splits = ws;
-            wide_split = true;
+}
+
+}  // namespace
+
+namespace {
+
+// The tiles of k_pf_gemm: weight rows, activation rows, and the time of one
+// 32-k stage of a work-group (ns, one work-group per CU with the chip full;
+// 13B shapes, random operands).  The larger tiles read fewer operand bytes
+// per product: 256 x 256 multiplies 2.3 times as fast per CU as 128 x 64.
+struct PfTile {
+    int bn, bm, ns;
+};
+constexpr PfTile PF_TILES[] = {{256, 256, 1820}, {256, 128, 1120}, {128, 128, 820}, {128, 64, 550}};
+
+// The tile and the split of the reduction with the least time by that table:
+// rounds of one work-group per CU, times the stages of a split, plus the
+// writing and reading of the partial sums at 5 TB/s.
+void pick_tile(const PfGemmArgs &a, int epi, int *tile, int *splits) {
+    const int stages = (a.K + 31) / 32;
+    // partial planes: PF_MAX_SPLITS of them, and in all 4 x PF_ROWS rows
+    const int most = epi == EPI_RESID ? std::min(PF_MAX_SPLITS, PF_PART_ROWS / a.M) : 1;
+    double best = 0.0;
+    *tile = -1;
+    for (int i = 0; i < 4; ++i) {
+        const PfTile &t = PF_TILES[i];
+        const int bc = epi == EPI_SWIGLU ? t.bn / 2 : t.bn, nc = epi == EPI_SWIGLU ? a.N / 2 : a.N;
+        const int64_t tiles = (int64_t)((nc + bc - 1) / bc) * ((a.M + t.bm - 1) / t.bm);
+        for (int s = 1; s <= most && (s == 1 || stages >= 8 * s); ++s) {
+            const double rounds = (double)((tiles * s + 255) / 256);
+            const double ns = rounds * ((stages + s - 1) / s) * t.ns + (epi == EPI_RESID ? s * 8.0e-3 / 5 * a.M * a.N : 0.0);
+            if (*tile < 0 || ns < best) {
+                best = ns;
+                *tile = i;
+                *splits = s;
+            }
         }
     }
+}
+
+}  // namespace
+
+hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out) {
+    if (a.M < 1 || a.N < 1 || a.K < 8 || a.K % 8 || a.lda != pf_pitch(a.K) || a.M > PF_ROWS || !a.rs)
+        return hipErrorInvalidValue;
+    if (epi == EPI_SWIGLU ? (a.N % 16 || !a.amax || !out) : epi == EPI_RESID ? (!a.part || !out) : epi != EPI_STORE)
+        return hipErrorInvalidValue;
     PfGemmArgs b = a;
-    b.splits = splits;
-    const dim3 grid(8 * ((tiles * b.splits + 7) / 8)), block(G_THREADS);
-    if (splits > 1) {
-        if (wide_split)
-            hipLaunchKernelGGL((k_pf_gemm_wide<EPI_PARTIAL, 256>), dim3(8 * ((wide_tiles * splits + 7) / 8)),
-                               dim3(GW_THREADS), 0, s, b);
-        else
-            hipLaunchKernelGGL((k_pf_gemm<EPI_PARTIAL, 4, 2, 1>), grid, block, 0, s, b);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-        if (fold && a.ldc == a.N) {
-            *fold = splits;  // the next norm adds the partials
-            return hipSuccess;
-        }
-        return launch_pf_split_sum(a.part, splits, (int64_t)a.M * a.ldc, a.C, s);
-    } else if (epi == EPI_STORE) {
-        hipLaunchKernelGGL((k_pf_gemm<EPI_STORE, 2, 4, 2>), grid, block, 0, s, b);
-    } else if (epi == EPI_RESID) {
-        hipLaunchKernelGGL((k_pf_gemm<EPI_RESID, 2, 4, 2>), grid, block, 0, s, b);
-    } else {
-        return hipErrorInvalidValue;
+    int tile = 0;
+    pick_tile(a, epi, &tile, &b.splits);
+    if (epi == EPI_RESID)
+        *out = b.splits;
+    if (epi == EPI_SWIGLU)
+        *out = (a.N + PF_TILES[tile].bn - 1) / PF_TILES[tile].bn;
+    const int e = epi == EPI_RESID ? EPI_PARTIAL : epi;
+    switch (tile) {
+    case 0:
+        return launch_tile<256, 256, 4, 4, 2, 4>(b, e, s);
+    case 1:
+        return launch_tile<256, 128, 4, 2, 2, 2>(b, e, s);
+    case 2:
+        return launch_tile<128, 128, 4, 2, 2, 2>(b, e, s);
+    default:
+        return launch_tile<128, 64, 4, 2, 3, 2>(b, e, s);
     }
-    return hipGetLastError();
+}
+
+bool pf_thin_ok(int M, int64_t N, int K) { return M <= PF_THIN_ROWS && K % 64 == 0 && N * K < ((int64_t)1 << 31); }
+
+hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out) {
+    PfThinArgs a = a0;
+    if (a.M < 1 || a.N < 1 || !pf_thin_ok(a.M, a.N, a.K) || !a.rs)
+        return hipErrorInvalidValue;
+    a.splits = 1;
+    if (epi == EPI_SWIGLU) {
+        if (a.N % 16 || !a.amax || !out)
+            return hipErrorInvalidValue;
+        a.n_tiles = a.N / 16;
+        *out = (a.n_tiles + 3) / 4;
+    } else if (epi == EPI_QKV) {
+        if ((a.head_dim / 2) % 8)
+            return hipErrorInvalidValue;
+        a.n_tiles = a.N / 16;
+    } else {
+        a.n_tiles = (a.N + 15) / 16;
+    }
+    const int groups = (a.n_tiles + 3) / 4;
+    if (epi == EPI_RESID) {
+        if (!out)
+            return hipErrorInvalidValue;
+        // output projections: as many splits of the reduction as fill the CUs
+        // with one work-group of eight waves (13B, 33 rows, 80 groups: O 22.3,
+        // 17.9 and 26.5 us with 2, 3 and 4 splits; down 46.4, 35.5 and 51.1)
+        a.splits = std::max(1, std::min({PF_MAX_SPLITS, 256 / groups, a.K / 512}));
+        *out = a.splits;
+        epi = EPI_PARTIAL;
+    }
+    // Eight waves where one work-group per CU takes the layer, four where two
+    // fit on many CUs (33 rows: 13B QKV, 240 groups, 41.2 against 43.6 us;
+    // gate/up, 432 groups, 75.0 against 70.9).
+    return groups * a.splits <= 256 ? launch_thin_nw<8>(a, epi, s) : launch_thin_nw<4>(a, epi, s);
 }
 
 hipError_t launch_pf_rope_kv(const float *qkv, int M, int start, const float2 *rope, int H, int KVH, int dh,
@@ -979,13 +1225,6 @@ hipError_t launch_pf_attention(const PfAttnArgs &a, hipStream_t s) {
     default:
         return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_pf_swiglu_split(const float *gu, int F, int M, uint16_t *out, int64_t out_term, hipStream_t s) {
-    if (F % 8)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_swiglu_split, dim3(M), dim3(256), 0, s, gu, F, out, out_term);
     return hipGetLastError();
 }
 

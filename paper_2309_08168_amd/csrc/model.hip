@@ -129,14 +129,16 @@ struct sd_model {
     int attn_splits_cap = 0;  // key chunks ws.attn_o / ws.attn_ml hold
     float2 *rope = nullptr;
     int rope_cap = 0;
-    // large-M forward (bfloat16 models): residual stream, GEMM output,
-    // rotated queries, and the GEMM inputs as X_TERMS terms, PF_ROWS rows each
+    // large-M forward (bfloat16 models), PF_ROWS rows each: residual stream,
+    // GEMM and attention outputs, rotated queries, partial sums of residual
+    // updates, and the GEMM inputs as PF_TERMS terms with their rows' scales
+    // and the maxima those come from
     bool pf_ok = false;
     float *pf_h = nullptr, *pf_c = nullptr, *pf_q = nullptr, *pf_part = nullptr;
-    uint16_t *pf_x = nullptr;  // terms of the GEMM inputs: normed rows, attention output
+    uint16_t *pf_x = nullptr;
     int64_t pf_term = 0;
-    uint16_t *pf_y = nullptr;  // terms of the MLP activation: the gate/up GEMM's output, the down GEMM's input
-    int64_t pf_y_term = 0;
+    float *pf_rs = nullptr, *pf_amax = nullptr;
+    int pf_amax_ld = 0;
     DevState *st = nullptr;
     Mailbox *mb_host = nullptr;
     Mailbox *mb_dev = nullptr;
@@ -731,88 +733,128 @@ sd_status ensure_gen_cache(sd_model *m, int32_t cap) {
 
 // Large-M forward (bfloat16 models): the M <= PF_ROWS tokens dev_tokens at
 // positions [start, start + M), matrix-core GEMMs over all rows at once;
-// logits (device [M][vocab]) when not null.
+// logits (device [M][vocab]) when not null.  Without logits the forward ends
+// with the keys and values of the last attention sublayer: nothing reads what
+// would follow.
 sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_t *skip, const int32_t *dev_tokens,
                                 int32_t M, int32_t start, float *logits) {
     const sd_config &c = m->cfg;
     const int H = c.n_heads, KVH = c.n_kv_heads, dh = c.head_dim, d = c.d_model, F = c.ffn_dim;
     const int hd = H * dh, nq = (H + 2 * KVH) * dh;
     const int64_t head_stride = (int64_t)cap * dh;
-    const int64_t xt = m->pf_term;
     hipStream_t s = m->stream;
-    // A split residual update leaves its partials in pf_part; the next norm
-    // adds them into the residual stream (fold = their count, 0: none).
+    // up to 64 rows on the thin GEMMs, if every layer fits them
+    const bool thin = pf_thin_ok(M, std::max({(int64_t)nq, (int64_t)2 * F, (int64_t)c.vocab}), d) &&
+                      pf_thin_ok(M, d, hd) && pf_thin_ok(M, d, F);
+    const PfTerms terms{m->pf_x, m->pf_rs, m->pf_term, thin ? pf_thin_blocks(M) : 0};
+    // A residual update leaves its partial sums in pf_part; the next norm adds
+    // them into the residual stream (fold = their count, 0: none).
     int fold = 0;
-    auto gemm = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, const uint16_t *A, int64_t a_term) {
+    auto gemm = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, int *out) {
         PfGemmArgs g{};
         g.W = static_cast<const uint16_t *>(W);
-        g.A = A;
-        g.a_term = a_term;
+        g.A = terms.x;
+        g.rs = terms.rs;
+        g.a_term = terms.term;
         g.C = C;
         g.ldc = ldc;
         g.M = M;
         g.N = N;
         g.K = K;
-        g.lda = K;
-        g.part = epi == EPI_RESID ? m->pf_part : nullptr;  // [PF_MAX_SPLITS][M][d]: split reductions
-        // EPI_SWIGLU: the MLP activation terms, not into A (other work-groups
-        // still read it)
-        g.xout = m->pf_y;
-        g.x_term = m->pf_y_term;
-        return launch(launch_pf_gemm(g, epi, s, epi == EPI_RESID && C == m->pf_h ? &fold : nullptr), "prefill GEMM");
+        g.lda = pf_pitch(K);
+        g.part = m->pf_part;
+        g.amax = m->pf_amax;
+        g.amax_ld = m->pf_amax_ld;
+        return launch(launch_pf_gemm(g, epi, s, out), "prefill GEMM");
+    };
+    auto thin_args = [&](const void *W, int N, int K, float *C, int64_t ldc) {
+        PfThinArgs g{};
+        g.W = static_cast<const uint16_t *>(W);
+        g.X = terms.x;
+        g.rs = terms.rs;
+        g.C = C;
+        g.ldc = ldc;
+        g.M = M;
+        g.N = N;
+        g.K = K;
+        g.amax = m->pf_amax;
+        g.amax_ld = m->pf_amax_ld;
+        return g;
+    };
+    auto product = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, int *out) {
+        if (!thin)
+            return gemm(W, N, K, C, ldc, epi, out);
+        return launch(launch_pf_thin(thin_args(W, N, K, epi == EPI_RESID ? m->pf_part : C, ldc), epi, s, out),
+                      "prefill GEMM");
     };
     auto norm = [&](const void *gain) {
-        const uint16_t *g = static_cast<const uint16_t *>(gain);
-        if (fold) {
-            const int f = fold;
-            fold = 0;
-            return launch(launch_pf_fold_norm_split(m->pf_h, m->pf_part, f, d, M, g, c.rms_eps, m->pf_x, xt, s),
-                          "prefill norm");
-        }
-        return launch(launch_pf_norm_split(m->pf_h, d, M, g, c.rms_eps, m->pf_x, xt, s), "prefill norm");
+        const int f = fold;
+        fold = 0;
+        return launch(launch_pf_norm_split(m->pf_h, m->pf_part, f, d, M, static_cast<const uint16_t *>(gain), c.rms_eps,
+                                           terms, s),
+                      "prefill norm");
     };
+    int last_attn = -1;
+    for (int l = 0; l < c.n_layers; ++l)
+        if (!(skip && skip[2 * l]))
+            last_attn = l;
+    if (!logits && last_attn < 0)
+        return SD_OK;
     SD_TRY(launch(launch_pf_embed(static_cast<const uint16_t *>(m->tok_emb), d, dev_tokens, M, m->pf_h, s),
                   "prefill embedding"));
+    int slots = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         if (!(skip && skip[2 * l])) {
             uint16_t *kbase = reinterpret_cast<uint16_t *>(kv) + (size_t)(2 * l) * KVH * head_stride;
             uint16_t *vbase = reinterpret_cast<uint16_t *>(kv) + (size_t)(2 * l + 1) * KVH * head_stride;
             SD_TRY(norm(m->attn_norm[l]));
-            SD_TRY(gemm(m->w_qkv[l], nq, d, m->pf_c, nq, EPI_STORE, m->pf_x, xt));
-            SD_TRY(launch(launch_pf_rope_kv(m->pf_c, M, start, m->rope, H, KVH, dh, m->pf_q, kbase, vbase,
-                                            head_stride, s),
-                          "prefill rotary"));
+            if (thin) {
+                PfThinArgs g = thin_args(m->w_qkv[l], nq, d, m->pf_q, hd);
+                g.kcache = kbase;
+                g.vcache = vbase;
+                g.kv_head_stride = head_stride;
+                g.rope = m->rope;
+                g.start = start;
+                g.n_heads = H;
+                g.n_kv_heads = KVH;
+                g.head_dim = dh;
+                SD_TRY(launch(launch_pf_thin(g, EPI_QKV, s), "prefill GEMM"));
+            } else {
+                SD_TRY(gemm(m->w_qkv[l], nq, d, m->pf_c, nq, EPI_STORE, nullptr));
+                SD_TRY(launch(launch_pf_rope_kv(m->pf_c, M, start, m->rope, H, KVH, dh, m->pf_q, kbase, vbase,
+                                                head_stride, s),
+                              "prefill rotary"));
+            }
+            if (!logits && l == last_attn)
+                return SD_OK;
             PfAttnArgs at{};
             at.q = m->pf_q;
             at.ldq = hd;
             at.kcache = kbase;
             at.vcache = vbase;
             at.kv_head_stride = head_stride;
-            at.out = m->pf_x;
-            at.out_term = xt;
+            at.out = m->pf_c;
             at.ldo = hd;
+            at.amax = m->pf_amax;
+            at.amax_ld = m->pf_amax_ld;
             at.M = M;
             at.start = start;
             at.n_heads = H;
             at.n_kv_heads = KVH;
             at.head_dim = dh;
             SD_TRY(launch(launch_pf_attention(at, s), "prefill attention"));
-            SD_TRY(gemm(m->w_o[l], d, hd, m->pf_h, d, EPI_RESID, m->pf_x, xt));
+            SD_TRY(launch(launch_pf_split(m->pf_c, hd, M, m->pf_amax, H, m->pf_amax_ld, terms, s), "prefill terms"));
+            SD_TRY(product(m->w_o[l], d, hd, nullptr, d, EPI_RESID, &fold));
         }
         if (!(skip && skip[2 * l + 1])) {
             SD_TRY(norm(m->mlp_norm[l]));
-            SD_TRY(gemm(m->w_gate_up[l], 2 * F, d, m->pf_c, 2 * F, EPI_SWIGLU, m->pf_x, xt));
-            SD_TRY(gemm(m->w_down[l], d, F, m->pf_h, d, EPI_RESID, m->pf_y, m->pf_y_term));
+            SD_TRY(product(m->w_gate_up[l], 2 * F, d, m->pf_c, F, EPI_SWIGLU, &slots));
+            SD_TRY(launch(launch_pf_split(m->pf_c, F, M, m->pf_amax, slots, m->pf_amax_ld, terms, s), "prefill terms"));
+            SD_TRY(product(m->w_down[l], d, F, nullptr, d, EPI_RESID, &fold));
         }
     }
-    if (logits) {
-        SD_TRY(norm(m->final_norm));
-        SD_TRY(gemm(m->lm_head, c.vocab, d, logits, c.vocab, EPI_STORE, m->pf_x, xt));
-    } else if (fold) {
-        // no norm follows: leave the residual stream whole
-        SD_TRY(launch(launch_pf_split_sum(m->pf_part, fold, (int64_t)M * d, m->pf_h, s), "prefill split sum"));
-    }
-    return SD_OK;
+    SD_TRY(norm(m->final_norm));
+    return product(m->lm_head, c.vocab, d, logits, c.vocab, EPI_STORE, nullptr);
 }
 
 // Prefill: full-model forward of tokens [0, n) already on the device, no
@@ -1405,7 +1447,8 @@ void destroy_model(sd_model *m) {
     dev_free(m->pf_q);
     dev_free(m->pf_part);
     dev_free(m->pf_x);
-    dev_free(m->pf_y);
+    dev_free(m->pf_rs);
+    dev_free(m->pf_amax);
     dev_free(m->ws.ctl);
     dev_free(m->st);
     dev_free(m->d_tokens);
@@ -1495,15 +1538,16 @@ sd_status create_model(const sd_config *cfg, const sd_weights *w, void *stream, 
     m->pf_ok = m->bf16 && (c.head_dim == 32 || c.head_dim == 64 || c.head_dim == 128);
     if (m->pf_ok) {
         const int64_t hd = (int64_t)c.n_heads * c.head_dim;
-        const int64_t nc = std::max<int64_t>((int64_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim, 2 * c.ffn_dim);
-        m->pf_term = (int64_t)PF_ROWS * std::max<int64_t>({c.d_model, hd, c.ffn_dim});
+        const int64_t nc = std::max<int64_t>((int64_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim, c.ffn_dim);
+        m->pf_term = (int64_t)PF_ROWS * pf_pitch((int)std::max<int64_t>({c.d_model, hd, c.ffn_dim}));
+        m->pf_amax_ld = std::max(c.n_heads, pf_swiglu_slots(c.ffn_dim));
         chain(dev_alloc(&m->pf_h, (size_t)PF_ROWS * c.d_model));
         chain(dev_alloc(&m->pf_c, (size_t)PF_ROWS * nc));
         chain(dev_alloc(&m->pf_q, (size_t)PF_ROWS * hd));
-        chain(dev_alloc(&m->pf_part, (size_t)PF_MAX_SPLITS * PF_ROWS * c.d_model));
-        chain(dev_alloc(&m->pf_x, (size_t)X_TERMS * m->pf_term));
-        m->pf_y_term = (int64_t)PF_ROWS * c.ffn_dim;
-        chain(dev_alloc(&m->pf_y, (size_t)X_TERMS * m->pf_y_term));
+        chain(dev_alloc(&m->pf_part, (size_t)PF_PART_ROWS * c.d_model));
+        chain(dev_alloc(&m->pf_x, (size_t)PF_TERMS * m->pf_term));
+        chain(dev_alloc(&m->pf_rs, (size_t)PF_ROWS));
+        chain(dev_alloc(&m->pf_amax, (size_t)PF_ROWS * m->pf_amax_ld));
     }
     if (st != SD_OK) {
         destroy_model(m);

@@ -258,64 +258,107 @@ struct AttnArgs {
 // ---------------------------------------------------------------------------
 // Large-M forward (prompt prefill, long forwards): up to PF_ROWS rows at
 // positions [start, start + M), bfloat16 weights and KV.  Activations that
-// feed a matrix-core GEMM are held as X_TERMS bf16 terms, row-major:
-// [X_TERMS][PF_ROWS][ld] with the term stride PF_ROWS * ld.
+// feed a matrix-core GEMM are held as PF_TERMS float16 planes of the row times
+// a power of two (kernels_prefill.hip), row-major: [PF_TERMS][PF_ROWS][ld] with
+// ld the row length rounded up to 32 (zeros past the end), and rs[row], the
+// inverse of the row's power of two.
 constexpr int PF_ROWS = 1024;
-constexpr int PF_MAX_SPLITS = 4;  // k-splits of a narrow residual-update GEMM
+constexpr int PF_TERMS = 2;
+constexpr int PF_MAX_SPLITS = 8;  // k-splits of a residual-update GEMM, and the rows of all its partial planes
+constexpr int PF_PART_ROWS = 4 * PF_ROWS;
+__host__ __device__ constexpr int pf_pitch(int K) { return (K + 31) & ~31; }
 
-// C[m][n] = (EPI_STORE) or += (EPI_RESID) sum over the terms t of
-// A_t[m][0..K) . W[n][0..K).
+// C[m][n] = sum over the terms t of rs[m] A_t[m][0..K) . W[n][0..K).
 struct PfGemmArgs {
     const uint16_t *W;  // [N][K] bf16
-    const uint16_t *A;  // [X_TERMS][.][lda] bf16 terms, M rows used
+    const uint16_t *A;  // [PF_TERMS][.][lda] float16 terms, M rows used
+    const float *rs;    // [M]
     int64_t a_term;     // elements between terms
     float *C;           // [M][ldc]
     int64_t ldc;
     int32_t M, N, K, lda;
-    float *part;        // EPI_RESID: [PF_MAX_SPLITS][M][ldc] scratch for a split reduction, or null
+    float *part;        // EPI_RESID: [splits][M][ldc], the partial sums (at most PF_PART_ROWS rows)
     int32_t splits;     // set by the launcher
-    // EPI_SWIGLU (W = [gate; up], N = 2 F): silu(gate) * up as X_TERMS bf16
-    // terms into xout [X_TERMS][.][F] (term stride x_term); C [M][2 F] is
-    // scratch for shapes the fused kernel does not take
-    uint16_t *xout;
-    int64_t x_term;
+    // EPI_SWIGLU (W = [gate; up], N = 2 F): silu(gate) * up into C [M][F], and
+    // in amax[m][0 .. slots) (pitch amax_ld) maxima of |C[m]| over column ranges
+    float *amax;
+    int32_t amax_ld;
+};
+
+// The same products for 17 to PF_THIN_ROWS rows (K a multiple of 64).  The
+// activation terms come in fragment order: term t of element k of row m is at
+// thin_off(t, m, k, blocks), blocks = ceil(M / 16), rows past M undefined.
+constexpr int PF_THIN_ROWS = 64;
+__host__ __device__ inline int64_t thin_off(int t, int m, int k, int blocks) {
+    return ((((int64_t)(k >> 5) * PF_TERMS + t) * blocks + (m >> 4)) << 9) +
+           ((m & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
+struct PfThinArgs {
+    const uint16_t *W;  // [N][K] bf16
+    const uint16_t *X;  // float16 terms in fragment order
+    const float *rs;    // [M]
+    float *C;           // STORE [M][ldc]; PARTIAL [splits][M][ldc]; SWIGLU [M][ldc] (N = 2 F); QKV: q [M][ldc]
+    int64_t ldc;
+    int32_t M, N, K;
+    int32_t splits, n_tiles;  // n_tiles: 16-row weight tiles
+    float *amax;              // SWIGLU: maxima of |C[m]| over the work-groups' columns
+    int32_t amax_ld;
+    // QKV: rotary embedding, and K and V rows start .. start + M - 1 into the cache
+    uint16_t *kcache, *vcache;
+    int64_t kv_head_stride;
+    const float2 *rope;
+    int32_t start, n_heads, n_kv_heads, head_dim;
 };
 
 // Causal attention of M query rows (row m at position start + m) over the
-// cached keys [0, start + m], output written as X_TERMS bf16 terms.
+// cached keys [0, start + m], output in float32 with the largest magnitude of
+// each (row, head) in amax[m][head].
 struct PfAttnArgs {
     const float *q;  // [M][ldq] rotated queries
     int64_t ldq;
     const uint16_t *kcache, *vcache;  // this layer: [n_kv_heads][cap][head_dim]
     int64_t kv_head_stride;
-    uint16_t *out;  // [X_TERMS][.][ldo]
-    int64_t out_term, ldo;
+    float *out;      // [M][ldo]
+    int64_t ldo;
+    float *amax;
+    int32_t amax_ld;
     int32_t M, start, n_heads, n_kv_heads, head_dim;
 };
 
 hipError_t launch_pf_embed(const uint16_t *emb, int d, const int32_t *tokens, int M, float *h, hipStream_t s);
-// g * h / rms(h) of every row (g: gain [K] bf16), as X_TERMS terms into out.
-hipError_t launch_pf_norm_split(const float *h, int K, int M, const uint16_t *gain, float eps, uint16_t *out,
-                                int64_t out_term, hipStream_t s);
-// The same after folding split-K partials into h: h[m] += part[0][m] +
-// part[1][m] + ... (splits of them, [splits][M][K], in split order) first.
-hipError_t launch_pf_fold_norm_split(float *h, const float *part, int splits, int K, int M, const uint16_t *gain,
-                                     float eps, uint16_t *out, int64_t out_term, hipStream_t s);
-// C = A W^T (EPI_STORE), C += A W^T (EPI_RESID), or the SwiGLU of a gate/up
-// product as terms (EPI_SWIGLU, see PfGemmArgs).  A narrow EPI_RESID may
-// split its reduction into a.part; with fold null the partials are added
-// into C before the call returns (on the stream), else *fold receives the
-// number of splits left in a.part for launch_pf_fold_norm_split (0: none).
-hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *fold = nullptr);
-// C[i] += part[0][i] + part[1][i] + ... for i < n (part [splits][n]).
-hipError_t launch_pf_split_sum(const float *part, int splits, int64_t n, float *C, hipStream_t s);
+// Where a GEMM input's terms go: row-major planes `term` elements apart
+// (blocks 0), or fragment order over `blocks` blocks of 16 rows (thin_off).
+struct PfTerms {
+    uint16_t *x;
+    float *rs;
+    int64_t term;
+    int32_t blocks;
+};
+// g * h / rms(h) of every row (g: gain [K] bf16) as terms; with splits > 0
+// after adding split-K partials into h: h[m] += part[0][m] + part[1][m] + ...
+// ([splits][M][K], in split order).
+hipError_t launch_pf_norm_split(float *h, const float *part, int splits, int K, int M, const uint16_t *gain, float eps,
+                                const PfTerms &t, hipStream_t s);
+// x [M][K] as terms, given maxima of each row in amax[m][0 .. slots).
+hipError_t launch_pf_split(const float *x, int K, int M, const float *amax, int slots, int amax_ld, const PfTerms &t,
+                           hipStream_t s);
+// C = A W^T (EPI_STORE), the partial sums of a residual update into a.part
+// (EPI_RESID; *out receives their number, for launch_pf_norm_split), or the SwiGLU of a gate/up product (EPI_SWIGLU; *out
+// receives the number of amax slots).
+hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out = nullptr);
+// The same with the rules of PfThinArgs: EPI_STORE, EPI_RESID (partial sums
+// into C, *out their number), EPI_SWIGLU (*out the amax slots) or EPI_QKV.
+bool pf_thin_ok(int M, int64_t N, int K);
+hipError_t launch_pf_thin(const PfThinArgs &a, int epi, hipStream_t s, int *out = nullptr);
+// Blocks of 16 rows of a thin GEMM's input.
+constexpr int pf_thin_blocks(int M) { return M <= 32 ? 2 : (M + 15) / 16; }
+// amax slots a gate/up product of ffn columns writes at most.
+constexpr int pf_swiglu_slots(int ffn) { return (ffn + 31) / 32; }
 // Rotary embedding of q and k from the QKV GEMM output [M][(H + 2 KVH) dh];
 // q into q [M][H dh], k and v into the cache at positions start + m.
 hipError_t launch_pf_rope_kv(const float *qkv, int M, int start, const float2 *rope, int H, int KVH, int dh,
                              float *q, uint16_t *kcache, uint16_t *vcache, int64_t kv_head_stride, hipStream_t s);
 hipError_t launch_pf_attention(const PfAttnArgs &a, hipStream_t s);
-// silu(gate) * up of the gate/up GEMM output [M][2 F], as X_TERMS terms.
-hipError_t launch_pf_swiglu_split(const float *gu, int F, int M, uint16_t *out, int64_t out_term, hipStream_t s);
 
 // Kernel paths of the linear layers.
 // PATH_WAVE2: up to two rows on one-wave tiles (bf16 weights).

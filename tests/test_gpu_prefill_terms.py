@@ -1,0 +1,109 @@
+"""GPU parity of the large-M GEMMs at the edges of their tiles and of the
+float16 window of their operands.
+
+- MLP and head products of one-layer models (attention skipped, so nothing is
+  rounded to bfloat16 on the way): 17 to 64 rows on the thin GEMM and more on
+  the tile GEMM, at every boundary of 16-row blocks, 64- and 128-row tiles; a
+  shape whose reductions are no multiple of 64 or 32 takes the tile GEMM at
+  every row count.
+- Weight rows far outside the float16 window of the GEMMs' common scale (they
+  run again with a scale per row), and an MLP activation 2^12 times the others
+  that its down weights undo, beside one 2^-35 times the others.
+- The rotary embedding and KV append in the thin QKV product, after a prefix
+  and after a decode step over the keys it wrote.
+
+Tolerance of the products: every output is a chain of three products of at
+most 2048 terms, accumulated in float32 in at most 2 (terms) x 64 (steps of 32)
+matrix instructions and 8 partial sums, each rounding to 2^-24 of the running
+sum, and the two float16 terms hold an activation to 2^-22.  The sum of their
+worst cases, 3 x (136 x 2^-24 + 2^-22) = 2.5e-5 of the norm of the row, bounds
+the difference to 5e-5 of the row's logit deviation times the factor the
+oracle's own logit rows are scaled by.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+import sd_synth as S
+from tests import gpu_util as U
+from tests import test_gpu_attention as A
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+MLP_REL = 5e-5
+THIN = S.ModelConfig("terms_thin", 1, 256, 4, 2, 64, 1344, 777, "bf16")
+RAGGED = S.ModelConfig("terms_ragged", 1, 136, 3, 1, 32, 200, 777, "bf16")
+LONG_K = S.ModelConfig("terms_long_k", 1, 512, 4, 2, 64, 2048, 400, "bf16")
+# head rows scaled far below and above the rest; gate / up / down rows that undo each other
+HEAD_ROWS = {5: -30, 6: -30, 200: 9, 399: -60}
+_models = {}
+
+
+def _pair(cfg, scaled):
+    if (cfg.name, scaled) not in _models:
+        w = S.make_weights(cfg, 11)
+        if scaled:
+            F = cfg.ffn_dim
+            for r, e in HEAD_ROWS.items():
+                w["lm_head"][r] = S.scale_tensor(w["lm_head"][r], 2.0 ** e, "bf16")
+            gu = w["layers.0.w_gate_up"]
+            gu[F + 3] = S.scale_tensor(gu[F + 3], 2.0 ** 12, "bf16")
+            gu[F + 40] = S.scale_tensor(gu[F + 40], 2.0 ** -35, "bf16")
+            w["layers.0.w_down"][:, 3] = S.scale_tensor(np.ascontiguousarray(w["layers.0.w_down"][:, 3]), 2.0 ** -12,
+                                                        "bf16")
+        _models[(cfg.name, scaled)] = (w, oracle.Model(cfg, w), U.device_model(cfg, w))
+    return _models[(cfg.name, scaled)]
+
+
+def _check(cfg, rows, scaled):
+    _, om, dm = _pair(cfg, scaled)
+    toks = S.prompt(cfg, rows, seed=rows)
+    skip = np.array([1, 0], np.uint8)
+    ref = om.score(toks, skip)["logits"]
+    out = torch.full((rows, cfg.vocab), float("nan"), dtype=torch.float32, device="cuda")
+    dm.forward(toks, dm.cache(rows), skip=skip, logits=out)
+    scale = np.ones(cfg.vocab)
+    if scaled:
+        for r, e in HEAD_ROWS.items():
+            scale[r] = 2.0 ** e
+    plain = scale == 1
+    err = np.abs(out.cpu().numpy().astype(np.float64) - ref) / scale
+    worst = float((err / (MLP_REL * ref[:, plain].std(axis=1, keepdims=True))).max())
+    print(f"{cfg.name} {rows} rows scaled {scaled}: max |d| / tol {worst:.3f}")
+    assert worst <= 1
+
+
+@pytest.mark.parametrize("rows", [17, 32, 33, 48, 49, 64, 65, 96, 129, 257, 513])
+@pytest.mark.parametrize("cfg", [THIN, RAGGED], ids=lambda c: c.name)
+def test_products_at_tile_edges(cfg, rows):
+    _check(cfg, rows, False)
+
+
+@pytest.mark.parametrize("rows", [33, 64, 100, 300])
+@pytest.mark.parametrize("cfg", [THIN, LONG_K], ids=lambda c: c.name)
+def test_rows_outside_the_float16_window(cfg, rows):
+    _check(cfg, rows, True)
+
+
+@pytest.mark.parametrize("name", list(A.CONFIGS))
+@pytest.mark.parametrize("rows", [17, 40, 64])
+def test_thin_rotary_and_kv_append(name, rows):
+    """rows after a prefix of 50 and one decode row over all of them."""
+    cfg, _, om, dm = A._pair(name)
+    toks = S.prompt(cfg, 50 + rows + 1, seed=rows + 1)
+    oc, gc = om.cache(len(toks)), dm.cache(len(toks))
+    for lo, hi in ((0, 50), (50, 50 + rows), (50 + rows, 51 + rows)):
+        ref = om.forward(oc, toks[lo:hi])["logits"]
+        out = torch.empty((hi - lo, cfg.vocab), dtype=torch.float32, device="cuda")
+        dm.forward(toks[lo:hi], gc, logits=out)
+        A._tight(ref, out.cpu().numpy(), f"{name} rows {lo}..{hi}")
