@@ -1020,6 +1020,282 @@ __global__ __launch_bounds__(256) void k_pf_rope_kv(const float *qkv, int start,
     }
 }
 
+// ---------------------------------------------------------------------------
+// Causal attention, head_dim 128.  A work-group takes 128 query rows of one
+// head, 32 per wave, over one chunk of the keys, in stages of 64 keys whose K
+// and V rows all four waves read from LDS (loaded straight there, one stage
+// ahead).  With every wave loading its own K and V for 16 rows, as k_pf_attn
+// does, 1000 rows over 8000 keys read 11 GB through the L2s per 13B layer and
+// spent most of their issue slots on the softmax: 1082 us a layer; this kernel
+// TTT us.  It is bound by its matrix instructions (three bfloat16 terms of q
+// and of the probabilities).
+//
+// 32 keys at a time: scores S^T = K q as 32x32x16 MFMAs leave lane (col, half)
+// the keys 8 (v / 4) + 4 half + v % 4, v = 0..15, of query col; the values
+// v = 8 j .. 8 j + 7 are the operand slots (half, u) of the j-th 16-key value
+// MFMA, so the probabilities stay in their lanes and V^T is read to match.
+// Scores are in units of log2: q carries the factor log2(e) / sqrt(128).
+//
+// LDS rows are 256 bytes; row r keeps its 16-byte chunk c at c ^ swz(r), so
+// that a K read (32 rows, one chunk) and a transposed V read (four rows, four
+// adjacent chunks) touch every bank once.  The loads permute the chunks of a
+// row on the way in, within the row's own cache lines.
+//
+// Each (chunk, row, head) leaves its unnormalised output and (max, sum), which
+// k_pf_attn_terms combines in chunk order.  Work-group i takes head i % H (the
+// work-groups of a head run on one XCD when H is a multiple of 8), the longest
+// row blocks first.
+
+constexpr int PA2_ROWS = 128;  // query rows per work-group
+constexpr int PA2_KB = 64;     // keys per stage
+
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2v_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ f32x16_t mfma32(u32x4_t a, u32x4_t b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
+                                                   0, 0, 0);
+}
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2v_t{a, b}), bf16x2_t));
+}
+// The three bf16 terms of two values, packed (the conversion rounds to nearest even).
+__device__ __forceinline__ void split3_pk(float a, float b, uint32_t (&t)[X_TERMS]) {
+    t[0] = cvt_pk_bf16(a, b);
+    const float a1 = a - __uint_as_float(t[0] << 16), b1 = b - __uint_as_float(t[0] & 0xffff0000u);
+    t[1] = cvt_pk_bf16(a1, b1);
+    t[2] = cvt_pk_bf16(a1 - __uint_as_float(t[1] << 16), b1 - __uint_as_float(t[1] & 0xffff0000u));
+}
+
+__global__ __launch_bounds__(256, 2) void k_pf_attn128(PfAttnArgs a) {
+    constexpr int DH = 128, T = X_TERMS;
+    __shared__ __attribute__((aligned(1024))) uint16_t kv[2][2][PA2_KB * DH];  // [stage % 2][K, V]
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    const int RB = (a.M + PA2_ROWS - 1) / PA2_ROWS;
+    const int head = (int)(blockIdx.x % a.n_heads), g = head / (a.n_heads / a.n_kv_heads);
+    const int unit = (int)(blockIdx.x / a.n_heads);
+    const int chunk = unit % a.chunks, rb = RB - 1 - unit / a.chunks;
+    const int w0 = rb * PA2_ROWS, r0 = w0 + wave * 32;
+    const int kend = a.start + min(w0 + PA2_ROWS, a.M);  // keys some row of the work-group sees
+    const int k_lo = chunk * a.chunk_keys, k_hi = min(kend, k_lo + a.chunk_keys);
+    if (k_lo >= k_hi)
+        return;  // uniform over the work-group: k_pf_attn_terms leaves this chunk out
+    const int rq = min(r0 + col, a.M - 1), qpos = a.start + rq;
+    const int q_min = a.start + r0;                          // the wave's first row sees keys up to here
+    const int q_max = a.start + min(r0 + 31, a.M - 1);       // and its last row up to here
+
+    // query terms: B operand of the score MFMAs
+    u32x4_t qf[8][T];
+    {
+        const float *qs = a.q + (int64_t)rq * a.ldq + (int64_t)head * DH + 8 * half;
+        const float scale = 1.4426950408889634f / sqrtf((float)DH);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            float x[8];
+            load8f(qs + 16 * s, x);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t t[T];
+                split3_pk(x[2 * j] * scale, x[2 * j + 1] * scale, t);
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+                    qf[s][i][j] = t[i];
+            }
+        }
+    }
+
+    const uint16_t *Kg = a.kcache + (int64_t)g * a.kv_head_stride, *Vg = a.vcache + (int64_t)g * a.kv_head_stride;
+    auto swz = [](int r) { return ((r & 3) << 2) | ((r >> 2) & 3); };
+    // load instruction i of a wave fills rows 16 wave + 4 i .. + 3 of K or V
+    auto load_stage = [&](int kb, int buf) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 16 * wave + 4 * i + (lane >> 4), key = min(kb + r, kend - 1);
+            const int64_t o = (int64_t)key * DH + 8 * ((lane & 15) ^ swz(r));
+            load_to_lds16(Kg + o, &kv[buf][0][(16 * wave + 4 * i) * DH]);
+            load_to_lds16(Vg + o, &kv[buf][1][(16 * wave + 4 * i) * DH]);
+        }
+    };
+
+    float m_run = -INFINITY, l_run = 0.0f;
+    f32x16_t oacc[4];
+#pragma unroll
+    for (int et = 0; et < 4; ++et)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            oacc[et][v] = 0.0f;
+
+    load_stage(k_lo, 0);
+    int buf = 0;
+    for (int kb = k_lo; kb < k_hi; kb += PA2_KB, buf ^= 1) {
+        // this wave's loads of the stage have landed, then everyone's; every
+        // read of the other buffer has returned
+        __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (kb + PA2_KB < k_hi)
+            load_stage(kb + PA2_KB, buf ^ 1);
+        const uint16_t *ks = kv[buf][0], *vs = kv[buf][1];
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            const int k0 = kb + 32 * h;
+            if (k0 > q_max || k0 >= k_hi)
+                break;  // uniform over the wave: no row of it sees these keys
+            f32x16_t s;
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                s[v] = 0.0f;
+            const int kr = 32 * h + col;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const u32x4_t kf =
+                    *reinterpret_cast<const u32x4_t *>(ks + kr * DH + 8 * ((2 * e + half) ^ swz(kr)));
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+                    s = mfma32(kf, qf[e][i], s);
+            }
+            if (k0 + 31 > q_min || k0 + 31 >= k_hi) {
+                // keys a row does not see, and keys past the chunk
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int key = k0 + 8 * (v >> 2) + 4 * half + (v & 3);
+                    s[v] = key <= qpos && key < k_hi ? s[v] : -INFINITY;
+                }
+            }
+            float mx = s[0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v)
+                mx = fmaxf(mx, s[v]);
+            {
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+                mx = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+            }
+            if (__any(mx > m_run)) {
+                // (a row that has seen no key yet keeps zeros)
+                const float m_new = fmaxf(m_run, mx);
+                const float sc = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+                l_run *= sc;
+#pragma unroll
+                for (int et = 0; et < 4; ++et)
+                    oacc[et] *= sc;
+                m_run = m_new;
+            }
+            const float m_use = m_run == -INFINITY ? 0.0f : m_run;
+            float p[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                p[v] = __builtin_amdgcn_exp2f(s[v] - m_use);
+                l_run += p[v];
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                u32x4_t pf[T];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    uint32_t t[T];
+                    split3_pk(p[8 * j + 2 * u], p[8 * j + 2 * u + 1], t);
+#pragma unroll
+                    for (int i = 0; i < T; ++i)
+                        pf[i][u] = t[i];
+                }
+                // A operand V^T: lane (col, half) needs column 32 et + col of
+                // keys 16 j + 8 (u / 4) + 4 half + u % 4.  ds_read_b64_tr_b16
+                // hands lane l of each 16-lane group element l % 4 of the 8
+                // bytes that lanes l / 4 + 4 k (k = 0..3) point at: lane l
+                // points at key 16 j + 8 I + 4 half + l / 4 % 4, columns 32 et +
+                // 16 (l / 16 % 2) + 4 (l % 4) ...
+#pragma unroll
+                for (int et = 0; et < 4; ++et) {
+                    u32x4_t vf;
+#pragma unroll
+                    for (int I = 0; I < 2; ++I) {
+                        const int r = 32 * h + 16 * j + 8 * I + 4 * half + ((lane >> 2) & 3);
+                        const int c = 4 * et + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+                        const uint16_t *src = vs + r * DH + 8 * (c ^ swz(r)) + 4 * (lane & 1);
+                        const s16x4_t x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)src);
+                        const u32x2_t y = __builtin_bit_cast(u32x2_t, x);
+                        vf[2 * I] = y[0];
+                        vf[2 * I + 1] = y[1];
+                    }
+#pragma unroll
+                    for (int i = 0; i < T; ++i)
+                        oacc[et] = mfma32(vf, pf[i], oacc[et]);
+                }
+            }
+        }
+    }
+
+    // lane holds O^T[32 et + 8 (v / 4) + 4 half + v % 4][query col]
+    const auto lr = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+    const float l = __uint_as_float(lr[0]) + __uint_as_float(lr[1]);
+    if (r0 + col < a.M) {
+        const int64_t row = (int64_t)chunk * a.M + rq;
+        float *o = a.out + row * a.ldo + (int64_t)head * DH + 4 * half;
+#pragma unroll
+        for (int et = 0; et < 4; ++et)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4_t *>(o + 32 * et + 8 * q) =
+                    f32x4_t{oacc[et][4 * q], oacc[et][4 * q + 1], oacc[et][4 * q + 2], oacc[et][4 * q + 3]};
+        if (half == 0)
+            a.ml[row * a.n_heads + head] = make_float2(m_run, l);
+    }
+}
+
+// The chunks of k_pf_attn128 combined in order and normalised, one work-group
+// per row, as float16 terms with the row's scale.  LDS: the row (hd floats) and
+// the chunks' weights [H][chunks].
+__global__ __launch_bounds__(256) void k_pf_attn_terms(PfAttnArgs a, uint16_t *out, int64_t out_term, int blocks,
+                                                       float *rs) {
+    extern __shared__ __attribute__((aligned(16))) float sm[];
+    __shared__ float red[4];
+    const int m = blockIdx.x, tid = threadIdx.x, H = a.n_heads, hd = H * 128;
+    float *row = sm, *wt = sm + hd;
+    // chunks some row of this row's work-group saw keys of
+    const int kend = a.start + min((m / PA2_ROWS + 1) * PA2_ROWS, a.M);
+    const int nc = min(a.chunks, (kend + a.chunk_keys - 1) / a.chunk_keys);
+    for (int h = tid; h < H; h += 256) {
+        float mx = -INFINITY, L = 0.0f;
+        for (int c = 0; c < nc; ++c)
+            mx = fmaxf(mx, a.ml[((int64_t)c * a.M + m) * H + h].x);
+        for (int c = 0; c < nc; ++c) {
+            const float2 v = a.ml[((int64_t)c * a.M + m) * H + h];
+            const float w = v.x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(v.x - mx);
+            wt[h * nc + c] = w;
+            L = fmaf(w, v.y, L);
+        }
+        const float inv = 1.0f / L;
+        for (int c = 0; c < nc; ++c)
+            wt[h * nc + c] *= inv;
+    }
+    __syncthreads();
+    float mx = 0.0f;
+    for (int k = 4 * tid; k < hd; k += 4 * 256) {
+        const float *w = wt + (k >> 7) * nc, *p = a.out + (int64_t)m * a.ldo + k;
+        f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int c = 0; c < nc; ++c)
+            v += w[c] * *reinterpret_cast<const f32x4_t *>(p + (int64_t)c * a.M * a.ldo);
+        *reinterpret_cast<f32x4_t *>(row + k) = v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            mx = fmaxf(mx, fabsf(v[j]));
+    }
+    mx = wave_max_all(mx);
+    if ((tid & 63) == 0)
+        red[tid >> 6] = mx;
+    __syncthreads();
+    float rinv;
+    const float sc = row_scale(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), &rinv);
+    if (tid == 0)
+        rs[m] = rinv;
+    store_terms(m, hd, out, out_term, blocks, [&](int k, float(&u)[8]) {
+        load8f(row + k, u);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            u[j] *= sc;
+    });
+}
+
 }  // namespace
 
 hipError_t launch_pf_embed(const uint16_t *emb, int d, const int32_t *tokens, int M, float *h, hipStream_t s) {
@@ -1208,9 +1484,29 @@ hipError_t launch_pf_rope_kv(const float *qkv, int M, int start, const float2 *r
     return hipGetLastError();
 }
 
-hipError_t launch_pf_attention(const PfAttnArgs &a, hipStream_t s) {
+// Chunks of the keys per row block: enough work-groups for PA_UNITS of them,
+// chunks of at least 256 keys, and no more partial rows than the scratch holds.
+constexpr int PA_UNITS = 1280;
+
+hipError_t launch_pf_attention(const PfAttnArgs &a0, const PfTerms &t, hipStream_t s) {
+    PfAttnArgs a = a0;
     if (a.M < 1 || a.n_heads < 1 || a.n_kv_heads < 1 || a.n_heads % a.n_kv_heads)
         return hipErrorInvalidValue;
+    const int hd = a.n_heads * a.head_dim;
+    if (a.head_dim == 128 && hd <= 8192) {
+        const int units = ((a.M + PA2_ROWS - 1) / PA2_ROWS) * a.n_heads, keys = a.start + a.M;
+        const int most = std::min({PF_PART_ROWS / a.M, keys / 256, (16384 - hd) / a.n_heads});
+        a.chunks = std::max(1, std::min(most, (PA_UNITS + units - 1) / units));
+        a.chunk_keys = ((keys + a.chunks - 1) / a.chunks + PA2_KB - 1) / PA2_KB * PA2_KB;
+        a.chunks = (keys + a.chunk_keys - 1) / a.chunk_keys;
+        hipLaunchKernelGGL(k_pf_attn128, dim3(units * a.chunks), dim3(256), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(k_pf_attn_terms, dim3(a.M), dim3(256), (size_t)(hd + a.n_heads * a.chunks) * sizeof(float),
+                           s, a, t.x, t.term, t.blocks, t.rs);
+        return hipGetLastError();
+    }
     const dim3 grid(((a.M + 63) / 64) * a.n_heads), block(256);
     switch (a.head_dim) {
     case 32:
@@ -1225,7 +1521,10 @@ hipError_t launch_pf_attention(const PfAttnArgs &a, hipStream_t s) {
     default:
         return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    return launch_pf_split(a.out, hd, a.M, a.amax, a.n_heads, a.amax_ld, t, s);
 }
 
 }  // namespace sdk

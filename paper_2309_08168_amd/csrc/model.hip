@@ -138,6 +138,7 @@ struct sd_model {
     uint16_t *pf_x = nullptr;
     int64_t pf_term = 0;
     float *pf_rs = nullptr, *pf_amax = nullptr;
+    float2 *pf_ml = nullptr;  // attention: (max, sum) per chunk of the keys, row and head
     int pf_amax_ld = 0;
     DevState *st = nullptr;
     Mailbox *mb_host = nullptr;
@@ -833,8 +834,9 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
             at.kcache = kbase;
             at.vcache = vbase;
             at.kv_head_stride = head_stride;
-            at.out = m->pf_c;
+            at.out = m->pf_part;
             at.ldo = hd;
+            at.ml = m->pf_ml;
             at.amax = m->pf_amax;
             at.amax_ld = m->pf_amax_ld;
             at.M = M;
@@ -842,8 +844,7 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
             at.n_heads = H;
             at.n_kv_heads = KVH;
             at.head_dim = dh;
-            SD_TRY(launch(launch_pf_attention(at, s), "prefill attention"));
-            SD_TRY(launch(launch_pf_split(m->pf_c, hd, M, m->pf_amax, H, m->pf_amax_ld, terms, s), "prefill terms"));
+            SD_TRY(launch(launch_pf_attention(at, terms, s), "prefill attention"));
             SD_TRY(product(m->w_o[l], d, hd, nullptr, d, EPI_RESID, &fold));
         }
         if (!(skip && skip[2 * l + 1])) {
@@ -1449,6 +1450,7 @@ void destroy_model(sd_model *m) {
     dev_free(m->pf_x);
     dev_free(m->pf_rs);
     dev_free(m->pf_amax);
+    dev_free(m->pf_ml);
     dev_free(m->ws.ctl);
     dev_free(m->st);
     dev_free(m->d_tokens);
@@ -1544,7 +1546,9 @@ sd_status create_model(const sd_config *cfg, const sd_weights *w, void *stream, 
         chain(dev_alloc(&m->pf_h, (size_t)PF_ROWS * c.d_model));
         chain(dev_alloc(&m->pf_c, (size_t)PF_ROWS * nc));
         chain(dev_alloc(&m->pf_q, (size_t)PF_ROWS * hd));
-        chain(dev_alloc(&m->pf_part, (size_t)PF_PART_ROWS * c.d_model));
+        // partial sums of residual updates, and the attention chunks' outputs
+        chain(dev_alloc(&m->pf_part, (size_t)PF_PART_ROWS * std::max<int64_t>(c.d_model, hd)));
+        chain(dev_alloc(&m->pf_ml, (size_t)PF_PART_ROWS * c.n_heads));
         chain(dev_alloc(&m->pf_x, (size_t)PF_TERMS * m->pf_term));
         chain(dev_alloc(&m->pf_rs, (size_t)PF_ROWS));
         chain(dev_alloc(&m->pf_amax, (size_t)PF_ROWS * m->pf_amax_ld));

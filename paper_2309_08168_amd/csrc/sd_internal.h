@@ -311,18 +311,21 @@ struct PfThinArgs {
 };
 
 // Causal attention of M query rows (row m at position start + m) over the
-// cached keys [0, start + m], output in float32 with the largest magnitude of
-// each (row, head) in amax[m][head].
+// cached keys [0, start + m], the output as terms of the next GEMM.
 struct PfAttnArgs {
     const float *q;  // [M][ldq] rotated queries
     int64_t ldq;
     const uint16_t *kcache, *vcache;  // this layer: [n_kv_heads][cap][head_dim]
     int64_t kv_head_stride;
-    float *out;      // [M][ldo]
+    // scratch: float32 outputs of the chunks of the keys (PF_PART_ROWS rows) and
+    // their (max, sum) per head; maxima of the rows [M][amax_ld]
+    float *out;      // [chunks][M][ldo]
     int64_t ldo;
+    float2 *ml;      // [chunks][M][n_heads]
     float *amax;
     int32_t amax_ld;
     int32_t M, start, n_heads, n_kv_heads, head_dim;
+    int32_t chunks, chunk_keys;  // set by the launcher
 };
 
 hipError_t launch_pf_embed(const uint16_t *emb, int d, const int32_t *tokens, int M, float *h, hipStream_t s);
@@ -358,7 +361,7 @@ constexpr int pf_swiglu_slots(int ffn) { return (ffn + 31) / 32; }
 // q into q [M][H dh], k and v into the cache at positions start + m.
 hipError_t launch_pf_rope_kv(const float *qkv, int M, int start, const float2 *rope, int H, int KVH, int dh,
                              float *q, uint16_t *kcache, uint16_t *vcache, int64_t kv_head_stride, hipStream_t s);
-hipError_t launch_pf_attention(const PfAttnArgs &a, hipStream_t s);
+hipError_t launch_pf_attention(const PfAttnArgs &a, const PfTerms &t, hipStream_t s);
 
 // Kernel paths of the linear layers.
 // PATH_WAVE2: up to two rows on one-wave tiles (bf16 weights).
