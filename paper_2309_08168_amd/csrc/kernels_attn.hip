@@ -344,10 +344,9 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
     const int pos = a.ctl->pos, M = a.ctl->m;
     const int ctx = pos + M;
     const int H = a.n_heads, G = H / a.n_kv_heads, Q = G * M;
-    const int c0 = split * ATTN_CHUNK;
+    const int c0 = split * a.chunk, c1 = min(c0 + a.chunk, ctx);
     if (M == 0 || c0 >= ctx || qt * 16 >= Q)
         return;  // uniform over the work-group (M = 0: a cancelled step)
-    const int cw = c0 + wave * MKW;  // first key of this wave
     const int col = lane & 15, grp = lane >> 4;
     const uint16_t *Kg = reinterpret_cast<const uint16_t *>(a.kcache) + (int64_t)g * a.kv_head_stride;
     const uint16_t *Vg = reinterpret_cast<const uint16_t *>(a.vcache) + (int64_t)g * a.kv_head_stride;
@@ -367,23 +366,29 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
             qraw[s][1] = reinterpret_cast<const f32x4_t *>(qs + 32 * s)[1];
         }
     }
-    // K operands (A of the score MFMAs) and the wave's V rows.  Keys past the
-    // context read the last row inside it: their scores are masked and their
-    // weights are zero, and the row read is a finite one.
+    // K operands (A of the score MFMAs) and the wave's V rows of the block at
+    // kb.  Keys past the context read the last row inside it: their scores are
+    // masked and their weights are zero, and the row read is a finite one.
     u32x4_t kf[2][ES], vr[NVJ];
+    auto load_k = [&](int kb) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int key = min(cw + 16 * t + 4 * (col & 3) + (col >> 2), ctx - 1);
-        const uint16_t *kp = Kg + (int64_t)key * DH + 8 * grp;
+        for (int t = 0; t < 2; ++t) {
+            const int key = min(kb + wave * MKW + 16 * t + 4 * (col & 3) + (col >> 2), ctx - 1);
+            const uint16_t *kp = Kg + (int64_t)key * DH + 8 * grp;
 #pragma unroll
-        for (int s = 0; s < ES; ++s)
-            kf[t][s] = *reinterpret_cast<const u32x4_t *>(kp + 32 * s);
-    }
+            for (int s = 0; s < ES; ++s)
+                kf[t][s] = *reinterpret_cast<const u32x4_t *>(kp + 32 * s);
+        }
+    };
+    auto load_v = [&](int kb) {
 #pragma unroll
-    for (int j = 0; j < NVJ; ++j) {
-        const int key = min(cw + j * RPI + lane / LPR, ctx - 1);
-        vr[j] = *reinterpret_cast<const u32x4_t *>(Vg + (int64_t)key * DH + 8 * (lane % LPR));
-    }
+        for (int j = 0; j < NVJ; ++j) {
+            const int key = min(kb + wave * MKW + j * RPI + lane / LPR, ctx - 1);
+            vr[j] = *reinterpret_cast<const u32x4_t *>(Vg + (int64_t)key * DH + 8 * (lane % LPR));
+        }
+    };
+    load_k(c0);
+    load_v(c0);
     // every load above is issued before the first result is waited for
     __builtin_amdgcn_sched_barrier(0);
     float qx[ES][8];
@@ -398,13 +403,23 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
             }
     }
 
-    // scores of the wave's 32 keys for query column col
-    f32x4_t sacc[2];
-    {
-        u32x4_t qf[ES][X_TERMS];
+    u32x4_t qf[ES][X_TERMS];
 #pragma unroll
-        for (int s = 0; s < ES; ++s)
-            split3x8(qx[s], qf[s]);
+    for (int s = 0; s < ES; ++s)
+        split3x8(qx[s], qf[s]);
+    uint16_t *vs = reinterpret_cast<uint16_t *>(tile[wave]);
+    const int lim = pos + r;  // last key row r sees
+    float mx = -INFINITY, ls = 0.0f;
+    f32x4_t oacc[ET];
+#pragma unroll
+    for (int et = 0; et < ET; ++et)
+        oacc[et] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    // A chunk is one block of 128 keys while the blocks are few, else several
+    // (attn_blocks), with an online softmax
+    for (int kb = c0; kb < c1; kb += ATTN_CHUNK) {
+        const int cw = kb + wave * MKW;  // first key of this wave
+        // scores of the wave's 32 keys for query column col
+        f32x4_t sacc[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             sacc[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
@@ -414,57 +429,69 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
                 for (int i = 0; i < X_TERMS; ++i)
                     sacc[t] = mfma_bf16(kf[t][s], qf[s][i], sacc[t]);
         }
-    }
-    // softmax over those keys; slot u = 4 t + v of this lane is key 16 t + 4 v + grp
-    const int lim = pos + r;  // last key row r sees
-    float sv[8], mx = -INFINITY;
+        const bool more = kb + ATTN_CHUNK < c1;  // uniform
+        if (more)
+            load_k(kb + ATTN_CHUNK);
+        // softmax over those keys; slot u = 4 t + v of this lane is key 16 t + 4 v + grp
+        float sv[8], mb = -INFINITY;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int key = cw + 16 * (u >> 2) + 4 * (u & 3) + grp;
-        sv[u] = (qok && key < ctx && key <= lim) ? sacc[u >> 2][u & 3] : -INFINITY;
-        mx = fmaxf(mx, sv[u]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    float p[8], ls = 0.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        p[u] = mx == -INFINITY ? 0.0f : expf(sv[u] - mx);
-        ls += p[u];
-    }
-    ls += __shfl_xor(ls, 16, 64);
-    ls += __shfl_xor(ls, 32, 64);
-    u32x4_t pf[X_TERMS];
-    split3x8(p, pf);
-
-    // V rows into the wave's LDS tile, then O^T = V^T P^T tile by tile
-    uint16_t *vs = reinterpret_cast<uint16_t *>(tile[wave]);
-#pragma unroll
-    for (int j = 0; j < NVJ; ++j)
-        *reinterpret_cast<u32x4_t *>(vs + (j * RPI + lane / LPR) * VP + 8 * (lane % LPR)) = vr[j];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    f32x4_t oacc[ET];
-#pragma unroll
-    for (int et = 0; et < ET; ++et) {
-        // A operand V^T: lane (col, grp) needs column 16 et + col of keys
-        // 16 (u >> 2) + 4 (u & 3) + grp, u = 0..7 (the score slots).
-        // ds_read_b64_tr_b16 hands lane l of each 16-lane group element l % 4
-        // of the 8 bytes that lanes l / 4 + 4 k (k = 0..3) point at, so lane
-        // r points at key 16 I + 4 (r >> 2) + grp, columns 16 et + 4 (r & 3)
-        // ..: two reads give the eight keys in order.
-        uint32_t w[4];
-#pragma unroll
-        for (int I = 0; I < 2; ++I) {
-            const uint16_t *src = vs + (16 * I + 4 * (col >> 2) + grp) * VP + 16 * et + 4 * (col & 3);
-            const s16x4_t rv = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)src);
-            w[2 * I] = (uint32_t)(uint16_t)rv[0] | ((uint32_t)(uint16_t)rv[1] << 16);
-            w[2 * I + 1] = (uint32_t)(uint16_t)rv[2] | ((uint32_t)(uint16_t)rv[3] << 16);
+        for (int u = 0; u < 8; ++u) {
+            const int key = cw + 16 * (u >> 2) + 4 * (u & 3) + grp;
+            sv[u] = (qok && key < ctx && key <= lim) ? sacc[u >> 2][u & 3] : -INFINITY;
+            mb = fmaxf(mb, sv[u]);
         }
-        const u32x4_t vf = {w[0], w[1], w[2], w[3]};
-        oacc[et] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        mb = fmaxf(mb, __shfl_xor(mb, 16, 64));
+        mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
+        const float mn = fmaxf(mx, mb);
+        if (kb > c0) {  // uniform: what the earlier blocks left, at the new maximum
+            const float sc = mx == -INFINITY ? 0.0f : expf(mx - mn);
+            ls *= sc;
 #pragma unroll
-        for (int i = 0; i < X_TERMS; ++i)
-            oacc[et] = mfma_bf16(vf, pf[i], oacc[et]);
+            for (int et = 0; et < ET; ++et)
+                oacc[et] *= sc;
+        }
+        mx = mn;
+        float p[8], lb = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            p[u] = mx == -INFINITY ? 0.0f : expf(sv[u] - mx);
+            lb += p[u];
+        }
+        lb += __shfl_xor(lb, 16, 64);
+        lb += __shfl_xor(lb, 32, 64);
+        ls += lb;
+        u32x4_t pf[X_TERMS];
+        split3x8(p, pf);
+
+        // V rows into the wave's LDS tile, then O^T += V^T P^T tile by tile
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int j = 0; j < NVJ; ++j)
+            *reinterpret_cast<u32x4_t *>(vs + (j * RPI + lane / LPR) * VP + 8 * (lane % LPR)) = vr[j];
+        if (more)
+            load_v(kb + ATTN_CHUNK);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int et = 0; et < ET; ++et) {
+            // A operand V^T: lane (col, grp) needs column 16 et + col of keys
+            // 16 (u >> 2) + 4 (u & 3) + grp, u = 0..7 (the score slots).
+            // ds_read_b64_tr_b16 hands lane l of each 16-lane group element l % 4
+            // of the 8 bytes that lanes l / 4 + 4 k (k = 0..3) point at, so lane
+            // r points at key 16 I + 4 (r >> 2) + grp, columns 16 et + 4 (r & 3)
+            // ..: two reads give the eight keys in order.
+            uint32_t w[4];
+#pragma unroll
+            for (int I = 0; I < 2; ++I) {
+                const uint16_t *src = vs + (16 * I + 4 * (col >> 2) + grp) * VP + 16 * et + 4 * (col & 3);
+                const s16x4_t rv = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)src);
+                w[2 * I] = (uint32_t)(uint16_t)rv[0] | ((uint32_t)(uint16_t)rv[1] << 16);
+                w[2 * I + 1] = (uint32_t)(uint16_t)rv[2] | ((uint32_t)(uint16_t)rv[3] << 16);
+            }
+            const u32x4_t vf = {w[0], w[1], w[2], w[3]};
+#pragma unroll
+            for (int i = 0; i < X_TERMS; ++i)
+                oacc[et] = mfma_bf16(vf, pf[i], oacc[et]);
+        }
     }
     // this wave's (max, sum, O^T) into its tile, which the V rows no longer need
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -522,7 +549,8 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
 // Decode attention of one or two query vectors per kv head (the draft,
 // autoregressive and one-draft verification steps of multi-head attention)
 // over a bfloat16 cache with head_dim 128, on the VALU: one work-group of
-// two waves per (64-key chunk, kv head), 32 keys per wave.
+// two waves per (chunk of the keys, kv head), 32 keys of every 64-key block
+// per wave.
 //
 // Lane group j4 (lanes 16 j4 .. 16 j4 + 15) holds the key rows
 // cw + 4 i + j4 (i = 0..7) of its wave and lane e16 of the group the
@@ -560,10 +588,10 @@ __global__ __launch_bounds__(VW * 64) void k_attn_valu(AttnArgs a) {
     const int pos = a.ctl->pos, M = a.ctl->m;
     const int ctx = pos + M;
     const int H = a.n_heads, G = H / a.n_kv_heads, Q = G * M;
-    const int c0 = split * ATTN_CHUNK_VALU;
+    const int c0 = split * a.chunk;
     if (M == 0 || c0 >= ctx)
         return;  // uniform over the work-group (M = 0: a cancelled step)
-    const int cw = c0 + wave * 32;
+    const int c1 = min(c0 + a.chunk, ctx);
     const uint16_t *Kg = reinterpret_cast<const uint16_t *>(a.kcache) + (int64_t)g * a.kv_head_stride + 8 * e16;
     const uint16_t *Vg = reinterpret_cast<const uint16_t *>(a.vcache) + (int64_t)g * a.kv_head_stride + 8 * e16;
 
@@ -577,80 +605,99 @@ __global__ __launch_bounds__(VW * 64) void k_attn_valu(AttnArgs a) {
         qraw[qi][0] = reinterpret_cast<const f32x4_t *>(qs)[0];
         qraw[qi][1] = reinterpret_cast<const f32x4_t *>(qs)[1];
     }
-    int keyrow[8];
+    // key row i of this lane in the wave's part of the block at kb (rows past
+    // the context read the last row inside it)
+    auto keyrow = [&](int kb, int i) { return min(kb + wave * 32 + 4 * i + j4, ctx - 1); };
     u32x4_t kr[8], vr[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        keyrow[i] = min(cw + 4 * i + j4, ctx - 1);
-        kr[i] = *reinterpret_cast<const u32x4_t *>(Kg + (int64_t)keyrow[i] * DH);
-    }
+    for (int i = 0; i < 8; ++i)
+        kr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Kg + (int64_t)keyrow(c0, i) * DH));
     __builtin_amdgcn_sched_barrier(0);
 
     const float scale = 1.0f / sqrtf((float)DH);
-    float s[QV][8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float kx[8];
-        unpack8_bf16(kr[i], kx);
-#pragma unroll
-        for (int qi = 0; qi < QV; ++qi) {
-            float t = 0.0f;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                t = fmaf(qraw[qi][0][u] * scale, kx[u], t);
-                t = fmaf(qraw[qi][1][u] * scale, kx[4 + u], t);
-            }
-            s[qi][i] = t;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        vr[i] = *reinterpret_cast<const u32x4_t *>(Vg + (int64_t)keyrow[i] * DH);
     const int b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
     const int row = 4 * b1 + 2 * b2 + b3;  // the row whose score this lane ends with
-    const int key = cw + 4 * row + j4;
-    float mx[QV], ls[QV];
+    float mx[QV], ls[QV], o[QV][8];
 #pragma unroll
     for (int qi = 0; qi < QV; ++qi) {
-        float x4[4], x2[2];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            x4[u] = bfly8(s[qi][2 * u], s[qi][2 * u + 1], lane);
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            x2[u] = bfly4(x4[2 * u], x4[2 * u + 1], lane);
-        float t = bfly2(x2[0], x2[1], lane);
-        t += dpp_mov<DPP_QUAD_XOR1>(t);
-        const int r = qi < Q ? qi / G : 0;
-        const bool ok = qi < Q && key < ctx && key <= pos + r;
-        const float sv = ok ? t : -INFINITY;
-        mx[qi] = wave_max_all(sv);
-        const float p = mx[qi] == -INFINITY ? 0.0f : expf(sv - mx[qi]);
-        ls[qi] = wave_sum_all(b0 ? 0.0f : p);
-        if (!b0)
-            sp[wave][qi][8 * j4 + row] = p;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // O = sum over the rows of p V, for the lane's 8 elements
-    float o[QV][8];
-#pragma unroll
-    for (int qi = 0; qi < QV; ++qi)
+        mx[qi] = -INFINITY;
+        ls[qi] = 0.0f;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             o[qi][u] = 0.0f;
-#pragma unroll
-    for (int qi = 0; qi < QV; ++qi) {
-        const f32x4_t pa = *reinterpret_cast<const f32x4_t *>(&sp[wave][qi][8 * j4]);
-        const f32x4_t pb = *reinterpret_cast<const f32x4_t *>(&sp[wave][qi][8 * j4 + 4]);
-        const float pw[8] = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
+    }
+    for (int kb = c0; kb < c1; kb += ATTN_CHUNK_VALU) {
+        float s[QV][8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            float vx[8];
-            unpack8_bf16(vr[i], vx);
+            float kx[8];
+            unpack8_bf16(kr[i], kx);
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                o[qi][u] = fmaf(pw[i], vx[u], o[qi][u]);
+            for (int qi = 0; qi < QV; ++qi) {
+                float t = 0.0f;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    t = fmaf(qraw[qi][0][u] * scale, kx[u], t);
+                    t = fmaf(qraw[qi][1][u] * scale, kx[4 + u], t);
+                }
+                s[qi][i] = t;
+            }
         }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Vg + (int64_t)keyrow(kb, i) * DH));
+        if (kb + ATTN_CHUNK_VALU < c1) {  // uniform
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                kr[i] = __builtin_nontemporal_load(
+                    reinterpret_cast<const u32x4_t *>(Kg + (int64_t)keyrow(kb + ATTN_CHUNK_VALU, i) * DH));
+        }
+        const int key = kb + wave * 32 + 4 * row + j4;
+#pragma unroll
+        for (int qi = 0; qi < QV; ++qi) {
+            float x4[4], x2[2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                x4[u] = bfly8(s[qi][2 * u], s[qi][2 * u + 1], lane);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                x2[u] = bfly4(x4[2 * u], x4[2 * u + 1], lane);
+            float t = bfly2(x2[0], x2[1], lane);
+            t += dpp_mov<DPP_QUAD_XOR1>(t);
+            const int r = qi < Q ? qi / G : 0;
+            const bool ok = qi < Q && key < ctx && key <= pos + r;
+            const float sv = ok ? t : -INFINITY;
+            const float mn = fmaxf(mx[qi], wave_max_all(sv));
+            const float p = mn == -INFINITY ? 0.0f : expf(sv - mn);
+            if (kb > c0) {  // uniform: what the earlier blocks left, at the new maximum
+                const float sc = mx[qi] == -INFINITY ? 0.0f : expf(mx[qi] - mn);
+                ls[qi] *= sc;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    o[qi][u] *= sc;
+            }
+            mx[qi] = mn;
+            ls[qi] += wave_sum_all(b0 ? 0.0f : p);
+            if (!b0)
+                sp[wave][qi][8 * j4 + row] = p;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // O += sum over the rows of p V, for the lane's 8 elements
+#pragma unroll
+        for (int qi = 0; qi < QV; ++qi) {
+            const f32x4_t pa = *reinterpret_cast<const f32x4_t *>(&sp[wave][qi][8 * j4]);
+            const f32x4_t pb = *reinterpret_cast<const f32x4_t *>(&sp[wave][qi][8 * j4 + 4]);
+            const float pw[8] = {pa[0], pa[1], pa[2], pa[3], pb[0], pb[1], pb[2], pb[3]};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float vx[8];
+                unpack8_bf16(vr[i], vx);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    o[qi][u] = fmaf(pw[i], vx[u], o[qi][u]);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 #pragma unroll
     for (int qi = 0; qi < QV; ++qi) {
@@ -1018,24 +1065,32 @@ static hipError_t launch_attn_head(const AttnArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Query vectors per kv head from which bfloat16 caches take the MFMA kernel.
-constexpr int ATTN_MFMA_MIN_Q = 1;
+// Key blocks per work-group: one while that gives at most ATTN_GROUPS
+// work-groups (five per CU), else as many as bring them back to that.
+constexpr int ATTN_GROUPS = 1280;
+static int attn_blocks(int ctx_max, int block, int rows) {
+    const int64_t groups = (int64_t)((ctx_max + block - 1) / block) * rows;
+    return (int)((groups + ATTN_GROUPS - 1) / ATTN_GROUPS);
+}
 
 hipError_t launch_attention(const AttnArgs &a0, bool bf16, int max_rows, hipStream_t s) {
-    if (a0.cap < 1 || a0.cap > MAX_CONTEXT)
+    if (a0.cap < 1 || a0.cap > MAX_CONTEXT || a0.ctx_max < 1 || a0.ctx_max > a0.cap)
         return hipErrorInvalidValue;
     AttnArgs a = a0;
     const int G = a.n_heads / a.n_kv_heads;
     const int max_q = G * max_rows;
     // one work-group per kv head while the context is short and the query
     // vectors per head fit; otherwise split the keys over work-groups
-    if (max_q <= QH && a.cap <= 256)
+    if (max_q <= QH && a.ctx_max <= 256)
         return bf16 ? launch_attn_head<uint16_t>(a, s) : launch_attn_head<float>(a, s);
     // (the workspace holds the partials of 64-key chunks whenever a model can
     // take this path: attn_chunk_min)
     const bool valu = bf16 && a.head_dim == 128 && max_q <= 2;
-    a.chunk = valu ? ATTN_CHUNK_VALU : ATTN_CHUNK;
-    a.splits = (a.cap + a.chunk - 1) / a.chunk;
+    const bool mfma = bf16 && a.head_dim >= 32;
+    a.chunk = valu   ? ATTN_CHUNK_VALU * attn_blocks(a.ctx_max, ATTN_CHUNK_VALU, a.n_kv_heads)
+              : mfma ? ATTN_CHUNK * attn_blocks(a.ctx_max, ATTN_CHUNK, a.n_kv_heads * ((max_q + 15) / 16))
+                     : ATTN_CHUNK;
+    a.splits = (a.ctx_max + a.chunk - 1) / a.chunk;
     hipError_t e = hipSuccess;
     if (valu) {
         // one or two query vectors per kv head: VALU tiles
@@ -1043,7 +1098,7 @@ hipError_t launch_attention(const AttnArgs &a0, bool bf16, int max_rows, hipStre
             hipLaunchKernelGGL(k_attn_valu<1>, dim3(a.splits, a.n_kv_heads), dim3(VW * 64), 0, s, a);
         else
             hipLaunchKernelGGL(k_attn_valu<2>, dim3(a.splits, a.n_kv_heads), dim3(VW * 64), 0, s, a);
-    } else if (bf16 && a.head_dim >= 32 && max_q >= ATTN_MFMA_MIN_Q)
+    } else if (mfma)
         e = launch_attn_mfma(a, max_q, s);
     else
         e = bf16 ? launch_attn_split<uint16_t>(a, max_q, s) : launch_attn_split<float>(a, max_q, s);

@@ -493,12 +493,13 @@ struct HeadSpec {
 struct ForwardCursor {
     const Plan *P = nullptr;
     int max_rows = 0;
+    int ctx_max = 0;       // host bound on the positions after this forward
     int next_layer = 0;
     int pending = 0;       // split-K partials not yet folded into h
     bool guarded = false;  // launches may find the step cancelled (ctl->m = 0)
 };
 
-sd_status forward_begin(sd_model *m, const Workspace &w, int max_rows, ForwardCursor *cur) {
+sd_status forward_begin(sd_model *m, const Workspace &w, int max_rows, int ctx_max, ForwardCursor *cur) {
     const Plan *P = max_rows <= 1 ? m->plan1 : (max_rows <= 2 ? m->plan2 : m->planm);
     // The measurement hook times the class in one of every TIMED_SAMPLE
     // forwards of its regime, with events the runtime attaches to the
@@ -508,6 +509,7 @@ sd_status forward_begin(sd_model *m, const Workspace &w, int max_rows, ForwardCu
     *cur = ForwardCursor{};
     cur->P = P;
     cur->max_rows = max_rows;
+    cur->ctx_max = ctx_max;
     return launch(launch_embed(m->tok_emb, m->bf16, m->cfg.d_model, w.ctl, w.h, m->cfg.d_model, m->stream),
                   "embedding");
 }
@@ -568,6 +570,7 @@ sd_status forward_layers(sd_model *m, const Workspace &w, void *kv, int32_t cap,
             at.n_kv_heads = c.n_kv_heads;
             at.head_dim = c.head_dim;
             at.cap = cap;
+            at.ctx_max = cur->ctx_max;
             at.ctl = w.ctl;
             SD_TRY(launch(launch_attention(at, m->bf16, max_rows, m->stream), "attention"));
             EpiArgs eo{};
@@ -626,9 +629,9 @@ sd_status forward_head(sd_model *m, const Workspace &w, ForwardCursor *cur, cons
 }
 
 sd_status enqueue_forward(sd_model *m, const Workspace &w, void *kv, int32_t cap, const uint8_t *skip, int max_rows,
-                          const HeadSpec &hs) {
+                          int ctx_max, const HeadSpec &hs) {
     ForwardCursor cur;
-    SD_TRY(forward_begin(m, w, max_rows, &cur));
+    SD_TRY(forward_begin(m, w, max_rows, ctx_max, &cur));
     SD_TRY(forward_layers(m, w, kv, cap, skip, &cur, m->cfg.n_layers));
     return forward_head(m, w, &cur, hs);
 }
@@ -871,7 +874,7 @@ sd_status enqueue_prefill(sd_model *m, sd_kv_cache *kc, const int32_t *dev_token
     for (int32_t c = 0; c < n; c += MAX_ROWS) {
         const int32_t rows = std::min<int32_t>(MAX_ROWS, n - c);
         SD_TRY(launch(launch_set_ctl(m->ws.ctl, start + c, rows, dev_tokens + c, m->stream), "control block"));
-        SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, nullptr, rows, HeadSpec{}));
+        SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, nullptr, rows, start + c + rows, HeadSpec{}));
     }
     return SD_OK;
 }
@@ -1087,10 +1090,14 @@ sd_status self_spec(sd_model *m, const int32_t *prompt, int32_t prompt_len, int3
         }
         open_slots.erase(open_slots.begin(), open_slots.begin() + (ptrdiff_t)n);
     };
+    // Bound on the positions a step enqueued now can end at: the committed
+    // tokens the host has seen, plus what the verification in flight can
+    // commit, plus the step's own rows.
+    int ctx_bound = prompt_len + 2 * (k_max + 1);
     auto begin_step = [&](const Step &st, ForwardCursor *cur) -> sd_status {
         SD_TRY(slot_open());
         SD_TRY(launch(launch_step_guard(w.ctl, m->st, st.phase, st.rows, m->stream), "step guard"));
-        SD_TRY(forward_begin(m, w, st.rows, cur));
+        SD_TRY(forward_begin(m, w, st.rows, std::min(kc->cap, ctx_bound), cur));
         cur->guarded = true;
         return forward_layers(m, w, kc->buf, kc->cap, st.phase == PHASE_DRAFT ? skip : nullptr, cur,
                               st.phase == PHASE_DRAFT ? split_draft : split_verify);
@@ -1138,8 +1145,10 @@ sd_status self_spec(sd_model *m, const int32_t *prompt, int32_t prompt_len, int3
             uint64_t word = 0;
             SD_TRY(wait_mailbox(m, seq, &word));
             account(2);  // the current step's end event and the part ahead may still be pending
-            if (cur_step.phase == PHASE_VERIFY)
+            if (cur_step.phase == PHASE_VERIFY) {
                 kcap = std::min(k_max, max_new - mb_emitted(word) - 1);
+                ctx_bound = prompt_len + mb_emitted(word) + 2 * (k_max + 1);
+            }
             const bool done = mb_done(word);
             const Step truth{mb_phase(word), mb_phase(word) == PHASE_DRAFT ? 1 : stage_k + 1};
             if (!done && truth.phase == pred.phase && truth.rows == pred.rows) {
@@ -1189,7 +1198,7 @@ sd_status autoregressive(sd_model *m, const int32_t *prompt, int32_t prompt_len,
     hs.mode = HEAD_AR;
     hs.sampled = sp != nullptr;
     for (int32_t i = 0; i < max_new; ++i)
-        SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, nullptr, 1, hs));
+        SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, nullptr, 1, prompt_len + i, hs));
     SD_HIP(hipEventRecord(m->ev[2], m->stream));
     SD_TRY(copy_results(m, max_new, out_tokens, stats));
     if (stats) {
@@ -1234,7 +1243,7 @@ sd_status forward(sd_model *m, const int32_t *tokens, int32_t n, const uint8_t *
         hs.run = logits != nullptr;
         hs.mode = HEAD_NONE;
         hs.logits = logits ? logits + (size_t)c * m->cfg.vocab : nullptr;
-        SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, skip, rows, hs));
+        SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, skip, rows, kc->len + c + rows, hs));
     }
     SD_HIP(hipStreamSynchronize(m->stream));
     collect_timing(m);
@@ -1351,7 +1360,7 @@ sd_status forward_static(sd_model *m, const int32_t *tokens, int32_t n, const ui
     // the measurement hook's events stay out of this path
     const int timed = m->timed_kind;
     m->timed_kind = -1;
-    const sd_status st = enqueue_forward(m, w, kc->buf, kc->cap, skip, n, hs);
+    const sd_status st = enqueue_forward(m, w, kc->buf, kc->cap, skip, n, kc->len + n, hs);
     m->timed_kind = timed;
     SD_TRY(st);
     SD_HIP(hipStreamSynchronize(m->stream));

@@ -251,6 +251,7 @@ struct AttnArgs {
     int64_t ld_out;
     int32_t n_heads, n_kv_heads, head_dim;
     int32_t cap;           // cache capacity: positions past it are never read
+    int32_t ctx_max;       // host bound on the context (ctl->pos + ctl->m): sizes the grid
     int32_t splits, chunk; // set by launch_attention: key chunks and keys per chunk
     const DevCtl *ctl;
 };
