@@ -164,12 +164,11 @@ __device__ void decode_decision(const HeadArgs &h, DevCtl *ctl, const int *y, co
     }
 }
 
-// One work-group after the head: combine the per-tile partials of every
-// row in a fixed order (deterministic), then take the decoding decision.
-// Thread j takes tiles j, j + 256, ... of every row; the loads of up to
-// HF_BATCH tiles per thread are issued together (one round trip for up to
-// 4096 tiles), then the 256 partial results of a row are combined by a
-// fixed tree across lanes and waves.
+// One work-group after the head: combine the per-tile partials of every row
+// in a fixed order (deterministic), then take the decoding decision.  The
+// waves are dealt to the rows (16 on one row, one on each of 9 to 16), so the
+// loads of all rows are in flight together: with four waves taking the rows in
+// turn, 13 rows of the 13B head took 39 us, one row 8.
 __device__ HeadPart head_shfl(HeadPart v, int o) {
     HeadPart r;
     r.mx = __shfl_xor(v.mx, o, 64);
@@ -178,40 +177,43 @@ __device__ HeadPart head_shfl(HeadPart v, int o) {
     return r;
 }
 
-constexpr int HF_THREADS = 256;
-constexpr int HF_BATCH = 16;
+constexpr int HF_WAVES = 16;
+constexpr int HF_THREADS = 64 * HF_WAVES;
+constexpr int HF_BATCH = 8;  // loads in flight per thread
 
 __device__ void head_finalize(const LinearArgs &a, int n_tiles, int M) {
-    constexpr int NWF = HF_THREADS / 64;
-    __shared__ HeadPart wred[NWF][MAX_ROWS];
+    static_assert(MAX_ROWS <= HF_WAVES, "a wave per row");
+    __shared__ HeadPart wred[HF_WAVES];
     __shared__ int ys[MAX_ROWS];
     __shared__ float ps[MAX_ROWS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const HeadArgs &h = a.epi.head;
-    for (int m = 0; m < M; ++m) {
-        HeadPart acc = head_empty();
-        for (int t0 = 0; t0 < n_tiles; t0 += HF_THREADS * HF_BATCH) {
+    const int per = HF_WAVES / M, m = wave / per, first = (wave - m * per) * 64 + lane, step = 64 * per;
+    HeadPart acc = head_empty();
+    if (m < M) {
+        const float4 *p = h.partials + (int64_t)m * n_tiles;
+        for (int t0 = first; t0 < n_tiles; t0 += step * HF_BATCH) {
             // tiles past n_tiles read the last one and are skipped
             float4 v[HF_BATCH];
 #pragma unroll
             for (int u = 0; u < HF_BATCH; ++u)
-                v[u] = h.partials[(int64_t)min(t0 + tid + HF_THREADS * u, n_tiles - 1) * MAX_ROWS + m];
+                v[u] = p[min(t0 + step * u, n_tiles - 1)];
 #pragma unroll
             for (int u = 0; u < HF_BATCH; ++u)
-                if (t0 + tid + HF_THREADS * u < n_tiles)
+                if (t0 + step * u < n_tiles)
                     acc = head_comb(acc, HeadPart{v[u].x, __float_as_int(v[u].y), v[u].z});
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1)
             acc = head_comb(acc, head_shfl(acc, o));
-        if (lane == 0)
-            wred[wave][m] = acc;
     }
+    if (lane == 0)
+        wred[wave] = acc;
     __syncthreads();
     if (tid < M) {
-        HeadPart r = wred[0][tid];
-        for (int w = 1; w < NWF; ++w)
-            r = head_comb(r, wred[w][tid]);
+        HeadPart r = wred[tid * per];
+        for (int w = 1; w < per; ++w)
+            r = head_comb(r, wred[tid * per + w]);
         ys[tid] = r.idx;
         ps[tid] = 1.0f / r.sum;
     }
@@ -323,33 +325,38 @@ __device__ __forceinline__ void run_epilogue(const LinearArgs &a, float *fin, in
         }
     } else if constexpr (EPI == EPI_HEAD) {
         const HeadArgs &h = e.head;
+        // The greedy decision needs each tile's maximum, its first index and
+        // the sum of exponentials; a forward that only returns logits, and the
+        // sampling kernels, do not.  R (a power of two up to 16) consecutive
+        // lanes hold a row's values of the tile (13B head, 13 rows, logits
+        // only: 75 us with one thread per row walking them, 61 without the
+        // statistics).
+        const bool stats = h.mode != HEAD_NONE && !h.sampled;
         for (int j = tid; j < R * M; j += blockDim.x) {
             const int i = j % R, m = j / R, n = t * R + i;
-            if (n < a.N) {
-                const float v = fin[i * MR + m] * inv[m];
-                fin[i * MR + m] = v;
-                if (h.logits)
-                    h.logits[(int64_t)(h.logits_by_draft ? h.st->k : m) * h.ld_logits + n] = v;
-            }
-        }
-        __syncthreads();
-        if (tid < M) {
-            const int m = tid;
-            float mx = -INFINITY;
-            int ix = 0x7fffffff;
-            for (int i = 0; i < R && t * R + i < a.N; ++i) {
-                const float v = fin[i * MR + m];
-                if (v > mx) {
-                    mx = v;
-                    ix = t * R + i;
+            const bool ok = n < a.N;
+            const float v = fin[i * MR + m] * inv[m];
+            if (ok && h.logits)
+                h.logits[(int64_t)(h.logits_by_draft ? h.st->k : m) * h.ld_logits + n] = v;
+            if (!stats)
+                continue;
+            const bool some = ok && v > -INFINITY;
+            float mx = some ? v : -INFINITY;
+            int ix = some ? n : 0x7fffffff;
+            for (int o = 1; o < R; o <<= 1) {
+                const float m2 = __shfl_xor(mx, o, 64);
+                const int i2 = __shfl_xor(ix, o, 64);
+                if (m2 > mx || (m2 == mx && i2 < ix)) {
+                    mx = m2;
+                    ix = i2;
                 }
             }
-            float s = 0.0f;
-            for (int i = 0; i < R && t * R + i < a.N; ++i)
-                s += expf(fin[i * MR + m] - mx);
-            h.partials[(int64_t)t * MAX_ROWS + m] = make_float4(mx, __int_as_float(ix), s, 0.0f);
+            float s = ok ? expf(v - mx) : 0.0f;
+            for (int o = 1; o < R; o <<= 1)
+                s += __shfl_xor(s, o, 64);
+            if (i == 0)
+                h.partials[(int64_t)m * a.n_tiles + t] = make_float4(mx, __int_as_float(ix), s, 0.0f);
         }
-        __syncthreads();
     }
 }
 

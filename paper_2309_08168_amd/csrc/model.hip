@@ -459,7 +459,7 @@ sd_status run_linear(sd_model *m, const Workspace &w, const Plan &p, int max_row
         sa.dstat = m->sdstat;
         sa.head = epi.head;
         SD_TRY(launch(launch_sample_step(sa, max_rows, m->stream), "sampling step"));
-    } else if (p.epi == EPI_HEAD) {
+    } else if (p.epi == EPI_HEAD && epi.head.mode != HEAD_NONE) {
         SD_TRY(launch(launch_head_finalize(a, p.n_tiles, m->stream), "head finalize"));
     }
     return SD_OK;

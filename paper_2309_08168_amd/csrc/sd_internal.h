@@ -152,7 +152,7 @@ struct HeadArgs {
     int32_t mode;
     float *logits;       // optional float32 [m][ld_logits]
     int64_t ld_logits;
-    float4 *partials;    // [n_tiles][MAX_ROWS]: (max, argmax bits, sum exp(l - max), 0)
+    float4 *partials;    // [rows][n_tiles]: (max, argmax bits, sum exp(l - max), 0)
     DevState *st;
     Mailbox *mb;         // device view of the pinned mailbox (HEAD_DRAFT / HEAD_VERIFY)
     int32_t *out_tokens;
