@@ -743,16 +743,19 @@ __global__ __launch_bounds__(VW * 64) void k_attn_valu(AttnArgs a) {
 
 // Decode attention without a combine pass: one work-group of HW waves per
 // kv head, for up to QH query vectors (the draft, autoregressive and short
-// verification steps of multi-head attention).  Wave w takes the 16-key
+// verification steps of multi-head attention; up to QH_WIDE on caches the
+// matrix-core kernel does not take, where a second kernel and a combine would
+// cost more than walking the vectors: the tiny float32 model's verification of
+// 5 rows, 12.4 -> 10.6 us a layer).  Wave w takes the 16-key
 // blocks w, w + HW, ...; within a block, lane group j (16 lanes) takes keys
 // j, j + 4, j + 8, j + 12 and lane e16 holds head_dim / 16 elements.  Each
 // group keeps an online-softmax state; the block after next is loaded while
 // the current one is used.  The groups merge by shuffles, the waves in LDS
 // in wave order, and the result goes straight to the output.
-constexpr int QH = 4;
+constexpr int QH_NARROW = 4, QH_WIDE = 8;
 constexpr int HW = 8;
 
-template <typename TK, int ED, int NWV = HW>
+template <typename TK, int ED, int QH, int NWV = HW>
 __global__ __launch_bounds__(NWV * 64) void k_attn_head(AttnArgs a) {
     __shared__ float wst[NWV][QH][2];
     __shared__ float wo[NWV][QH][MAX_HEAD_DIM];
@@ -1043,21 +1046,22 @@ static hipError_t launch_attn_mfma(const AttnArgs &a, int max_q, hipStream_t s) 
     return hipSuccess;
 }
 
-template <typename TK>
+template <typename TK, int QH>
 static hipError_t launch_attn_head(const AttnArgs &a, hipStream_t s) {
     dim3 grid(a.n_kv_heads), block(HW * 64);
     switch (a.head_dim) {
     case 16:
-        hipLaunchKernelGGL((k_attn_head<TK, 1>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_attn_head<TK, 1, QH>), grid, block, 0, s, a);
         break;
     case 32:
-        hipLaunchKernelGGL((k_attn_head<TK, 2>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_attn_head<TK, 2, QH>), grid, block, 0, s, a);
         break;
     case 64:
-        hipLaunchKernelGGL((k_attn_head<TK, 4>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_attn_head<TK, 4, QH>), grid, block, 0, s, a);
         break;
     case 128:
-        hipLaunchKernelGGL((k_attn_head<TK, 8>), grid, block, 0, s, a);
+        // (eight elements per lane: no room for the wide form)
+        hipLaunchKernelGGL((k_attn_head<TK, 8, QH_NARROW>), grid, block, 0, s, a);
         break;
     default:
         return hipErrorInvalidValue;
@@ -1081,12 +1085,14 @@ hipError_t launch_attention(const AttnArgs &a0, bool bf16, int max_rows, hipStre
     const int max_q = G * max_rows;
     // one work-group per kv head while the context is short and the query
     // vectors per head fit; otherwise split the keys over work-groups
-    if (max_q <= QH && a.ctx_max <= 256)
-        return bf16 ? launch_attn_head<uint16_t>(a, s) : launch_attn_head<float>(a, s);
+    if (max_q <= QH_NARROW && a.ctx_max <= 256)
+        return bf16 ? launch_attn_head<uint16_t, QH_NARROW>(a, s) : launch_attn_head<float, QH_NARROW>(a, s);
+    const bool mfma = bf16 && a.head_dim >= 32;
+    if (!mfma && a.head_dim <= 64 && max_q <= QH_WIDE && a.ctx_max <= 256)
+        return bf16 ? launch_attn_head<uint16_t, QH_WIDE>(a, s) : launch_attn_head<float, QH_WIDE>(a, s);
     // (the workspace holds the partials of 64-key chunks whenever a model can
     // take this path: attn_chunk_min)
     const bool valu = bf16 && a.head_dim == 128 && max_q <= 2;
-    const bool mfma = bf16 && a.head_dim >= 32;
     a.chunk = valu   ? ATTN_CHUNK_VALU * attn_blocks(a.ctx_max, ATTN_CHUNK_VALU, a.n_kv_heads)
               : mfma ? ATTN_CHUNK * attn_blocks(a.ctx_max, ATTN_CHUNK, a.n_kv_heads * ((max_q + 15) / 16))
                      : ATTN_CHUNK;
@@ -1119,34 +1125,23 @@ hipError_t launch_attention(const AttnArgs &a0, bool bf16, int max_rows, hipStre
 // embedding row of token r, 8 per thread with one load each, so every load
 // of the row is in flight at once (d is a multiple of 8).
 template <typename TW>
-__global__ __launch_bounds__(256) void k_embed(const TW *E, int d, const DevCtl *ctl, float *h, int64_t ldh) {
-    const int r = blockIdx.x;
-    if (r >= ctl->m)
-        return;
+__device__ __forceinline__ void embed_slice(const TW *E, int d, int token, float *h) {
     const int i = (blockIdx.y * 256 + threadIdx.x) * 8;
     if (i >= d)
         return;
-    const TW *src = E + (int64_t)ctl->tokens[r] * d + i;
+    const TW *src = E + (int64_t)token * d + i;
     float v[8];
-    if constexpr (sizeof(TW) == 2) {
-        const u32x4_t w = *reinterpret_cast<const u32x4_t *>(src);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            v[2 * j] = __uint_as_float(w[j] << 16);
-            v[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-        }
-    } else {
-        const f32x4_t a = reinterpret_cast<const f32x4_t *>(src)[0];
-        const f32x4_t b = reinterpret_cast<const f32x4_t *>(src)[1];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            v[j] = a[j];
-            v[4 + j] = b[j];
-        }
-    }
-    f32x4_t *dst = reinterpret_cast<f32x4_t *>(h + (int64_t)r * ldh + i);
+    load8_kv(src, v);
+    f32x4_t *dst = reinterpret_cast<f32x4_t *>(h + i);
     dst[0] = f32x4_t{v[0], v[1], v[2], v[3]};
     dst[1] = f32x4_t{v[4], v[5], v[6], v[7]};
+}
+
+template <typename TW>
+__global__ __launch_bounds__(256) void k_embed(const TW *E, int d, const DevCtl *ctl, float *h, int64_t ldh) {
+    const int r = blockIdx.x;
+    if (r < ctl->m)
+        embed_slice(E, d, ctl->tokens[r], h + (int64_t)r * ldh);
 }
 
 hipError_t launch_embed(const void *emb, bool bf16, int d, const DevCtl *ctl, float *h, int64_t ldh,
@@ -1178,29 +1173,42 @@ hipError_t launch_set_ctl(DevCtl *ctl, int32_t pos, int32_t m, const int32_t *de
     return hipGetLastError();
 }
 
-// The control block from host values passed by value (no copy from host
-// memory): up to MAX_ROWS tokens.
+// The same with the control block's values and the tokens (m <= MAX_ROWS) passed
+// by value: no copy from host memory and no launch of its own for the control
+// block, which the first work-group writes for the kernels that follow.
 struct CtlTokens {
     int32_t t[MAX_ROWS];
 };
 
-__global__ void k_set_ctl_value(DevCtl *ctl, int32_t pos, int32_t m, CtlTokens tokens) {
-    const int i = threadIdx.x;
-    if (i == 0) {
-        ctl->pos = pos;
-        ctl->m = m;
+template <typename TW>
+__global__ __launch_bounds__(256) void k_embed_host(const TW *E, int d, DevCtl *ctl, int32_t pos, int32_t m,
+                                                    CtlTokens tokens, float *h, int64_t ldh) {
+    const int r = blockIdx.x;
+    if (r == 0 && blockIdx.y == 0) {
+        if (threadIdx.x == 0) {
+            ctl->pos = pos;
+            ctl->m = m;
+        }
+        if ((int)threadIdx.x < m)
+            ctl->tokens[threadIdx.x] = tokens.t[threadIdx.x];
     }
-    if (i < m)
-        ctl->tokens[i] = tokens.t[i];
+    embed_slice(E, d, tokens.t[r], h + (int64_t)r * ldh);
 }
 
-hipError_t launch_set_ctl_host(DevCtl *ctl, int32_t pos, int32_t m, const int32_t *host_tokens, hipStream_t s) {
-    if (m < 1 || m > MAX_ROWS)
+hipError_t launch_embed_host(const void *emb, bool bf16, int d, DevCtl *ctl, int32_t pos, int32_t m,
+                             const int32_t *host_tokens, float *h, int64_t ldh, hipStream_t s) {
+    if ((d & 7) || (ldh & 7) || m < 1 || m > MAX_ROWS)
         return hipErrorInvalidValue;
     CtlTokens t{};
     for (int i = 0; i < m; ++i)
         t.t[i] = host_tokens[i];
-    hipLaunchKernelGGL(k_set_ctl_value, dim3(1), dim3(64), 0, s, ctl, pos, m, t);
+    const dim3 grid(m, (d + 2047) / 2048);
+    if (bf16)
+        hipLaunchKernelGGL(k_embed_host<uint16_t>, grid, dim3(256), 0, s, reinterpret_cast<const uint16_t *>(emb), d,
+                           ctl, pos, m, t, h, ldh);
+    else
+        hipLaunchKernelGGL(k_embed_host<float>, grid, dim3(256), 0, s, reinterpret_cast<const float *>(emb), d, ctl,
+                           pos, m, t, h, ldh);
     return hipGetLastError();
 }
 

@@ -499,7 +499,10 @@ struct ForwardCursor {
     bool guarded = false;  // launches may find the step cancelled (ctl->m = 0)
 };
 
-sd_status forward_begin(sd_model *m, const Workspace &w, int max_rows, int ctx_max, ForwardCursor *cur) {
+// host_tokens: the max_rows tokens of a forward that ends at ctx_max, or null
+// when the control block on the device holds the step.
+sd_status forward_begin(sd_model *m, const Workspace &w, int max_rows, int ctx_max, ForwardCursor *cur,
+                        const int32_t *host_tokens = nullptr) {
     const Plan *P = max_rows <= 1 ? m->plan1 : (max_rows <= 2 ? m->plan2 : m->planm);
     // The measurement hook times the class in one of every TIMED_SAMPLE
     // forwards of its regime, with events the runtime attaches to the
@@ -510,6 +513,10 @@ sd_status forward_begin(sd_model *m, const Workspace &w, int max_rows, int ctx_m
     cur->P = P;
     cur->max_rows = max_rows;
     cur->ctx_max = ctx_max;
+    if (host_tokens)
+        return launch(launch_embed_host(m->tok_emb, m->bf16, m->cfg.d_model, w.ctl, ctx_max - max_rows, max_rows,
+                                        host_tokens, w.h, m->cfg.d_model, m->stream),
+                      "embedding");
     return launch(launch_embed(m->tok_emb, m->bf16, m->cfg.d_model, w.ctl, w.h, m->cfg.d_model, m->stream),
                   "embedding");
 }
@@ -629,9 +636,9 @@ sd_status forward_head(sd_model *m, const Workspace &w, ForwardCursor *cur, cons
 }
 
 sd_status enqueue_forward(sd_model *m, const Workspace &w, void *kv, int32_t cap, const uint8_t *skip, int max_rows,
-                          int ctx_max, const HeadSpec &hs) {
+                          int ctx_max, const HeadSpec &hs, const int32_t *host_tokens = nullptr) {
     ForwardCursor cur;
-    SD_TRY(forward_begin(m, w, max_rows, ctx_max, &cur));
+    SD_TRY(forward_begin(m, w, max_rows, ctx_max, &cur, host_tokens));
     SD_TRY(forward_layers(m, w, kv, cap, skip, &cur, m->cfg.n_layers));
     return forward_head(m, w, &cur, hs);
 }
@@ -1231,19 +1238,23 @@ sd_status forward(sd_model *m, const int32_t *tokens, int32_t n, const uint8_t *
         return fail(SD_ERR_CAPACITY, "cache of capacity " + std::to_string(kc->cap) + " holds " +
                                          std::to_string(kc->len) + " positions; " + std::to_string(n) +
                                          " more do not fit");
-    SD_TRY(ensure_buf(m, &m->d_tokens, &m->d_tokens_cap, n));
-    SD_HIP(hipMemcpyAsync(m->d_tokens, tokens, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, m->stream));
-    for (int32_t c = 0; m->pf_ok && n > MAX_ROWS && c < n; c += PF_ROWS)
-        SD_TRY(enqueue_forward_large(m, kc->buf, kc->cap, skip, m->d_tokens + c, std::min(PF_ROWS, n - c),
-                                     kc->len + c, logits ? logits + (size_t)c * m->cfg.vocab : nullptr));
-    for (int32_t c = 0; !(m->pf_ok && n > MAX_ROWS) && c < n; c += MAX_ROWS) {
-        const int32_t rows = std::min<int32_t>(MAX_ROWS, n - c);
-        SD_TRY(launch(launch_set_ctl(m->ws.ctl, kc->len + c, rows, m->d_tokens + c, m->stream), "control block"));
-        HeadSpec hs;
-        hs.run = logits != nullptr;
-        hs.mode = HEAD_NONE;
-        hs.logits = logits ? logits + (size_t)c * m->cfg.vocab : nullptr;
-        SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, skip, rows, kc->len + c + rows, hs));
+    if (m->pf_ok && n > MAX_ROWS) {
+        SD_TRY(ensure_buf(m, &m->d_tokens, &m->d_tokens_cap, n));
+        SD_HIP(hipMemcpyAsync(m->d_tokens, tokens, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, m->stream));
+        for (int32_t c = 0; c < n; c += PF_ROWS)
+            SD_TRY(enqueue_forward_large(m, kc->buf, kc->cap, skip, m->d_tokens + c, std::min(PF_ROWS, n - c),
+                                         kc->len + c, logits ? logits + (size_t)c * m->cfg.vocab : nullptr));
+    } else {
+        // the tokens travel with the embedding launch: a copy of a few bytes
+        // from pageable memory, and a launch for the control block, cost more
+        for (int32_t c = 0; c < n; c += MAX_ROWS) {
+            const int32_t rows = std::min<int32_t>(MAX_ROWS, n - c);
+            HeadSpec hs;
+            hs.run = logits != nullptr;
+            hs.mode = HEAD_NONE;
+            hs.logits = logits ? logits + (size_t)c * m->cfg.vocab : nullptr;
+            SD_TRY(enqueue_forward(m, m->ws, kc->buf, kc->cap, skip, rows, kc->len + c + rows, hs, tokens + c));
+        }
     }
     SD_HIP(hipStreamSynchronize(m->stream));
     collect_timing(m);
@@ -1352,7 +1363,6 @@ sd_status forward_static(sd_model *m, const int32_t *tokens, int32_t n, const ui
     SD_TRY(launch(launch_fill_zero(w.o, sizeof(float) * MAX_ROWS * m->cfg.n_heads * m->cfg.head_dim, m->stream),
                   "scratch clear"));
     SD_TRY(launch(launch_fill_zero(w.mbuf, sizeof(float) * MAX_ROWS * m->cfg.ffn_dim, m->stream), "scratch clear"));
-    SD_TRY(launch(launch_set_ctl_host(w.ctl, kc->len, n, tokens, m->stream), "control block"));
     HeadSpec hs;
     hs.run = logits != nullptr;
     hs.mode = HEAD_NONE;
@@ -1360,7 +1370,7 @@ sd_status forward_static(sd_model *m, const int32_t *tokens, int32_t n, const ui
     // the measurement hook's events stay out of this path
     const int timed = m->timed_kind;
     m->timed_kind = -1;
-    const sd_status st = enqueue_forward(m, w, kc->buf, kc->cap, skip, n, kc->len + n, hs);
+    const sd_status st = enqueue_forward(m, w, kc->buf, kc->cap, skip, n, kc->len + n, hs, tokens);
     m->timed_kind = timed;
     SD_TRY(st);
     SD_HIP(hipStreamSynchronize(m->stream));
