@@ -741,57 +741,43 @@ __global__ __launch_bounds__(VW * 64) void k_attn_valu(AttnArgs a) {
     }
 }
 
-// Decode attention without a combine pass: one work-group of HW waves per
-// kv head, for up to QH query vectors (the draft, autoregressive and short
-// verification steps of multi-head attention; up to QH_WIDE on caches the
-// matrix-core kernel does not take, where a second kernel and a combine would
-// cost more than walking the vectors: the tiny float32 model's verification of
-// 5 rows, 12.4 -> 10.6 us a layer).  Wave w takes the 16-key
-// blocks w, w + HW, ...; within a block, lane group j (16 lanes) takes keys
-// j, j + 4, j + 8, j + 12 and lane e16 holds head_dim / 16 elements.  Each
-// group keeps an online-softmax state; the block after next is loaded while
-// the current one is used.  The groups merge by shuffles, the waves in LDS
-// in wave order, and the result goes straight to the output.
-constexpr int QH_NARROW = 4, QH_WIDE = 8;
+// Decode attention without a combine pass, for short contexts: one work-group
+// of HW waves per query vector.  Wave w takes the 16-key blocks w, w + HW, ...;
+// within a block, lane group j (16 lanes) takes keys j, j + 4, j + 8, j + 12 and
+// lane e16 holds head_dim / 16 elements.  Each lane group keeps an
+// online-softmax state; the block after next is loaded while the current one
+// is used.  The groups merge by shuffles, the waves in LDS in wave order, and
+// the result goes straight to the output.  The vectors of a kv head read the
+// same few keys from L2: walking them in one work-group made the tiny float32
+// model's verification of 5 rows 10.6 us a layer against 4.8 (12.4 split over
+// the keys and combined), 4-layer 13B forwards of 4 rows over 230 keys 638 us
+// against 612 (split and combined 13 rows over 100 keys: 714 against 707).
 constexpr int HW = 8;
 
-template <typename TK, int ED, int QH, int NWV = HW>
-__global__ __launch_bounds__(NWV * 64) void k_attn_head(AttnArgs a) {
-    __shared__ float wst[NWV][QH][2];
-    __shared__ float wo[NWV][QH][MAX_HEAD_DIM];
-    const int g = blockIdx.x;
+template <typename TK, int ED>
+__global__ __launch_bounds__(HW * 64) void k_attn_head(AttnArgs a) {
+    __shared__ float wst[HW][2];
+    __shared__ float wo[HW][MAX_HEAD_DIM];
+    const int g = blockIdx.x, qi = blockIdx.y;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int pos = a.ctl->pos, M = a.ctl->m;
-    if (M == 0)
-        return;  // a cancelled step
+    const int dh = a.head_dim, H = a.n_heads, G = H / a.n_kv_heads;
+    if (qi >= G * M)
+        return;  // uniform over the work-group (M = 0: a cancelled step)
     const int ctx = pos + M;
-    const int dh = a.head_dim, H = a.n_heads;
-    const int G = H / a.n_kv_heads;
-    const int nq = G * M;  // <= QH, checked by the host
+    const int r = qi / G, head = g * G + (qi - r * G), lim = pos + r;
     const int ks = lane >> 4, e16 = lane & 15;
     const TK *Kg = reinterpret_cast<const TK *>(a.kcache) + (int64_t)g * a.kv_head_stride + e16 * ED;
     const TK *Vg = reinterpret_cast<const TK *>(a.vcache) + (int64_t)g * a.kv_head_stride + e16 * ED;
     const float scale = 1.0f / sqrtf((float)dh);
 
-    float qv[QH][ED], o[QH][ED], mr[QH], lr[QH];
-    int lim[QH];
-#pragma unroll
-    for (int qi = 0; qi < QH; ++qi) {
-        mr[qi] = -INFINITY;
-        lr[qi] = 0.0f;
-        lim[qi] = -1;
+    float qv[ED], o[ED], mr = -INFINITY, lr = 0.0f;
+    {
+        const float *qs = a.q + (int64_t)r * a.ld_q + (int64_t)head * dh + e16 * ED;
 #pragma unroll
         for (int e = 0; e < ED; ++e) {
-            qv[qi][e] = 0.0f;
-            o[qi][e] = 0.0f;
-        }
-        if (qi < nq) {
-            const int r = qi / G, head = g * G + (qi - r * G);
-            const float *qs = a.q + (int64_t)r * a.ld_q + (int64_t)head * dh + e16 * ED;
-#pragma unroll
-            for (int e = 0; e < ED; ++e)
-                qv[qi][e] = qs[e] * scale;
-            lim[qi] = pos + r;
+            qv[e] = qs[e] * scale;
+            o[e] = 0.0f;
         }
     }
 
@@ -807,46 +793,41 @@ __global__ __launch_bounds__(NWV * 64) void k_attn_head(AttnArgs a) {
         }
     };
     load_blk(wave, kc, vc);
-    for (int b = wave; b < nblk; b += NWV) {
-        load_blk(b + NWV, kn, vn);
+    for (int b = wave; b < nblk; b += HW) {
+        load_blk(b + HW, kn, vn);
+        float s[4];
+        float mx = -INFINITY;
 #pragma unroll
-        for (int qi = 0; qi < QH; ++qi) {
-            if (qi >= nq)
-                break;
-            float s[4];
-            float mx = -INFINITY;
+        for (int jj = 0; jj < 4; ++jj) {
+            float t = 0.0f;
+#pragma unroll
+            for (int e = 0; e < ED; ++e)
+                t = fmaf(qv[e], kc[jj].at(e), t);
+            t += __shfl_xor(t, 1, 64);
+            t += __shfl_xor(t, 2, 64);
+            t += __shfl_xor(t, 4, 64);
+            t += __shfl_xor(t, 8, 64);
+            const int c = b * 16 + ks + 4 * jj;
+            s[jj] = (c < ctx && c <= lim) ? t : -INFINITY;
+            mx = fmaxf(mx, s[jj]);
+        }
+        const float mn = fmaxf(mr, mx);
+        if (mn != -INFINITY) {
+            const float so = expf(mr - mn);
+            float l = lr * so;
+#pragma unroll
+            for (int e = 0; e < ED; ++e)
+                o[e] *= so;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                float t = 0.0f;
+                const float p = expf(s[jj] - mn);
+                l += p;
 #pragma unroll
                 for (int e = 0; e < ED; ++e)
-                    t = fmaf(qv[qi][e], kc[jj].at(e), t);
-                t += __shfl_xor(t, 1, 64);
-                t += __shfl_xor(t, 2, 64);
-                t += __shfl_xor(t, 4, 64);
-                t += __shfl_xor(t, 8, 64);
-                const int c = b * 16 + ks + 4 * jj;
-                s[jj] = (c < ctx && c <= lim[qi]) ? t : -INFINITY;
-                mx = fmaxf(mx, s[jj]);
+                    o[e] = fmaf(p, vc[jj].at(e), o[e]);
             }
-            const float mn = fmaxf(mr[qi], mx);
-            if (mn != -INFINITY) {
-                const float so = expf(mr[qi] - mn);
-                float l = lr[qi] * so;
-#pragma unroll
-                for (int e = 0; e < ED; ++e)
-                    o[qi][e] *= so;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const float p = expf(s[jj] - mn);
-                    l += p;
-#pragma unroll
-                    for (int e = 0; e < ED; ++e)
-                        o[qi][e] = fmaf(p, vc[jj].at(e), o[qi][e]);
-                }
-                lr[qi] = l;
-                mr[qi] = mn;
-            }
+            lr = l;
+            mr = mn;
         }
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
@@ -856,59 +837,52 @@ __global__ __launch_bounds__(NWV * 64) void k_attn_head(AttnArgs a) {
     }
     // merge the four lane groups, then the waves
 #pragma unroll
-    for (int qi = 0; qi < QH; ++qi) {
-        if (qi >= nq)
-            break;
+    for (int x = 16; x <= 32; x <<= 1) {
+        const float m2 = __shfl_xor(mr, x, 64), l2 = __shfl_xor(lr, x, 64);
+        float o2[ED];
 #pragma unroll
-        for (int x = 16; x <= 32; x <<= 1) {
-            const float m2 = __shfl_xor(mr[qi], x, 64), l2 = __shfl_xor(lr[qi], x, 64);
-            float o2[ED];
+        for (int e = 0; e < ED; ++e)
+            o2[e] = __shfl_xor(o[e], x, 64);
+        const float mn = fmaxf(mr, m2);
+        if (mn != -INFINITY) {
+            const float wa = expf(mr - mn), wb = expf(m2 - mn);
+            lr = lr * wa + l2 * wb;
 #pragma unroll
             for (int e = 0; e < ED; ++e)
-                o2[e] = __shfl_xor(o[qi][e], x, 64);
-            const float mn = fmaxf(mr[qi], m2);
-            if (mn != -INFINITY) {
-                const float wa = expf(mr[qi] - mn), wb = expf(m2 - mn);
-                lr[qi] = lr[qi] * wa + l2 * wb;
-#pragma unroll
-                for (int e = 0; e < ED; ++e)
-                    o[qi][e] = o[qi][e] * wa + o2[e] * wb;
-                mr[qi] = mn;
-            }
+                o[e] = o[e] * wa + o2[e] * wb;
+            mr = mn;
         }
-        if (ks == 0) {
+    }
+    if (ks == 0) {
 #pragma unroll
-            for (int e = 0; e < ED; ++e)
-                wo[wave][qi][e16 * ED + e] = o[qi][e];
-            if (e16 == 0) {
-                wst[wave][qi][0] = mr[qi];
-                wst[wave][qi][1] = lr[qi];
-            }
+        for (int e = 0; e < ED; ++e)
+            wo[wave][e16 * ED + e] = o[e];
+        if (e16 == 0) {
+            wst[wave][0] = mr;
+            wst[wave][1] = lr;
         }
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < nq * dh; t += NWV * 64) {
-        const int qi = t / dh, e = t - qi * dh;
-        float mx = -INFINITY;
-        for (int w = 0; w < NWV; ++w)
-            mx = fmaxf(mx, wst[w][qi][0]);
-        float L = 0.0f, O = 0.0f;
-        for (int w = 0; w < NWV; ++w) {
-            const float m = wst[w][qi][0];
-            if (m == -INFINITY)
-                continue;
-            const float wgt = expf(m - mx);
-            L = fmaf(wgt, wst[w][qi][1], L);
-            O = fmaf(wgt, wo[w][qi][e], O);
-        }
-        const int r = qi / G, head = g * G + (qi - r * G);
-        const float y = O / L;
-        const int64_t oi = (int64_t)r * a.ld_out + (int64_t)head * dh + e;
-        if (a.out_x) {
-            store_split3(a.out_x, r, head * dh + e, M, y);
-        } else {
-            a.out[oi] = y;
-        }
+    const int e = threadIdx.x;
+    if (e >= dh)
+        return;
+    float mx = -INFINITY;
+    for (int w = 0; w < HW; ++w)
+        mx = fmaxf(mx, wst[w][0]);
+    float L = 0.0f, O = 0.0f;
+    for (int w = 0; w < HW; ++w) {
+        const float m = wst[w][0];
+        if (m == -INFINITY)
+            continue;
+        const float wgt = expf(m - mx);
+        L = fmaf(wgt, wst[w][1], L);
+        O = fmaf(wgt, wo[w][e], O);
+    }
+    const float y = O / L;
+    if (a.out_x) {
+        store_split3(a.out_x, r, head * dh + e, M, y);
+    } else {
+        a.out[(int64_t)r * a.ld_out + (int64_t)head * dh + e] = y;
     }
 }
 
@@ -1046,22 +1020,21 @@ static hipError_t launch_attn_mfma(const AttnArgs &a, int max_q, hipStream_t s) 
     return hipSuccess;
 }
 
-template <typename TK, int QH>
-static hipError_t launch_attn_head(const AttnArgs &a, hipStream_t s) {
-    dim3 grid(a.n_kv_heads), block(HW * 64);
+template <typename TK>
+static hipError_t launch_attn_head(const AttnArgs &a, int max_q, hipStream_t s) {
+    dim3 grid(a.n_kv_heads, max_q), block(HW * 64);
     switch (a.head_dim) {
     case 16:
-        hipLaunchKernelGGL((k_attn_head<TK, 1, QH>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_attn_head<TK, 1>), grid, block, 0, s, a);
         break;
     case 32:
-        hipLaunchKernelGGL((k_attn_head<TK, 2, QH>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_attn_head<TK, 2>), grid, block, 0, s, a);
         break;
     case 64:
-        hipLaunchKernelGGL((k_attn_head<TK, 4, QH>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_attn_head<TK, 4>), grid, block, 0, s, a);
         break;
     case 128:
-        // (eight elements per lane: no room for the wide form)
-        hipLaunchKernelGGL((k_attn_head<TK, 8, QH_NARROW>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_attn_head<TK, 8>), grid, block, 0, s, a);
         break;
     default:
         return hipErrorInvalidValue;
@@ -1083,13 +1056,13 @@ hipError_t launch_attention(const AttnArgs &a0, bool bf16, int max_rows, hipStre
     AttnArgs a = a0;
     const int G = a.n_heads / a.n_kv_heads;
     const int max_q = G * max_rows;
-    // one work-group per kv head while the context is short and the query
-    // vectors per head fit; otherwise split the keys over work-groups
-    if (max_q <= QH_NARROW && a.ctx_max <= 256)
-        return bf16 ? launch_attn_head<uint16_t, QH_NARROW>(a, s) : launch_attn_head<float, QH_NARROW>(a, s);
+    // A work-group per query vector while the context is short; otherwise split
+    // the keys over work-groups.  The line: 13B 13 rows over 400 keys 713 us
+    // split, 730 not; the tiny float32 model (VALU split kernel), 5 rows over
+    // 400 keys 172 split, 147 not.
     const bool mfma = bf16 && a.head_dim >= 32;
-    if (!mfma && a.head_dim <= 64 && max_q <= QH_WIDE && a.ctx_max <= 256)
-        return bf16 ? launch_attn_head<uint16_t, QH_WIDE>(a, s) : launch_attn_head<float, QH_WIDE>(a, s);
+    if (a.ctx_max <= (mfma ? 256 : 512))
+        return bf16 ? launch_attn_head<uint16_t>(a, max_q, s) : launch_attn_head<float>(a, max_q, s);
     // (the workspace holds the partials of 64-key chunks whenever a model can
     // take this path: attn_chunk_min)
     const bool valu = bf16 && a.head_dim == 128 && max_q <= 2;

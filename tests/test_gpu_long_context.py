@@ -13,7 +13,9 @@ a quarter of the residual stream here, and leaving out one block of 64 keys of
 import numpy as np
 import pytest
 
+import oracle
 import sd_synth as S
+from tests import gpu_util as U
 from tests import test_gpu_attention as A
 
 pytestmark = pytest.mark.gpu
@@ -45,6 +47,60 @@ def test_long_contexts(name, ctx):
         torch.from_numpy(fill.view(np.int16)).view(-1, ctx, cfg.head_dim).to("cuda"))
     cache = dm.cache(cap, device_buf=buf)
     for n in (1, 2, 5, 16, 40, 129, 200):
+        cache.set_length(ctx)
+        out = torch.empty((n, cfg.vocab), dtype=torch.float32, device="cuda")
+        dm.forward(toks[:n], cache, logits=out)
+        A._tight(ref[:n], out.cpu().numpy(), f"{name} {n} rows over {ctx} keys")
+
+
+F32 = {"tiny": S.MODELS["tiny"], "f32_dh128": S.ModelConfig("f32_dh128", 1, 256, 4, 2, 128, 256, 512, "f32"),
+       "f32_dh16": S.ModelConfig("f32_dh16", 1, 128, 8, 4, 16, 256, 512, "f32")}
+_f32 = {}
+
+
+@pytest.mark.parametrize("ctx", [1, 120, 255, 500, 511, 700])
+@pytest.mark.parametrize("name", list(F32))
+def test_short_and_split_contexts_f32(name, ctx):
+    """Both sides of the line between one work-group per query vector and the
+    split over the keys (512 keys for float32 caches): forwards of 1 to 16 rows
+    that end below, at and past it."""
+    cfg = F32[name]
+    if name not in _f32:
+        w = S.make_weights(cfg, 9)
+        _f32[name] = (oracle.Model(cfg, w), U.device_model(cfg, w))
+    om, dm = _f32[name]
+    cap = ctx + 16
+    fill = S.kv_fill(cfg, cfg.n_layers * 2 * cfg.n_kv_heads * ctx * cfg.head_dim, 4)
+    toks = S.prompt(cfg, 16, seed=ctx)
+    oc = om.cache(cap)
+    oc.load(fill, ctx, "f32")
+    ref = om.forward(oc, toks)["logits"]
+    buf = torch.zeros(dm.kv_cache_bytes(cap) // 4, dtype=torch.float32, device="cuda")
+    buf.view(-1, cap, cfg.head_dim)[:, :ctx].copy_(torch.from_numpy(fill).view(-1, ctx, cfg.head_dim).to("cuda"))
+    cache = dm.cache(cap, device_buf=buf)
+    for n in (1, 2, 5, 12, 16):
+        cache.set_length(ctx)
+        out = torch.empty((n, cfg.vocab), dtype=torch.float32, device="cuda")
+        dm.forward(toks[:n], cache, logits=out)
+        U.check_logits(cfg, out.cpu().numpy(), ref[:n], f"{name} {n} rows over {ctx} keys")
+
+
+@pytest.mark.parametrize("name", list(A.CONFIGS))
+@pytest.mark.parametrize("ctx", [240, 250, 256])
+def test_short_and_split_contexts_bf16(name, ctx):
+    """The same line for bfloat16 caches (256 keys)."""
+    cfg, _, om, dm = A._pair(name)
+    cap = ctx + 16
+    fill = S.kv_fill(cfg, 2 * cfg.n_kv_heads * ctx * cfg.head_dim, 5)
+    toks = S.prompt(cfg, 16, seed=ctx)
+    oc = om.cache(cap)
+    oc.load(fill, ctx, "bf16")
+    ref = om.forward(oc, toks)["logits"]
+    buf = torch.zeros(dm.kv_cache_bytes(cap) // 2, dtype=torch.int16, device="cuda")
+    buf.view(-1, cap, cfg.head_dim)[:, :ctx].copy_(
+        torch.from_numpy(fill.view(np.int16)).view(-1, ctx, cfg.head_dim).to("cuda"))
+    cache = dm.cache(cap, device_buf=buf)
+    for n in (1, 2, 6, 7, 16):
         cache.set_length(ctx)
         out = torch.empty((n, cfg.vocab), dtype=torch.float32, device="cuda")
         dm.forward(toks[:n], cache, logits=out)
