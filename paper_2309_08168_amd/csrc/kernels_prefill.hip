@@ -8,16 +8,18 @@
 //     tiles of 256 x 256 down to 128 x 64, every operand loaded straight into
 //     LDS in MFMA fragment order; tiles are ordered so the work-groups one XCD
 //     runs together share their weight and activation slices in that XCD's
-//     L2; residual updates split the reduction into partials;
+//     L2; residual updates split the reduction into partials
+//     (the QKV product's epilogue rotates q and k and appends to the cache, the
+//     gate/up product's applies the SwiGLU);
 //   - k_pf_thin: the same products for up to 64 rows, bound by the weight
-//     stream, with the rotary embedding and KV append in the QKV epilogue;
+//     stream;
 //   - k_pf_attn: causal attention, one wave per 16 query rows of a head,
 //     scores and the weighted sum of values on matrix cores with an online
 //     softmax over 32-key blocks, the longest row blocks dispatched first and
 //     spread evenly over the XCDs;
 //   - small row kernels between them: embedding, RMSNorm into terms (adding a
-//     residual update's partials first), rotary embedding + KV append, and
-//     the terms of the attention output and of the MLP activation.
+//     residual update's partials first), and the terms of the attention output
+//     and of the MLP activation.
 #include "sd_internal.h"
 
 #include <algorithm>
@@ -116,6 +118,51 @@ __device__ __forceinline__ void split_f16x8(const float (&x)[8], u32x4_t &hi, u3
     lo = __builtin_bit_cast(u32x4_t, l);
 }
 
+// Row i of 16-row weight tile t of a QKV product: eight elements of the first
+// half of a head (i < 8), then their rotary partners, half = head_dim / 2 on.
+__device__ __forceinline__ int qkv_row(int t, int i, int head_dim) {
+    const int half = head_dim >> 1, per_head = half >> 3;
+    const int head = t / per_head, p = (t - head * per_head) * 8 + (i & 7);
+    return head * head_dim + (i < 8 ? p : half + p);
+}
+
+// Elements i .. i + 3 of tile t (y0) and their partners (y1) of row m: rotated q
+// into q [M][ldq], rotated k and v into the cache (bfloat16).
+__device__ __forceinline__ void store_qkv4(const PfRope &a, int t, int i, int m, f32x4_t y0, f32x4_t y1, float *q,
+                                           int64_t ldq) {
+    const int dh = a.head_dim, half = dh >> 1, per_head = half >> 3;
+    const int head = t / per_head, e = (t - head * per_head) * 8 + i, pos = a.start + m;
+    if (head < a.n_heads + a.n_kv_heads) {
+        const float *cs = reinterpret_cast<const float *>(a.table + (int64_t)pos * half + e);
+        const f32x4_t c01 = reinterpret_cast<const f32x4_t *>(cs)[0], c23 = reinterpret_cast<const f32x4_t *>(cs)[1];
+        const float cx[4] = {c01[0], c01[2], c23[0], c23[2]}, cy[4] = {c01[1], c01[3], c23[1], c23[3]};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float r0 = y0[j] * cx[j] - y1[j] * cy[j];
+            const float r1 = y1[j] * cx[j] + y0[j] * cy[j];
+            y0[j] = r0;
+            y1[j] = r1;
+        }
+    }
+    if (head < a.n_heads) {
+        float *o = q + (int64_t)m * ldq + head * dh + e;
+        *reinterpret_cast<f32x4_t *>(o) = y0;
+        *reinterpret_cast<f32x4_t *>(o + half) = y1;
+    } else {
+        const bool is_k = head < a.n_heads + a.n_kv_heads;
+        const int g = head - a.n_heads - (is_k ? 0 : a.n_kv_heads);
+        uint16_t *c = (is_k ? a.kcache : a.vcache) + (int64_t)g * a.kv_head_stride + (int64_t)pos * dh + e;
+        u32x2_t w0, w1;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            w0[j] = (uint32_t)bf16_rne_bits(y0[2 * j]) | ((uint32_t)bf16_rne_bits(y0[2 * j + 1]) << 16);
+            w1[j] = (uint32_t)bf16_rne_bits(y1[2 * j]) | ((uint32_t)bf16_rne_bits(y1[2 * j + 1]) << 16);
+        }
+        *reinterpret_cast<u32x2_t *>(c) = w0;
+        *reinterpret_cast<u32x2_t *>(c + half) = w1;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // GEMM
 //
@@ -154,8 +201,8 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
     constexpr int NBW = BN / 16, NBA = T * BM / 16;      // weight and activation blocks per stage
     constexpr int WPW = (NBW + NW - 1) / NW, APW = (NBA + NW - 1) / NW;  // load instructions per wave and stage
     static_assert(NT * 16 == WN && MT * 16 == WM, "tile split");
-    static_assert(EPI == EPI_STORE || EPI == EPI_PARTIAL || EPI == EPI_SWIGLU, "epilogue");
-    constexpr bool SWI = EPI == EPI_SWIGLU;
+    static_assert(EPI == EPI_STORE || EPI == EPI_PARTIAL || EPI == EPI_SWIGLU || EPI == EPI_QKV, "epilogue");
+    constexpr bool SWI = EPI == EPI_SWIGLU, QKV = EPI == EPI_QKV;
     // float16 weights, activation terms, bfloat16 weights (a block per wave and load)
     constexpr int LW = 2 * NBW * 512, LA = (P + 1) * NBA * 512, LR = P * WPW * NW * 512;
     __shared__ __attribute__((aligned(1024))) uint16_t lds[LW + LA + LR];
@@ -190,8 +237,9 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wn = wave % NWN, wm = wave / NWN, col = lane & 15, grp = lane >> 4;
 
-    // Weight block b holds rows n0 + 16 b .., or with SWI eight gate rows
-    // f = n0 + 8 b .. and then the up rows of the same f; lane l loads row
+    // Weight block b holds rows n0 + 16 b .., with SWI eight gate rows
+    // f = n0 + 8 b .. and then the up rows of the same f, with QKV eight rows of
+    // the first half of a head and then their rotary partners; lane l loads row
     // l % 16, k chunk l / 16 (rows past the end read the last one: never
     // stored).  The lane keeps the largest magnitude of what it loads.
     const uint16_t *wsrc[WPW];
@@ -203,6 +251,8 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
         int row;
         if constexpr (SWI)
             row = (col < 8 ? 0 : F) + min(n0 + 8 * b + (col & 7), F - 1);
+        else if constexpr (QKV)
+            row = qkv_row(min(n0 / 16 + b, N / 16 - 1), col, a.rope.head_dim);
         else
             row = min(n0 + 16 * b + col, N - 1);
         wsrc[i] = a.W + (int64_t)row * K;
@@ -399,6 +449,32 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
                 a.amax[(int64_t)(m0 + i) * a.amax_ld + tn] = __uint_as_float(ymax[i]);
         return;
     }
+    if constexpr (QKV) {
+        // the same swap leaves a row's element p and its partner p + half
+#pragma unroll
+        for (int i = 0; i < NT; i += 2) {
+            const int i2 = i + 1 < NT ? i + 1 : i, ti = lane < 32 ? i : i2;
+            const bool own = lane < 32 || i2 != i;
+            const int bl = wn * NT + ti, rb = bl * 16 + 4 * (grp & 1);
+            const f32x4_t s0 = *reinterpret_cast<const f32x4_t *>(&wsc[rb]);
+            const f32x4_t s1 = *reinterpret_cast<const f32x4_t *>(&wsc[rb + 8]);
+#pragma unroll
+            for (int j = 0; j < MT; ++j) {
+                const int m = m0 + wm * WM + 16 * j + col;
+                f32x4_t y0, y1;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][j][v]),
+                                                                    __float_as_uint(acc[i2][j][v]), false, false);
+                    y0[v] = __uint_as_float(r[0]) * (rs[j] * s0[v]);
+                    y1[v] = __uint_as_float(r[1]) * (rs[j] * s1[v]);
+                }
+                if (m < M && n0 + 16 * bl < N && own)
+                    store_qkv4(a.rope, n0 / 16 + bl, 4 * (grp & 1), m, y0, y1, a.C, a.ldc);
+            }
+        }
+        return;
+    }
     float *C = EPI == EPI_PARTIAL ? a.part + (int64_t)split * M * a.ldc : a.C;
     const bool vec = (a.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
 #pragma unroll
@@ -438,10 +514,8 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
 
 template <int EPI>
 __device__ __forceinline__ int thin_row(int t, int i, const PfThinArgs &a) {
-    if constexpr (EPI == EPI_QKV) {  // eight rotary pairs of one head
-        const int half = a.head_dim >> 1, per_head = half >> 3;
-        const int head = t / per_head, p = (t - head * per_head) * 8 + (i & 7);
-        return head * a.head_dim + (i < 8 ? p : half + p);
+    if constexpr (EPI == EPI_QKV) {
+        return qkv_row(t, i, a.rope.head_dim);
     } else if constexpr (EPI == EPI_SWIGLU) {  // eight gate rows and their up rows
         const int f = min(t * 8 + (i & 7), (a.N >> 1) - 1);
         return i < 8 ? f : (a.N >> 1) + f;
@@ -450,9 +524,9 @@ __device__ __forceinline__ int thin_row(int t, int i, const PfThinArgs &a) {
     }
 }
 
-template <int EPI, int MB, int NW>
+template <int EPI, int MB, int NW, int TN>
 __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
-    constexpr int TN = 4, T = PF_TERMS;
+    constexpr int T = PF_TERMS;
     constexpr int WL = TN * 16 * 64;          // halves of a wave's staging tile
     constexpr int RC = MB * 16 + 1;           // pitch of the reduction rows
     constexpr size_t SMEM_W = (size_t)NW * WL * 2, SMEM_R = (size_t)NW * 16 * RC * 4;
@@ -537,26 +611,24 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                u32x4_t wf[TN];
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     const u32x4_t v = *reinterpret_cast<const u32x4_t *>(wl + j * 1024 + r16 * 64 +
                                                                          (((4 * i + kg) ^ (r16 & 7)) << 3));
+                    u32x4_t wf;
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         wmax[j] = pk_max_u16(wmax[j], v[u] & 0x7fff7fffu);
-                        wf[j][u] = __builtin_bit_cast(
+                        wf[u] = __builtin_bit_cast(
                             uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(v[u] << 16) * wscale[j],
                                                                  __uint_as_float(v[u] & 0xffff0000u) * wscale[j]));
                     }
-                }
 #pragma unroll
-                for (int t = 0; t < T; ++t)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
+                    for (int t = 0; t < T; ++t)
 #pragma unroll
                         for (int b = 0; b < MB; ++b)
-                            acc[j][b] = mfma16h(wf[j], xv[i][b][t], acc[j][b]);
+                            acc[j][b] = mfma16h(wf, xv[i][b][t], acc[j][b]);
+                }
                 // one set of registers per half step: its next activations
                 // (cache hits) are requested once its MFMAs have read these
                 __builtin_amdgcn_sched_barrier(0);
@@ -636,29 +708,15 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
             }
         } else if constexpr (EPI == EPI_QKV) {
             __syncthreads();
-            const int dh = a.head_dim, half = dh >> 1, per_head = half >> 3;
-            const int head = t / per_head, p0 = (t - head * per_head) * 8;
-            for (int o = tid; o < 8 * M; o += 64 * NW) {
-                const int i = o & 7, m = o >> 3, e = p0 + i, pos = a.start + m;
-                float y0 = fin[i * RC + m], y1 = fin[(i + 8) * RC + m];
-                if (head < a.n_heads + a.n_kv_heads) {
-                    const float2 cs = a.rope[(int64_t)pos * half + e];
-                    const float r0 = y0 * cs.x - y1 * cs.y;
-                    const float r1 = y1 * cs.x + y0 * cs.y;
-                    y0 = r0;
-                    y1 = r1;
+            for (int o = tid; o < 2 * M; o += 64 * NW) {
+                const int i = 4 * (o & 1), m = o >> 1;
+                f32x4_t y0, y1;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    y0[v] = fin[(i + v) * RC + m];
+                    y1[v] = fin[(i + v + 8) * RC + m];
                 }
-                if (head < a.n_heads) {
-                    float *qo = a.C + (int64_t)m * a.ldc + head * dh + e;
-                    qo[0] = y0;
-                    qo[half] = y1;
-                } else {
-                    const bool is_k = head < a.n_heads + a.n_kv_heads;
-                    const int g = head - a.n_heads - (is_k ? 0 : a.n_kv_heads);
-                    uint16_t *c = (is_k ? a.kcache : a.vcache) + (int64_t)g * a.kv_head_stride + (int64_t)pos * dh + e;
-                    c[0] = bf16_rne_bits(y0);
-                    c[half] = bf16_rne_bits(y1);
-                }
+                store_qkv4(a.rope, t, i, m, y0, y1, a.C, a.ldc);
             }
         }
     }
@@ -844,14 +902,6 @@ __global__ __launch_bounds__(256) void k_pf_attn(PfAttnArgs a) {
 // ---------------------------------------------------------------------------
 // Row kernels (one work-group per row)
 
-__global__ __launch_bounds__(256) void k_pf_embed(const uint16_t *E, int d, const int32_t *tokens, float *h) {
-    const int m = blockIdx.x;
-    const uint16_t *e = E + (int64_t)tokens[m] * d;
-    float *o = h + (int64_t)m * d;
-    for (int k = threadIdx.x; k < d; k += 256)
-        o[k] = bf_to_f(e[k]);
-}
-
 __device__ __forceinline__ void load8bf(const uint16_t *p, float (&x)[8]) {
     const u32x4_t w = *reinterpret_cast<const u32x4_t *>(p);
 #pragma unroll
@@ -861,13 +911,28 @@ __device__ __forceinline__ void load8bf(const uint16_t *p, float (&x)[8]) {
     }
 }
 
+__global__ __launch_bounds__(256) void k_pf_embed(const uint16_t *E, int d, const int32_t *tokens, float *h) {
+    const int m = blockIdx.x, k = (blockIdx.y * 256 + threadIdx.x) * 8;  // d is a multiple of 8
+    if (k >= d)
+        return;
+    float x[8];
+    load8bf(E + (int64_t)tokens[m] * d + k, x);
+    f32x4_t *o = reinterpret_cast<f32x4_t *>(h + (int64_t)m * d + k);
+    o[0] = f32x4_t{x[0], x[1], x[2], x[3]};
+    o[1] = f32x4_t{x[4], x[5], x[6], x[7]};
+}
+
+// Threads of a row kernel: a row's loads in one or two steps of latency where
+// there are few rows, smaller work-groups where rows fill the chip.
+constexpr int PF_FEW_ROWS = 256;
+
 // The terms of row m, x[0..K) (K a multiple of 8; x(k) gives elements k .. k + 7
 // times the row's scale): row-major, zero up to the next multiple of 32
 // (blocks 0), or in fragment order.
-template <typename F>
+template <int NT, typename F>
 __device__ __forceinline__ void store_terms(int m, int K, uint16_t *out, int64_t out_term, int blocks, F x) {
     const int ldk = pf_pitch(K);
-    for (int k = 8 * threadIdx.x; k < ldk; k += 8 * 256) {
+    for (int k = 8 * threadIdx.x; k < ldk; k += 8 * NT) {
         u32x4_t h = {0u, 0u, 0u, 0u}, l = h;
         if (k < K) {
             float u[8];
@@ -892,17 +957,18 @@ __device__ __forceinline__ void load8f(const float *p, float (&x)[8]) {
 // g * h / rms(h) of every row as float16 terms, with the row's scale.  With
 // splits > 0 the partials of a split residual update are added into h first,
 // in split order: h[m] += part[0][m] + part[1][m] + ...
-__global__ __launch_bounds__(256) void k_pf_norm_split(float *h, const float *part, int splits, int64_t stride, int K,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_pf_norm_split(float *h, const float *part, int splits, int64_t stride, int K,
                                                        const uint16_t *gain, float eps, uint16_t *out, int64_t out_term,
                                                        int blocks, float *rs) {
-    __shared__ float red[2][4];
+    __shared__ float red[2][NT / 64];
     const int m = blockIdx.x, tid = threadIdx.x;
     float *x = h + (int64_t)m * K;
     const float *p = part + (int64_t)m * K;
     float ss = 0.0f, mx = 0.0f;
     // 16-byte loads (K is a multiple of 8): with 4-byte loads this pass over
     // the row and three partial planes took 40 us per 13B call
-    for (int k = 8 * tid; k < K; k += 8 * 256) {
+    for (int k = 8 * tid; k < K; k += 8 * NT) {
         float v[8], g[8];
         load8f(x + k, v);
         if (splits) {
@@ -935,14 +1001,20 @@ __global__ __launch_bounds__(256) void k_pf_norm_split(float *h, const float *pa
         red[1][tid >> 6] = mx;
     }
     __syncthreads();
-    const float inv = 1.0f / sqrtf((red[0][0] + red[0][1] + red[0][2] + red[0][3]) / (float)K + eps);
-    const float amax = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3])) * inv;
+    ss = mx = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+        ss += red[0][w];
+        mx = fmaxf(mx, red[1][w]);
+    }
+    const float inv = 1.0f / sqrtf(ss / (float)K + eps);
+    const float amax = mx * inv;
     float rinv;
     const float sc = row_scale(amax, &rinv);
     if (tid == 0)
         rs[m] = rinv;
     // (re-reads what this thread wrote or read above)
-    store_terms(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
+    store_terms<NT>(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
         float v[8], g[8];
         load8f(x + k, v);
         load8bf(gain + k, g);
@@ -954,70 +1026,32 @@ __global__ __launch_bounds__(256) void k_pf_norm_split(float *h, const float *pa
 
 // The terms of every row of x [M][K] (the attention output or the MLP
 // activation), whose largest magnitude is the largest of its amax slots.
-__global__ __launch_bounds__(256) void k_pf_split(const float *x, int K, const float *amax, int slots, int amax_ld,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_pf_split(const float *x, int K, const float *amax, int slots, int amax_ld,
                                                   uint16_t *out, int64_t out_term, int blocks, float *rs) {
-    __shared__ float red[4];
+    __shared__ float red[NT / 64];
     const int m = blockIdx.x, tid = threadIdx.x;
     float mx = 0.0f;
-    for (int i = tid; i < slots; i += 256)
+    for (int i = tid; i < slots; i += NT)
         mx = fmaxf(mx, amax[(int64_t)m * amax_ld + i]);
     mx = wave_max_all(mx);
     if ((tid & 63) == 0)
         red[tid >> 6] = mx;
     __syncthreads();
+    mx = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w)
+        mx = fmaxf(mx, red[w]);
     float rinv;
-    const float sc = row_scale(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), &rinv);
+    const float sc = row_scale(mx, &rinv);
     if (tid == 0)
         rs[m] = rinv;
-    store_terms(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
+    store_terms<NT>(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
         load8f(x + (int64_t)m * K + k, u);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
             u[j] *= sc;
     });
-}
-
-__global__ __launch_bounds__(256) void k_pf_rope_kv(const float *qkv, int start, const float2 *rope, int H, int KVH,
-                                                    int dh, float *q, uint16_t *kc, uint16_t *vc, int64_t stride) {
-    const int m = blockIdx.x, pos = start + m, half = dh >> 1;
-    const int nq = (H + 2 * KVH) * dh;
-    const float *x = qkv + (int64_t)m * nq;
-    // four pair indices i .. i + 3 of one head per step (half is a multiple
-    // of 4): 16-byte loads and stores, 8-byte stores into the cache
-    for (int idx = 4 * threadIdx.x; idx < (H + 2 * KVH) * half; idx += 4 * 256) {
-        const int head = idx / half, i = idx - head * half;
-        f32x4_t y0 = *reinterpret_cast<const f32x4_t *>(x + head * dh + i);
-        f32x4_t y1 = *reinterpret_cast<const f32x4_t *>(x + head * dh + i + half);
-        if (head < H + KVH) {
-            const f32x4_t c01 = *reinterpret_cast<const f32x4_t *>(rope + (int64_t)pos * half + i);
-            const f32x4_t c23 = *reinterpret_cast<const f32x4_t *>(rope + (int64_t)pos * half + i + 2);
-            const float cx[4] = {c01[0], c01[2], c23[0], c23[2]}, cy[4] = {c01[1], c01[3], c23[1], c23[3]};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float r0 = y0[j] * cx[j] - y1[j] * cy[j];
-                const float r1 = y1[j] * cx[j] + y0[j] * cy[j];
-                y0[j] = r0;
-                y1[j] = r1;
-            }
-        }
-        if (head < H) {
-            float *qo = q + (int64_t)m * H * dh + head * dh + i;
-            *reinterpret_cast<f32x4_t *>(qo) = y0;
-            *reinterpret_cast<f32x4_t *>(qo + half) = y1;
-        } else {
-            const bool is_k = head < H + KVH;
-            const int g = is_k ? head - H : head - H - KVH;
-            uint16_t *c = (is_k ? kc : vc) + (int64_t)g * stride + (int64_t)pos * dh + i;
-            u32x2_t w0, w1;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                w0[j] = (uint32_t)bf16_rne_bits(y0[2 * j]) | ((uint32_t)bf16_rne_bits(y0[2 * j + 1]) << 16);
-                w1[j] = (uint32_t)bf16_rne_bits(y1[2 * j]) | ((uint32_t)bf16_rne_bits(y1[2 * j + 1]) << 16);
-            }
-            *reinterpret_cast<u32x2_t *>(c) = w0;
-            *reinterpret_cast<u32x2_t *>(c + half) = w1;
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1245,16 +1279,17 @@ __global__ __launch_bounds__(256, 2) void k_pf_attn128(PfAttnArgs a) {
 // The chunks of k_pf_attn128 combined in order and normalised, one work-group
 // per row, as float16 terms with the row's scale.  LDS: the row (hd floats) and
 // the chunks' weights [H][chunks].
-__global__ __launch_bounds__(256) void k_pf_attn_terms(PfAttnArgs a, uint16_t *out, int64_t out_term, int blocks,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_pf_attn_terms(PfAttnArgs a, uint16_t *out, int64_t out_term, int blocks,
                                                        float *rs) {
     extern __shared__ __attribute__((aligned(16))) float sm[];
-    __shared__ float red[4];
+    __shared__ float red[NT / 64];
     const int m = blockIdx.x, tid = threadIdx.x, H = a.n_heads, hd = H * 128;
     float *row = sm, *wt = sm + hd;
     // chunks some row of this row's work-group saw keys of
     const int kend = a.start + min((m / PA2_ROWS + 1) * PA2_ROWS, a.M);
     const int nc = min(a.chunks, (kend + a.chunk_keys - 1) / a.chunk_keys);
-    for (int h = tid; h < H; h += 256) {
+    for (int h = tid; h < H; h += NT) {
         float mx = -INFINITY, L = 0.0f;
         for (int c = 0; c < nc; ++c)
             mx = fmaxf(mx, a.ml[((int64_t)c * a.M + m) * H + h].x);
@@ -1270,7 +1305,7 @@ __global__ __launch_bounds__(256) void k_pf_attn_terms(PfAttnArgs a, uint16_t *o
     }
     __syncthreads();
     float mx = 0.0f;
-    for (int k = 4 * tid; k < hd; k += 4 * 256) {
+    for (int k = 4 * tid; k < hd; k += 4 * NT) {
         const float *w = wt + (k >> 7) * nc, *p = a.out + (int64_t)m * a.ldo + k;
         f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int c = 0; c < nc; ++c)
@@ -1284,11 +1319,15 @@ __global__ __launch_bounds__(256) void k_pf_attn_terms(PfAttnArgs a, uint16_t *o
     if ((tid & 63) == 0)
         red[tid >> 6] = mx;
     __syncthreads();
+    mx = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w)
+        mx = fmaxf(mx, red[w]);
     float rinv;
-    const float sc = row_scale(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), &rinv);
+    const float sc = row_scale(mx, &rinv);
     if (tid == 0)
         rs[m] = rinv;
-    store_terms(m, hd, out, out_term, blocks, [&](int k, float(&u)[8]) {
+    store_terms<NT>(m, hd, out, out_term, blocks, [&](int k, float(&u)[8]) {
         load8f(row + k, u);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -1299,7 +1338,7 @@ __global__ __launch_bounds__(256) void k_pf_attn_terms(PfAttnArgs a, uint16_t *o
 }  // namespace
 
 hipError_t launch_pf_embed(const uint16_t *emb, int d, const int32_t *tokens, int M, float *h, hipStream_t s) {
-    hipLaunchKernelGGL(k_pf_embed, dim3(M), dim3(256), 0, s, emb, d, tokens, h);
+    hipLaunchKernelGGL(k_pf_embed, dim3(M, (d + 2047) / 2048), dim3(256), 0, s, emb, d, tokens, h);
     return hipGetLastError();
 }
 
@@ -1307,7 +1346,8 @@ hipError_t launch_pf_norm_split(float *h, const float *part, int splits, int K, 
                                 const PfTerms &t, hipStream_t s) {
     if (K % 8 || (t.blocks && K % 32) || splits < 0 || splits > PF_MAX_SPLITS)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_norm_split, dim3(M), dim3(256), 0, s, h, part, splits, (int64_t)M * K, K, gain, eps, t.x,
+    auto kern = M <= PF_FEW_ROWS ? k_pf_norm_split<1024> : k_pf_norm_split<256>;
+    hipLaunchKernelGGL(kern, dim3(M), dim3(M <= PF_FEW_ROWS ? 1024 : 256), 0, s, h, part, splits, (int64_t)M * K, K, gain, eps, t.x,
                        t.term, t.blocks, t.rs);
     return hipGetLastError();
 }
@@ -1316,7 +1356,8 @@ hipError_t launch_pf_split(const float *x, int K, int M, const float *amax, int 
                            hipStream_t s) {
     if (K % 8 || (t.blocks && K % 32))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_split, dim3(M), dim3(256), 0, s, x, K, amax, slots, amax_ld, t.x, t.term, t.blocks, t.rs);
+    auto kern = M <= PF_FEW_ROWS ? k_pf_split<1024> : k_pf_split<256>;
+    hipLaunchKernelGGL(kern, dim3(M), dim3(M <= PF_FEW_ROWS ? 1024 : 256), 0, s, x, K, amax, slots, amax_ld, t.x, t.term, t.blocks, t.rs);
     return hipGetLastError();
 }
 
@@ -1333,24 +1374,26 @@ hipError_t launch_tile(const PfGemmArgs &a, int epi, hipStream_t s) {
         hipLaunchKernelGGL((k_pf_gemm<EPI_PARTIAL, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
     else if (epi == EPI_SWIGLU)
         hipLaunchKernelGGL((k_pf_gemm<EPI_SWIGLU, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
+    else if (epi == EPI_QKV)
+        hipLaunchKernelGGL((k_pf_gemm<EPI_QKV, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-template <int EPI, int NW>
+template <int EPI, int NW, int TN>
 hipError_t launch_thin_mb(const PfThinArgs &a, hipStream_t s) {
-    const dim3 grid((a.n_tiles + 3) / 4 * (EPI == EPI_PARTIAL ? a.splits : 1)), block(64 * NW);
+    const dim3 grid((a.n_tiles + TN - 1) / TN * (EPI == EPI_PARTIAL ? a.splits : 1)), block(64 * NW);
     switch ((a.M + 15) / 16) {
     case 1:
     case 2:
-        hipLaunchKernelGGL((k_pf_thin<EPI, 2, NW>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_pf_thin<EPI, 2, NW, TN>), grid, block, 0, s, a);
         break;
     case 3:
-        hipLaunchKernelGGL((k_pf_thin<EPI, 3, NW>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_pf_thin<EPI, 3, NW, TN>), grid, block, 0, s, a);
         break;
     case 4:
-        hipLaunchKernelGGL((k_pf_thin<EPI, 4, NW>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_pf_thin<EPI, 4, NW, TN>), grid, block, 0, s, a);
         break;
     default:
         return hipErrorInvalidValue;
@@ -1358,17 +1401,17 @@ hipError_t launch_thin_mb(const PfThinArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int NW>
+template <int NW, int TN>
 hipError_t launch_thin_nw(const PfThinArgs &a, int epi, hipStream_t s) {
     switch (epi) {
     case EPI_STORE:
-        return launch_thin_mb<EPI_STORE, NW>(a, s);
+        return launch_thin_mb<EPI_STORE, NW, TN>(a, s);
     case EPI_PARTIAL:
-        return launch_thin_mb<EPI_PARTIAL, NW>(a, s);
+        return launch_thin_mb<EPI_PARTIAL, NW, TN>(a, s);
     case EPI_SWIGLU:
-        return launch_thin_mb<EPI_SWIGLU, NW>(a, s);
+        return launch_thin_mb<EPI_SWIGLU, NW, TN>(a, s);
     case EPI_QKV:
-        return launch_thin_mb<EPI_QKV, NW>(a, s);
+        return launch_thin_mb<EPI_QKV, NW, TN>(a, s);
     default:
         return hipErrorInvalidValue;
     }
@@ -1417,7 +1460,8 @@ void pick_tile(const PfGemmArgs &a, int epi, int *tile, int *splits) {
 hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out) {
     if (a.M < 1 || a.N < 1 || a.K < 8 || a.K % 8 || a.lda != pf_pitch(a.K) || a.M > PF_ROWS || !a.rs)
         return hipErrorInvalidValue;
-    if (epi == EPI_SWIGLU ? (a.N % 16 || !a.amax || !out) : epi == EPI_RESID ? (!a.part || !out) : epi != EPI_STORE)
+    if (epi == EPI_SWIGLU ? (a.N % 16 || !a.amax || !out) : epi == EPI_RESID ? (!a.part || !out)
+        : epi == EPI_QKV ? (a.rope.head_dim % 16 || a.N % 16) : epi != EPI_STORE)
         return hipErrorInvalidValue;
     PfGemmArgs b = a;
     int tile = 0;
@@ -1429,6 +1473,9 @@ hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out)
     const int e = epi == EPI_RESID ? EPI_PARTIAL : epi;
     switch (tile) {
     case 0:
+        // 16 waves of 64 x 64; 8 of 64 x 128 read fewer fragments from LDS and
+        // were faster alone (13B QKV, 1023 rows: 331 against 296 us), not in
+        // the forward (1000 rows over 8000 keys: 7.59 against 7.64 ms)
         return launch_tile<256, 256, 4, 4, 2, 4>(b, e, s);
     case 1:
         return launch_tile<256, 128, 4, 2, 2, 2>(b, e, s);
@@ -1452,7 +1499,7 @@ hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out
         a.n_tiles = a.N / 16;
         *out = (a.n_tiles + 3) / 4;
     } else if (epi == EPI_QKV) {
-        if ((a.head_dim / 2) % 8)
+        if (a.rope.head_dim % 16)
             return hipErrorInvalidValue;
         a.n_tiles = a.N / 16;
     } else {
@@ -1472,16 +1519,7 @@ hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out
     // Eight waves where one work-group per CU takes the layer, four where two
     // fit on many CUs (33 rows: 13B QKV, 240 groups, 41.2 against 43.6 us;
     // gate/up, 432 groups, 75.0 against 70.9).
-    return groups * a.splits <= 256 ? launch_thin_nw<8>(a, epi, s) : launch_thin_nw<4>(a, epi, s);
-}
-
-hipError_t launch_pf_rope_kv(const float *qkv, int M, int start, const float2 *rope, int H, int KVH, int dh,
-                             float *q, uint16_t *kcache, uint16_t *vcache, int64_t kv_head_stride, hipStream_t s) {
-    if (dh % 8 || kv_head_stride % 4)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_rope_kv, dim3(M), dim3(256), 0, s, qkv, start, rope, H, KVH, dh, q, kcache, vcache,
-                       kv_head_stride);
-    return hipGetLastError();
+    return groups * a.splits <= 256 ? launch_thin_nw<8, 4>(a, epi, s) : launch_thin_nw<4, 4>(a, epi, s);
 }
 
 // Chunks of the keys per row block: enough work-groups for PA_UNITS of them,
@@ -1503,7 +1541,8 @@ hipError_t launch_pf_attention(const PfAttnArgs &a0, const PfTerms &t, hipStream
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-        hipLaunchKernelGGL(k_pf_attn_terms, dim3(a.M), dim3(256), (size_t)(hd + a.n_heads * a.chunks) * sizeof(float),
+        auto kern = a.M <= PF_FEW_ROWS ? k_pf_attn_terms<1024> : k_pf_attn_terms<256>;
+        hipLaunchKernelGGL(kern, dim3(a.M), dim3(a.M <= PF_FEW_ROWS ? 1024 : 256), (size_t)(hd + a.n_heads * a.chunks) * sizeof(float),
                            s, a, t.x, t.term, t.blocks, t.rs);
         return hipGetLastError();
     }

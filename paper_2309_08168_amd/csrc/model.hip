@@ -130,8 +130,8 @@ struct sd_model {
     float2 *rope = nullptr;
     int rope_cap = 0;
     // large-M forward (bfloat16 models), PF_ROWS rows each: residual stream,
-    // GEMM and attention outputs, rotated queries, partial sums of residual
-    // updates, and the GEMM inputs as PF_TERMS terms with their rows' scales
+    // MLP activation, rotated queries, partial sums of residual updates (and
+    // the attention's chunks), and the GEMM inputs as PF_TERMS terms with their rows' scales
     // and the maxima those come from
     bool pf_ok = false;
     float *pf_h = nullptr, *pf_c = nullptr, *pf_q = nullptr, *pf_part = nullptr;
@@ -761,6 +761,7 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
     // A residual update leaves its partial sums in pf_part; the next norm adds
     // them into the residual stream (fold = their count, 0: none).
     int fold = 0;
+    PfRope rope{m->rope, nullptr, nullptr, head_stride, start, H, KVH, dh};
     auto gemm = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, int *out) {
         PfGemmArgs g{};
         g.W = static_cast<const uint16_t *>(W);
@@ -776,27 +777,25 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
         g.part = m->pf_part;
         g.amax = m->pf_amax;
         g.amax_ld = m->pf_amax_ld;
+        g.rope = rope;
         return launch(launch_pf_gemm(g, epi, s, out), "prefill GEMM");
     };
-    auto thin_args = [&](const void *W, int N, int K, float *C, int64_t ldc) {
+    auto product = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, int *out) {
+        if (!thin)
+            return gemm(W, N, K, C, ldc, epi, out);
         PfThinArgs g{};
         g.W = static_cast<const uint16_t *>(W);
         g.X = terms.x;
         g.rs = terms.rs;
-        g.C = C;
+        g.C = epi == EPI_RESID ? m->pf_part : C;
         g.ldc = ldc;
         g.M = M;
         g.N = N;
         g.K = K;
         g.amax = m->pf_amax;
         g.amax_ld = m->pf_amax_ld;
-        return g;
-    };
-    auto product = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, int *out) {
-        if (!thin)
-            return gemm(W, N, K, C, ldc, epi, out);
-        return launch(launch_pf_thin(thin_args(W, N, K, epi == EPI_RESID ? m->pf_part : C, ldc), epi, s, out),
-                      "prefill GEMM");
+        g.rope = rope;
+        return launch(launch_pf_thin(g, epi, s, out), "prefill GEMM");
     };
     auto norm = [&](const void *gain) {
         const int f = fold;
@@ -819,23 +818,9 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
             uint16_t *kbase = reinterpret_cast<uint16_t *>(kv) + (size_t)(2 * l) * KVH * head_stride;
             uint16_t *vbase = reinterpret_cast<uint16_t *>(kv) + (size_t)(2 * l + 1) * KVH * head_stride;
             SD_TRY(norm(m->attn_norm[l]));
-            if (thin) {
-                PfThinArgs g = thin_args(m->w_qkv[l], nq, d, m->pf_q, hd);
-                g.kcache = kbase;
-                g.vcache = vbase;
-                g.kv_head_stride = head_stride;
-                g.rope = m->rope;
-                g.start = start;
-                g.n_heads = H;
-                g.n_kv_heads = KVH;
-                g.head_dim = dh;
-                SD_TRY(launch(launch_pf_thin(g, EPI_QKV, s), "prefill GEMM"));
-            } else {
-                SD_TRY(gemm(m->w_qkv[l], nq, d, m->pf_c, nq, EPI_STORE, nullptr));
-                SD_TRY(launch(launch_pf_rope_kv(m->pf_c, M, start, m->rope, H, KVH, dh, m->pf_q, kbase, vbase,
-                                                head_stride, s),
-                              "prefill rotary"));
-            }
+            rope.kcache = kbase;
+            rope.vcache = vbase;
+            SD_TRY(product(m->w_qkv[l], nq, d, m->pf_q, hd, EPI_QKV, nullptr));
             if (!logits && l == last_attn)
                 return SD_OK;
             PfAttnArgs at{};
@@ -1559,11 +1544,10 @@ sd_status create_model(const sd_config *cfg, const sd_weights *w, void *stream, 
     m->pf_ok = m->bf16 && (c.head_dim == 32 || c.head_dim == 64 || c.head_dim == 128);
     if (m->pf_ok) {
         const int64_t hd = (int64_t)c.n_heads * c.head_dim;
-        const int64_t nc = std::max<int64_t>((int64_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim, c.ffn_dim);
         m->pf_term = (int64_t)PF_ROWS * pf_pitch((int)std::max<int64_t>({c.d_model, hd, c.ffn_dim}));
         m->pf_amax_ld = std::max(c.n_heads, pf_swiglu_slots(c.ffn_dim));
         chain(dev_alloc(&m->pf_h, (size_t)PF_ROWS * c.d_model));
-        chain(dev_alloc(&m->pf_c, (size_t)PF_ROWS * nc));
+        chain(dev_alloc(&m->pf_c, (size_t)PF_ROWS * c.ffn_dim));
         chain(dev_alloc(&m->pf_q, (size_t)PF_ROWS * hd));
         // partial sums of residual updates, and the attention chunks' outputs
         chain(dev_alloc(&m->pf_part, (size_t)PF_PART_ROWS * std::max<int64_t>(c.d_model, hd)));

@@ -269,6 +269,15 @@ constexpr int PF_MAX_SPLITS = 8;  // k-splits of a residual-update GEMM, and the
 constexpr int PF_PART_ROWS = 4 * PF_ROWS;
 __host__ __device__ constexpr int pf_pitch(int K) { return (K + 31) & ~31; }
 
+// What a QKV product's epilogue needs: the rotary table, and K and V rows
+// start .. start + M - 1 of this layer's cache.
+struct PfRope {
+    const float2 *table;  // [positions][head_dim / 2] of (cos, sin)
+    uint16_t *kcache, *vcache;
+    int64_t kv_head_stride;
+    int32_t start, n_heads, n_kv_heads, head_dim;
+};
+
 // C[m][n] = sum over the terms t of rs[m] A_t[m][0..K) . W[n][0..K).
 struct PfGemmArgs {
     const uint16_t *W;  // [N][K] bf16
@@ -284,6 +293,7 @@ struct PfGemmArgs {
     // in amax[m][0 .. slots) (pitch amax_ld) maxima of |C[m]| over column ranges
     float *amax;
     int32_t amax_ld;
+    PfRope rope;        // EPI_QKV: q into C [M][ldc], k and v into the cache
 };
 
 // The same products for 17 to PF_THIN_ROWS rows (K a multiple of 64).  The
@@ -304,11 +314,7 @@ struct PfThinArgs {
     int32_t splits, n_tiles;  // n_tiles: 16-row weight tiles
     float *amax;              // SWIGLU: maxima of |C[m]| over the work-groups' columns
     int32_t amax_ld;
-    // QKV: rotary embedding, and K and V rows start .. start + M - 1 into the cache
-    uint16_t *kcache, *vcache;
-    int64_t kv_head_stride;
-    const float2 *rope;
-    int32_t start, n_heads, n_kv_heads, head_dim;
+    PfRope rope;              // QKV
 };
 
 // Causal attention of M query rows (row m at position start + m) over the
@@ -347,8 +353,9 @@ hipError_t launch_pf_norm_split(float *h, const float *part, int splits, int K, 
 hipError_t launch_pf_split(const float *x, int K, int M, const float *amax, int slots, int amax_ld, const PfTerms &t,
                            hipStream_t s);
 // C = A W^T (EPI_STORE), the partial sums of a residual update into a.part
-// (EPI_RESID; *out receives their number, for launch_pf_norm_split), or the SwiGLU of a gate/up product (EPI_SWIGLU; *out
-// receives the number of amax slots).
+// (EPI_RESID; *out receives their number, for launch_pf_norm_split), the SwiGLU
+// of a gate/up product (EPI_SWIGLU; *out receives the number of amax slots), or
+// the rotated q and the cache rows of a QKV product (EPI_QKV).
 hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out = nullptr);
 // The same with the rules of PfThinArgs: EPI_STORE, EPI_RESID (partial sums
 // into C, *out their number), EPI_SWIGLU (*out the amax slots) or EPI_QKV.
@@ -358,10 +365,6 @@ hipError_t launch_pf_thin(const PfThinArgs &a, int epi, hipStream_t s, int *out 
 constexpr int pf_thin_blocks(int M) { return M <= 32 ? 2 : (M + 15) / 16; }
 // amax slots a gate/up product of ffn columns writes at most.
 constexpr int pf_swiglu_slots(int ffn) { return (ffn + 31) / 32; }
-// Rotary embedding of q and k from the QKV GEMM output [M][(H + 2 KVH) dh];
-// q into q [M][H dh], k and v into the cache at positions start + m.
-hipError_t launch_pf_rope_kv(const float *qkv, int M, int start, const float2 *rope, int H, int KVH, int dh,
-                             float *q, uint16_t *kcache, uint16_t *vcache, int64_t kv_head_stride, hipStream_t s);
 hipError_t launch_pf_attention(const PfAttnArgs &a, const PfTerms &t, hipStream_t s);
 
 // Kernel paths of the linear layers.
