@@ -8,6 +8,8 @@
 // appended.  A draft step is the one-row case.
 #include "sd_internal.h"
 
+#include <type_traits>
+
 namespace sdk {
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
         oacc[et] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     // A chunk is one block of 128 keys while the blocks are few, else several
     // (attn_blocks), with an online softmax
-    for (int kb = c0; kb < c1; kb += ATTN_CHUNK) {
+    auto block = [&](int kb, auto more) {
         const int cw = kb + wave * MKW;  // first key of this wave
         // scores of the wave's 32 keys for query column col
         f32x4_t sacc[2];
@@ -429,8 +431,7 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
                 for (int i = 0; i < X_TERMS; ++i)
                     sacc[t] = mfma_bf16(kf[t][s], qf[s][i], sacc[t]);
         }
-        const bool more = kb + ATTN_CHUNK < c1;  // uniform
-        if (more)
+        if constexpr (decltype(more)::value)
             load_k(kb + ATTN_CHUNK);
         // softmax over those keys; slot u = 4 t + v of this lane is key 16 t + 4 v + grp
         float sv[8], mb = -INFINITY;
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
         for (int j = 0; j < NVJ; ++j)
             *reinterpret_cast<u32x4_t *>(vs + (j * RPI + lane / LPR) * VP + 8 * (lane % LPR)) = vr[j];
-        if (more)
+        if constexpr (decltype(more)::value)
             load_v(kb + ATTN_CHUNK);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
@@ -492,7 +493,11 @@ __global__ __launch_bounds__(MW * 64) void k_attn_mfma(AttnArgs a) {
             for (int i = 0; i < X_TERMS; ++i)
                 oacc[et] = mfma_bf16(vf, pf[i], oacc[et]);
         }
-    }
+    };
+    int kb = c0;
+    for (; kb + ATTN_CHUNK < c1; kb += ATTN_CHUNK)
+        block(kb, std::true_type{});
+    block(kb, std::false_type{});
     // this wave's (max, sum, O^T) into its tile, which the V rows no longer need
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     float *ro = reinterpret_cast<float *>(tile[wave]);
@@ -626,7 +631,7 @@ __global__ __launch_bounds__(VW * 64) void k_attn_valu(AttnArgs a) {
         for (int u = 0; u < 8; ++u)
             o[qi][u] = 0.0f;
     }
-    for (int kb = c0; kb < c1; kb += ATTN_CHUNK_VALU) {
+    auto block = [&](int kb, auto more) {
         float s[QV][8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -646,7 +651,7 @@ __global__ __launch_bounds__(VW * 64) void k_attn_valu(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Vg + (int64_t)keyrow(kb, i) * DH));
-        if (kb + ATTN_CHUNK_VALU < c1) {  // uniform
+        if constexpr (decltype(more)::value) {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 kr[i] = __builtin_nontemporal_load(
@@ -698,7 +703,13 @@ __global__ __launch_bounds__(VW * 64) void k_attn_valu(AttnArgs a) {
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
+    };
+    // (the last block is peeled: with the next block's loads under a branch the
+    // compiler would wait for them where V is used)
+    int kb = c0;
+    for (; kb + ATTN_CHUNK_VALU < c1; kb += ATTN_CHUNK_VALU)
+        block(kb, std::true_type{});
+    block(kb, std::false_type{});
 #pragma unroll
     for (int qi = 0; qi < QV; ++qi) {
         float y4[4], y2[2];

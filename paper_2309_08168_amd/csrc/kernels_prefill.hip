@@ -23,6 +23,7 @@
 #include "sd_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace sdk {
 namespace {
@@ -594,7 +595,12 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
             load_x(q, 0);
             load_x(q, 1);
         }
-        for (; q < ks1; q += NW) {
+        // One k-step, requesting the next one's operands if there is one.  The
+        // last is peeled: where the loads are under a branch, the compiler
+        // waits at the join for what may have been issued, that is for
+        // everything in flight (13B, 4 layers, 33 rows: 915 -> 895 us a
+        // forward; 64 rows 1063 -> 1017).
+        auto kstep = [&](int q, auto more) {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -602,8 +608,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
                     const int row = 8 * ii + lrow;
                     *reinterpret_cast<u32x4_t *>(wl + j * 1024 + row * 64 + ((lch ^ (row & 7)) << 3)) = wv[j][ii];
                 }
-            const bool more = q + NW < ks1;
-            if (more)
+            if constexpr (decltype(more)::value)
                 load_w(q + NW);
             // the staging tile is private to this wave, whose LDS accesses run
             // in program order; the fences only keep the compiler from
@@ -632,11 +637,15 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
                 // one set of registers per half step: its next activations
                 // (cache hits) are requested once its MFMAs have read these
                 __builtin_amdgcn_sched_barrier(0);
-                if (more)
+                if constexpr (decltype(more)::value)
                     load_x(q + NW, i);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        }
+        };
+        for (; q + NW < ks1; q += NW)
+            kstep(q, std::true_type{});
+        if (q < ks1)
+            kstep(q, std::false_type{});
         if (pass)
             break;
         // largest magnitude of every weight row over the waves
@@ -1061,7 +1070,7 @@ __global__ __launch_bounds__(NT) void k_pf_split(const float *x, int K, const fl
 // ahead).  With every wave loading its own K and V for 16 rows, as k_pf_attn
 // does, 1000 rows over 8000 keys read 11 GB through the L2s per 13B layer and
 // spent most of their issue slots on the softmax: 1082 us a layer; this kernel
-// TTT us.  It is bound by its matrix instructions (three bfloat16 terms of q
+// 480 us.  It is bound by its matrix instructions (three bfloat16 terms of q
 // and of the probabilities).
 //
 // 32 keys at a time: scores S^T = K q as 32x32x16 MFMAs leave lane (col, half)
