@@ -101,8 +101,8 @@ __device__ __forceinline__ bool wide_ok(uint32_t m) { return m == 0 || (m >= WRO
 // 2^sa for a row whose largest magnitude is amax, and 2^-sa
 __device__ __forceinline__ float row_scale(float amax, float *inv) {
     const int e = (int)((__float_as_uint(amax) >> 23) & 255u);
-    int sa = e == 255 || e == 0 ? 0 : 141 - e;  // inf, NaN and (sub)zero rows as they are
-    sa = sa < -100 ? -100 : (sa > 100 ? 100 : sa);
+    // both powers are normal numbers; rows with inf or NaN as they are
+    const int sa = e == 255 ? 0 : (141 - e > 126 ? 126 : 141 - e);
     *inv = __uint_as_float((uint32_t)(127 - sa) << 23);
     return __uint_as_float((uint32_t)(127 + sa) << 23);
 }

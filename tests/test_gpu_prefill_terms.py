@@ -9,6 +9,8 @@ float16 window of their operands.
 - Weight rows far outside the float16 window of the GEMMs' common scale (they
   run again with a scale per row), and an MLP activation 2^12 times the others
   that its down weights undo, beside one 2^-35 times the others.
+- MLP activations of every row near the ends of float32's range, the down
+  weights undoing the factor.
 - The rotary embedding and KV append in the thin QKV product, after a prefix
   and after a decode step over the keys it wrote.
 
@@ -73,7 +75,7 @@ def _check(cfg, rows, scaled):
     out = torch.full((rows, cfg.vocab), float("nan"), dtype=torch.float32, device="cuda")
     dm.forward(toks, dm.cache(rows), skip=skip, logits=out)
     scale = np.ones(cfg.vocab)
-    if scaled:
+    if scaled is True:
         for r, e in HEAD_ROWS.items():
             scale[r] = 2.0 ** e
     plain = scale == 1
@@ -93,6 +95,21 @@ def test_products_at_tile_edges(cfg, rows):
 @pytest.mark.parametrize("cfg", [THIN, LONG_K], ids=lambda c: c.name)
 def test_rows_outside_the_float16_window(cfg, rows):
     _check(cfg, rows, True)
+
+
+@pytest.mark.parametrize("rows", [33, 100])
+@pytest.mark.parametrize("exp", [-112, 112])
+def test_activations_near_the_ends_of_the_range(exp, rows):
+    """Up weights times 2^exp, down weights times 2^-exp: both exact in bfloat16, and so is every product's factor."""
+    key = (THIN.name, exp)
+    if key not in _models:
+        w = S.make_weights(THIN, 11)
+        F = THIN.ffn_dim
+        gu, down = w["layers.0.w_gate_up"], w["layers.0.w_down"]
+        gu[F:] = S.scale_tensor(np.ascontiguousarray(gu[F:]), 2.0 ** exp, "bf16")
+        down[:] = S.scale_tensor(down, 2.0 ** -exp, "bf16")
+        _models[key] = (w, oracle.Model(THIN, w), U.device_model(THIN, w))
+    _check(THIN, rows, exp)
 
 
 @pytest.mark.parametrize("name", list(A.CONFIGS))
