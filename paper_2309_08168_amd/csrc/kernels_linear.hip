@@ -835,8 +835,8 @@ static hipError_t launch_fp8_r(const LinearArgs &a, int epi, int n_tiles, hipStr
 // rows, two up to 10, three up to 16).  The host picks NP from its bound on
 // M (LinearArgs::max_rows).
 //
-// The launch bound asks for two waves per SIMD up to four tiles (eight do
-// not fit twice in LDS or in the registers).  With one set of activation
+// The launch bound asks for two waves per SIMD up to four tiles (seven do
+// not fit twice in LDS).  With one set of activation
 // registers (below) the four-tile kernel at three packings fits that in 218
 // registers without spilling; double-buffered activations took 260 (one
 // wave per SIMD), and 13B verification at 13-16 rows was 2% slower.
@@ -1168,67 +1168,48 @@ template <int TN, int NW, int NP>
 static hipError_t launch_mfma(const LinearArgs &a, int epi, int n_tiles, hipStream_t s, const LaunchTiming &t) {
     const int groups = (n_tiles + TN - 1) / TN;
     dim3 grid(groups * (epi == EPI_PARTIAL ? a.splits : 1)), block(NW * 64);
-    switch (epi) {
-    case EPI_PARTIAL:
-        if (a.splits < 1 || !a.part)
+    if constexpr (TN == 2) {  // (mfma_tiles)
+        if (epi != EPI_PARTIAL || a.splits < 1 || !a.part)
             return hipErrorInvalidValue;
         launch_k(k_linear_mfma<EPI_PARTIAL, TN, NW, NP>, grid, block, s, t, a);
-        break;
-    case EPI_STORE:
-        launch_k(k_linear_mfma<EPI_STORE, TN, NW, NP>, grid, block, s, t, a);
-        break;
-    case EPI_RESID:
-        launch_k(k_linear_mfma<EPI_RESID, TN, NW, NP>, grid, block, s, t, a);
-        break;
-    case EPI_SWIGLU:
-        launch_k(k_linear_mfma<EPI_SWIGLU, TN, NW, NP>, grid, block, s, t, a);
-        break;
-    case EPI_QKV:
-        launch_k(k_linear_mfma<EPI_QKV, TN, NW, NP>, grid, block, s, t, a);
-        break;
-    case EPI_HEAD:
-        launch_k(k_linear_mfma<EPI_HEAD, TN, NW, NP>, grid, block, s, t, a);
-        break;
-    default:
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-// The work-group shape follows the output kind and the packing count
-// (mfma_shape_tn / mfma_shape_nw).
-constexpr int MFMA_WIDE_TILES = 1600;
-
-static hipError_t launch_mfma_np(const LinearArgs &a, int epi, int n_tiles, hipStream_t s,
-                                 const LaunchTiming &t) {
-    const int np = mfma_packs(a.max_rows);
-    if (epi == EPI_PARTIAL) {
-        switch (np) {
-        case 1:
-            return launch_mfma<mfma_shape_tn(EPI_PARTIAL, 1), mfma_shape_nw(EPI_PARTIAL, 1), 1>(a, epi, n_tiles, s, t);
-        case 2:
-            return launch_mfma<mfma_shape_tn(EPI_PARTIAL, 2), mfma_shape_nw(EPI_PARTIAL, 2), 2>(a, epi, n_tiles, s, t);
-        case 3:
-            return launch_mfma<mfma_shape_tn(EPI_PARTIAL, 3), mfma_shape_nw(EPI_PARTIAL, 3), 3>(a, epi, n_tiles, s, t);
+        return hipGetLastError();
+    } else {
+        switch (epi) {
+        case EPI_STORE:
+            launch_k(k_linear_mfma<EPI_STORE, TN, NW, NP>, grid, block, s, t, a);
+            break;
+        case EPI_RESID:
+            launch_k(k_linear_mfma<EPI_RESID, TN, NW, NP>, grid, block, s, t, a);
+            break;
+        case EPI_SWIGLU:
+            launch_k(k_linear_mfma<EPI_SWIGLU, TN, NW, NP>, grid, block, s, t, a);
+            break;
+        case EPI_QKV:
+            launch_k(k_linear_mfma<EPI_QKV, TN, NW, NP>, grid, block, s, t, a);
+            break;
+        case EPI_HEAD:
+            launch_k(k_linear_mfma<EPI_HEAD, TN, NW, NP>, grid, block, s, t, a);
+            break;
         default:
             return hipErrorInvalidValue;
         }
+        return hipGetLastError();
     }
-    switch (np) {
-    case 1:
-        return launch_mfma<mfma_shape_tn(EPI_STORE, 1), mfma_shape_nw(EPI_STORE, 1), 1>(a, epi, n_tiles, s, t);
+}
+
+template <int NP>
+static hipError_t launch_mfma_np(const LinearArgs &a, int epi, int n_tiles, hipStream_t s, const LaunchTiming &t) {
+    switch (mfma_tiles(epi, NP, n_tiles)) {
     case 2:
-        return launch_mfma<mfma_shape_tn(EPI_STORE, 2), mfma_shape_nw(EPI_STORE, 2), 2>(a, epi, n_tiles, s, t);
+        return launch_mfma<2, MFMA_WAVES, NP>(a, epi, n_tiles, s, t);
     case 3:
-        // Three packings on a wide gate/up or lm-head: eight tiles per
-        // work-group halve the activation-fragment loads per weight byte.
-        // Measured at the 13B shapes, 13 rows: gate/up (1728 tiles) 57.9 ->
-        // 53.2 us, lm-head (2000 tiles) 60.7 -> 58.0; QKV (960 tiles, 120
-        // work-groups of eight) 33.0 -> 50.6, and at 4 or 8 rows eight tiles
-        // lose everywhere.
-        if ((epi == EPI_SWIGLU || epi == EPI_HEAD) && n_tiles >= MFMA_WIDE_TILES)
-            return launch_mfma<8, 4, 3>(a, epi, n_tiles, s, t);
-        return launch_mfma<mfma_shape_tn(EPI_STORE, 3), mfma_shape_nw(EPI_STORE, 3), 3>(a, epi, n_tiles, s, t);
+        return launch_mfma<3, MFMA_WAVES, NP>(a, epi, n_tiles, s, t);
+    case 4:
+        return launch_mfma<4, MFMA_WAVES, NP>(a, epi, n_tiles, s, t);
+    case 7:
+        if constexpr (NP > 1)
+            return launch_mfma<7, MFMA_WAVES, NP>(a, epi, n_tiles, s, t);
+        return hipErrorInvalidValue;
     default:
         return hipErrorInvalidValue;
     }
@@ -1256,7 +1237,16 @@ hipError_t launch_linear(const LinearArgs &a, int epi, bool bf16, int path, int 
             return hipErrorInvalidValue;
         LinearArgs b = a;
         b.n_tiles = n_tiles;
-        return launch_mfma_np(b, epi, n_tiles, s, t);
+        switch (mfma_packs(a.max_rows)) {
+        case 1:
+            return launch_mfma_np<1>(b, epi, n_tiles, s, t);
+        case 2:
+            return launch_mfma_np<2>(b, epi, n_tiles, s, t);
+        case 3:
+            return launch_mfma_np<3>(b, epi, n_tiles, s, t);
+        default:
+            return hipErrorInvalidValue;
+        }
     }
     if (path == PATH_GEMV_FP8) {
         if (!bf16 || (a.K & 15) || !a.wexp)

@@ -270,7 +270,7 @@ Plan make_plan(const sd_model *m, LinearKind kind, int rows) {
         else
             p.n_tiles = cdiv(p.N, 16);
         // 16-row tiles; the work-group shape is picked per launch from the
-        // packing count (mfma_shape_tn / mfma_shape_nw)
+        // packing count and the number of tiles (mfma_tiles)
         p.rows = 16;
         if (kind == LK_O || kind == LK_DOWN) {
             // Narrow outputs: the reduction is split over work-groups and the
@@ -1600,7 +1600,7 @@ std::string kernel_symbol(const sd_model *m, const Plan &p) {
         const int hi = m->timed_rows_hi ? m->timed_rows_hi : MAX_ROWS;
         const int np = mfma_packs(hi);
         std::string nm = "void sdk::k_linear_mfma<" + std::to_string(p.epi) + ", " +
-                         std::to_string(mfma_shape_tn(p.epi, np)) + ", " + std::to_string(mfma_shape_nw(p.epi, np)) +
+                         std::to_string(mfma_tiles(p.epi, np, p.n_tiles)) + ", " + std::to_string(MFMA_WAVES) +
                          ", " + std::to_string(np) + ">(sdk::LinearArgs)";
         if (m->timed_rows_lo && mfma_packs(m->timed_rows_lo) != mfma_packs(hi))
             nm += " (mixed packings)";

@@ -108,15 +108,29 @@ __device__ __forceinline__ uint16_t bf16_rne_bits(float f) {
 // MFMAs per k-step (16 packed columns each) for up to max_rows rows.
 __host__ __device__ constexpr int mfma_packs(int max_rows) { return (X_TERMS * max_rows + 15) / 16; }
 
-// MFMA work-group shape (16-row tiles per work-group, waves per work-group)
-// by output kind and packing count, from sweeps at the 13B shapes: two
-// tiles for the split-K output projections, four otherwise (at 4, 8 and 13
-// rows); four waves throughout.  The launcher takes eight tiles for wide
-// gate/up and lm-head layers at three packings (launch_mfma_np).
-__host__ __device__ constexpr int mfma_shape_tn(int epi, int np) {
-    return (void)np, epi == EPI_PARTIAL ? 2 : 4;
+// 16-row tiles per work-group of four waves on the MFMA path.  Split-K output
+// projections take two.  The others take the size that leaves the busiest of
+// the 256 CUs the fewest tiles: the time follows that count, not the total
+// (us, tiles on the busiest CU in brackets; sweep of 2, 3, 4, 6, 7 and 8):
+//   gate/up  7B, 5 rows:  3 tiles 32.9 (6), 4 tiles 43.4 (8), 6 tiles 38.1 (6)
+//            70B, 9 rows: 3 tiles 153.7 (15), 4 tiles 194.5 (16)
+//            13B, 5 rows: 3 tiles 53.0 (9), 4 tiles 47.8 (8)
+//   QKV      70B, 9 rows: 3 tiles 36.2 (3), 4 tiles 45.5 (4)
+//            13B, 5 rows: 3 tiles 36.3 (6), 4 tiles 30.1 (4)
+// From two packings on, activations are a good part of the loads, and seven
+// tiles share them where that is one work-group per CU (13B gate/up: 50.8 ->
+// 49.3 us at 9 rows, 54.7 -> 51.4 at 13; not at 5, 47.8 and 48.2, and not in
+// several rounds: 70B, 9 rows, 168).
+constexpr int MFMA_CUS = 256, MFMA_WAVES = 4;
+__host__ __device__ constexpr int mfma_busiest(int tn, int n_tiles) {
+    return ((n_tiles + tn - 1) / tn + MFMA_CUS - 1) / MFMA_CUS * tn;
 }
-__host__ __device__ constexpr int mfma_shape_nw(int epi, int np) { return (void)epi, (void)np, 4; }
+__host__ __device__ constexpr int mfma_tiles(int epi, int np, int n_tiles) {
+    if (epi == EPI_PARTIAL)
+        return 2;
+    const int tn = mfma_busiest(3, n_tiles) < mfma_busiest(4, n_tiles) ? 3 : 4;
+    return np > 1 && mfma_busiest(7, n_tiles) == 7 && mfma_busiest(tn, n_tiles) > 7 ? 7 : tn;
+}
 
 // Fragment layout of the MFMA-path activations.  For k-step q = k / 128,
 // packing p and 32-wide slice i = (k % 128) / 32, the 16 columns x 32 k of
