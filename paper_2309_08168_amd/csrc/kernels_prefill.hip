@@ -503,7 +503,7 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
 
 // ---------------------------------------------------------------------------
 // GEMM for few rows (17 to 64): bound by the weight stream, with 2 M flops per
-// weight byte on top.  A work-group owns four tiles of 16 weight rows, over all
+// weight byte on top.  A work-group owns TN tiles of 16 weight rows, over all
 // MB blocks of 16 activation rows; its NW waves take every NW-th 64-element
 // k-step and meet in LDS at the end, so nothing is shared and no wave waits
 // for another inside the loop (the tile kernel above spends 0.4 us per 32-k
@@ -1399,10 +1399,16 @@ hipError_t launch_thin_mb(const PfThinArgs &a, hipStream_t s) {
         hipLaunchKernelGGL((k_pf_thin<EPI, 2, NW, TN>), grid, block, 0, s, a);
         break;
     case 3:
-        hipLaunchKernelGGL((k_pf_thin<EPI, 3, NW, TN>), grid, block, 0, s, a);
+        if constexpr (TN > 4)
+            return hipErrorInvalidValue;
+        else
+            hipLaunchKernelGGL((k_pf_thin<EPI, 3, NW, TN>), grid, block, 0, s, a);
         break;
     case 4:
-        hipLaunchKernelGGL((k_pf_thin<EPI, 4, NW, TN>), grid, block, 0, s, a);
+        if constexpr (TN > 4)
+            return hipErrorInvalidValue;
+        else
+            hipLaunchKernelGGL((k_pf_thin<EPI, 4, NW, TN>), grid, block, 0, s, a);
         break;
     default:
         return hipErrorInvalidValue;
@@ -1506,7 +1512,6 @@ hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out
         if (a.N % 16 || !a.amax || !out)
             return hipErrorInvalidValue;
         a.n_tiles = a.N / 16;
-        *out = (a.n_tiles + 3) / 4;
     } else if (epi == EPI_QKV) {
         if (a.rope.head_dim % 16)
             return hipErrorInvalidValue;
@@ -1514,7 +1519,21 @@ hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out
     } else {
         a.n_tiles = (a.N + 15) / 16;
     }
-    const int groups = (a.n_tiles + 3) / 4;
+    // Tiles per work-group: four, or three where that takes an eighth off the
+    // tiles of the busiest CU (us, 33 rows: 7B gate/up, 6 for 8, 57.1 -> 49.1,
+    // QKV, 3 for 4, 33.2 -> 29.4; 70B QKV 54.5 -> 48.3; not 15 for 16, 70B
+    // gate/up 215 and 222: every group loads all activations).  Up to 32 rows
+    // seven where that is one group per CU (13B gate/up, 20 rows: 59.5 -> 53.4;
+    // at 33 rows, without registers for them, 70 -> 79).
+    int tn = 4;
+    if (epi != EPI_RESID) {
+        tn = 8 * mfma_busiest(3, a.n_tiles) <= 7 * mfma_busiest(4, a.n_tiles) ? 3 : 4;
+        if (a.M <= 32 && mfma_busiest(7, a.n_tiles) == 7 && mfma_busiest(tn, a.n_tiles) > 7)
+            tn = 7;
+    }
+    const int groups = (a.n_tiles + tn - 1) / tn;
+    if (epi == EPI_SWIGLU)
+        *out = groups;
     if (epi == EPI_RESID) {
         if (!out)
             return hipErrorInvalidValue;
@@ -1528,7 +1547,12 @@ hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out
     // Eight waves where one work-group per CU takes the layer, four where two
     // fit on many CUs (33 rows: 13B QKV, 240 groups, 41.2 against 43.6 us;
     // gate/up, 432 groups, 75.0 against 70.9).
-    return groups * a.splits <= 256 ? launch_thin_nw<8, 4>(a, epi, s) : launch_thin_nw<4, 4>(a, epi, s);
+    const bool one = groups * a.splits <= MFMA_CUS;
+    if (tn == 3)
+        return one ? launch_thin_nw<8, 3>(a, epi, s) : launch_thin_nw<4, 3>(a, epi, s);
+    if (tn == 7)
+        return launch_thin_nw<8, 7>(a, epi, s);
+    return one ? launch_thin_nw<8, 4>(a, epi, s) : launch_thin_nw<4, 4>(a, epi, s);
 }
 
 // Chunks of the keys per row block: enough work-groups for PA_UNITS of them,

@@ -377,8 +377,9 @@ bool pf_thin_ok(int M, int64_t N, int K);
 hipError_t launch_pf_thin(const PfThinArgs &a, int epi, hipStream_t s, int *out = nullptr);
 // Blocks of 16 rows of a thin GEMM's input.
 constexpr int pf_thin_blocks(int M) { return M <= 32 ? 2 : (M + 15) / 16; }
-// amax slots a gate/up product of ffn columns writes at most.
-constexpr int pf_swiglu_slots(int ffn) { return (ffn + 31) / 32; }
+// amax slots a gate/up product of ffn columns writes at most (24 columns each:
+// three tiles of k_pf_thin).
+constexpr int pf_swiglu_slots(int ffn) { return (ffn + 23) / 24; }
 hipError_t launch_pf_attention(const PfAttnArgs &a, const PfTerms &t, hipStream_t s);
 
 // Kernel paths of the linear layers.

@@ -1,5 +1,5 @@
-"""GPU parity of the verification products for every tile count their
-work-groups take.
+"""GPU parity of the products of verifications and short prompts for every tile
+count their work-groups take.
 
 One-layer models of d 128 (attention skipped: nothing is rounded to bfloat16 on
 the way) whose gate/up product and head have 24 to 2000 tiles of 16 rows: three
@@ -11,7 +11,9 @@ Tolerance: the products of the activations' three bfloat16 terms are exact, so
 only float32 sums round: at most 14000 terms in 3 x 437 matrix instructions and
 8 + 4 partial sums of 2^-24 of the running sum each, in a chain of three
 products; 3 x 1323 x 2^-24 = 2.4e-4 of the row's logit deviation bounds the
-difference, and the sums' rounding is far from its worst case: 1e-4.
+difference, and the sums' rounding is far from its worst case: 1e-4.  Prompts
+have two float16 terms: two thirds of the instructions, and 2^-22 of each
+activation.
 """
 
 import numpy as np
@@ -46,7 +48,7 @@ def _pair(F, V):
     return _models[(F, V)]
 
 
-@pytest.mark.parametrize("rows", [3, 5, 6, 10, 11, 16])
+@pytest.mark.parametrize("rows", [3, 5, 6, 10, 11, 16, 17, 32, 33, 64])
 @pytest.mark.parametrize("F,V", SHAPES)
 def test_tile_counts(F, V, rows):
     cfg, om, dm = _pair(F, V)
