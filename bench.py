@@ -110,14 +110,16 @@ def traffic_for(kernel: str, workload: str = "13b"):
 
 
 def prefill_flops(cfg, M: int, lin_terms: int = 1, attn_terms: int = 1) -> float:
-    """Useful flops of the full-model forward of M rows from position 0:
-    every linear layer (2 M N K) and causal attention (scores and weighted
-    values, 2 head_dim flops per query-key pair each)."""
+    """Useful flops of the full-model prefill of M rows from position 0: every
+    linear layer (2 M N K) and causal attention (scores and weighted values,
+    2 head_dim flops per query-key pair each), the last layer up to its keys
+    and values."""
     hd = cfg.n_heads * cfg.head_dim
     nq = (cfg.n_heads + 2 * cfg.n_kv_heads) * cfg.head_dim
     lin = nq * cfg.d_model + cfg.d_model * hd + 2 * cfg.ffn_dim * cfg.d_model + cfg.d_model * cfg.ffn_dim
     attn = 2 * 2 * cfg.head_dim * cfg.n_heads * M * (M + 1) / 2
-    return cfg.n_layers * (lin_terms * 2.0 * M * lin + attn_terms * attn)
+    L = cfg.n_layers
+    return lin_terms * 2.0 * M * (L * lin - (lin - nq * cfg.d_model)) + attn_terms * (L - 1) * attn
 
 
 def prefill_roofline(cfg, M: int, ms: float):
@@ -830,11 +832,15 @@ def _dispatches(path):
 
 def _forwards(disp):
     """The dispatches of each sd_forward (a forward of up to 16 rows starts with
-    the control-block kernel); runtime copies and torch kernels are left out."""
+    the control-block kernel, or with the embedding that writes the control
+    block); runtime copies and torch kernels are left out."""
     out, cur = [], None
     for name, c, ns in disp:
         if "k_set_ctl" in name:
             cur = []
+            out.append(cur)
+        elif "k_embed_host" in name:
+            cur = [(name, c, ns)]
             out.append(cur)
         elif cur is not None and "copyBuffer" not in name and "at::native" not in name:
             cur.append((name, c, ns))

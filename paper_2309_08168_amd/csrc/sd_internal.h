@@ -113,14 +113,14 @@ __host__ __device__ constexpr int mfma_packs(int max_rows) { return (X_TERMS * m
 // the 256 CUs the fewest tiles: the time follows that count, not the total
 // (us, tiles on the busiest CU in brackets; sweep of 2, 3, 4, 6, 7 and 8):
 //   gate/up  7B, 5 rows:  3 tiles 32.9 (6), 4 tiles 43.4 (8), 6 tiles 38.1 (6)
-//            70B, 9 rows: 3 tiles 153.7 (15), 4 tiles 194.5 (16)
+//            70B, 9 rows: 3 tiles 151.9 (15), 4 tiles 177.8 (16)
 //            13B, 5 rows: 3 tiles 53.0 (9), 4 tiles 47.8 (8)
-//   QKV      70B, 9 rows: 3 tiles 36.2 (3), 4 tiles 45.5 (4)
+//   QKV      70B, 9 rows: 3 tiles 35.6 (3), 4 tiles 42.5 (4)
 //            13B, 5 rows: 3 tiles 36.3 (6), 4 tiles 30.1 (4)
 // From two packings on, activations are a good part of the loads, and seven
 // tiles share them where that is one work-group per CU (13B gate/up: 50.8 ->
 // 49.3 us at 9 rows, 54.7 -> 51.4 at 13; not at 5, 47.8 and 48.2, and not in
-// several rounds: 70B, 9 rows, 168).
+// several rounds: 70B, 9 rows, 151 and 168 on two cards, 152 and 154 with three).
 constexpr int MFMA_CUS = 256, MFMA_WAVES = 4;
 __host__ __device__ constexpr int mfma_busiest(int tn, int n_tiles) {
     return ((n_tiles + tn - 1) / tn + MFMA_CUS - 1) / MFMA_CUS * tn;
