@@ -109,7 +109,7 @@ def traffic_for(kernel: str, workload: str = "13b"):
     return e["bytes_per_launch"]
 
 
-def prefill_flops(cfg, M: int, lin_terms: int = 1, attn_terms: int = 1) -> float:
+def prefill_flops(cfg, M: int) -> float:
     """Useful flops of the full-model prefill of M rows from position 0: every
     linear layer (2 M N K) and causal attention (scores and weighted values,
     2 head_dim flops per query-key pair each), the last layer up to its keys
@@ -119,23 +119,21 @@ def prefill_flops(cfg, M: int, lin_terms: int = 1, attn_terms: int = 1) -> float
     lin = nq * cfg.d_model + cfg.d_model * hd + 2 * cfg.ffn_dim * cfg.d_model + cfg.d_model * cfg.ffn_dim
     attn = 2 * 2 * cfg.head_dim * cfg.n_heads * M * (M + 1) / 2
     L = cfg.n_layers
-    return lin_terms * 2.0 * M * (L * lin - (lin - nq * cfg.d_model)) + attn_terms * (L - 1) * attn
+    return 2.0 * M * (L * lin - (lin - nq * cfg.d_model)) + (L - 1) * attn
 
 
 def prefill_roofline(cfg, M: int, ms: float):
-    """The prefill against the 16-bit matrix-core peak.  Activations enter the
-    linear layers as two float16 terms, and queries and probabilities the
-    attention as three bf16 terms, so the cores issue two and three times the
+    """The prefill against the bf16 matrix-core peak.  Activations enter the
+    matrix cores as three bf16 terms, so the cores issue three times the
     useful flops."""
     if ms <= 0 or M < 1:
         return None
     fl = prefill_flops(cfg, M)
     useful = fl / (ms / 1e3) / 1e12
-    issued = prefill_flops(cfg, M, 2, 3) / (ms / 1e3) / 1e12
     return {"bound": "mfma", "rows": M, "ms": round(ms, 2), "useful_tflops": round(useful, 1),
-            "issued_tflops": round(issued, 1), "peak_tflops": MFMA_BF16_PEAK_TFLOPS,
+            "issued_tflops": round(3 * useful, 1), "peak_tflops": MFMA_BF16_PEAK_TFLOPS,
             "frac_useful": round(useful / MFMA_BF16_PEAK_TFLOPS, 4),
-            "frac_issued": round(issued / MFMA_BF16_PEAK_TFLOPS, 4)}
+            "frac_issued": round(3 * useful / MFMA_BF16_PEAK_TFLOPS, 4)}
 
 
 def host_cpu() -> dict:

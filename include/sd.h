@@ -117,7 +117,7 @@ typedef struct {
  * hipStream_t (NULL = the default stream).  Validates the shape and
  * allocates the library's device workspace (activations of up to 16 rows,
  * rotary table, reduction scratch; for bfloat16 models with head_dim 32, 64
- * or 128 also the large-forward workspace of 1024 rows, about 270 MB at the
+ * or 128 also the large-forward workspace of 1024 rows, about 240 MB at the
  * 13B shape).  Errors: INVALID_ARG, OOM, DEVICE. */
 sd_status sd_model_create(const sd_config *config, const sd_weights *weights, void *hip_stream, sd_model **out);
 /* Waits for the model's stream, then frees the model and its workspace.

@@ -3,10 +3,10 @@
 // long forwards in general.  With hundreds of rows the linear layers are
 // dense contractions, 2 M N K flops per N K weight bytes, so they run on
 // matrix cores:
-//   - k_pf_gemm: C = A W^T with the float32 activations as two float16 terms
-//     and the weights turned into float16 on the way, v_mfma 16x16x32 f16 on
-//     tiles of 256 x 256 down to 128 x 64, every operand loaded straight into
-//     LDS in MFMA fragment order; tiles are ordered so the work-groups one XCD
+//   - k_pf_gemm: C = A W^T with the float32 activations as X_TERMS bfloat16
+//     terms (exact for float32 values), v_mfma 16x16x32 bf16 on tiles of
+//     256 x 256 down to 128 x 64, every operand loaded straight into LDS in
+//     MFMA fragment order; tiles are ordered so the work-groups one XCD
 //     runs together share their weight and activation slices in that XCD's
 //     L2; residual updates split the reduction into partials
 //     (the QKV product's epilogue rotates q and k and appends to the cache, the
@@ -17,9 +17,8 @@
 //     scores and the weighted sum of values on matrix cores with an online
 //     softmax over 32-key blocks, the longest row blocks dispatched first and
 //     spread evenly over the XCDs;
-//   - small row kernels between them: embedding, RMSNorm into terms (adding a
-//     residual update's partials first), and the terms of the attention output
-//     and of the MLP activation.
+//   - small row kernels between them: embedding, and RMSNorm into terms (adding
+//     a residual update's partials first).
 #include "sd_internal.h"
 
 #include <algorithm>
@@ -29,8 +28,6 @@ namespace sdk {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
-typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -41,18 +38,6 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                    c, 0, 0, 0);
 }
-
-__device__ __forceinline__ f32x4_t mfma16h(u32x4_t a, u32x4_t b, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0,
-                                                  0, 0);
-}
-
-__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a),
-                                                                  __builtin_bit_cast(u16x2_t, b)));
-}
-
-__device__ __forceinline__ float bf_to_f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
 // Terms of eight consecutive values, each packed as 8 bf16 (one 16-byte word).
 __device__ __forceinline__ void split8(const float (&x)[8], u32x4_t (&t)[X_TERMS]) {
@@ -73,50 +58,36 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4_t (&t)[X_TERMS
 }
 
 // ---------------------------------------------------------------------------
-// GEMM inputs as float16 terms
+// GEMM inputs
 //
-// A float32 activation row x is held as PF_TERMS = 2 float16 planes of the row
-// times a power of two: x 2^sa = hi + lo, hi = rne(x 2^sa), lo = rne(x 2^sa - hi),
-// with the row's largest magnitude in [2^14, 2^15), and rs[row] = 2^-sa undoes
-// the scale in the GEMM's epilogue.  hi and lo carry 22 bits of every element
-// down to 2^-18 of the row's largest and are within 2^-40 of the largest below
-// that: an activation smaller than 2^-18 of its row keeps fewer bits (three
-// bfloat16 terms kept them all), which shows in an output only if the larger
-// ones meet weights that much smaller.  The outlier channels of trained models
-// are about 2^12 times the rest.
-// Weights become float16 on their way into LDS, times WSCALE: exact for
-// bfloat16 values from 2^-17 / WSCALE up, and to 2^-24 / WSCALE absolutely
-// below that.  A tile whose rows do not fit that window (wide_ok) runs again
-// with a power of two per weight row.  Products of the terms are exact, only
-// the float32 accumulation rounds, as with three bfloat16 terms, in two
-// thirds of the matrix instructions and so of the accumulation steps: against
-// float64 the outputs are nearer.
+// A float32 activation is held as X_TERMS bfloat16 terms, which reproduce it
+// exactly, and the weights are multiplied as stored, so every product is exact
+// and only the float32 accumulation rounds.  (Two float16 terms of the row times
+// a power of two take two thirds of the matrix instructions, but hold 22 bits,
+// fewer below 2^-18 of the row's largest: MLP channels 2^24 and 2^30 times the
+// others, undone by their down weights, moved logits by 0.39 of their deviation.)
 
-constexpr float WSCALE = 1024.0f;
-// magnitudes (bf16 bits) a weight row's largest may have at WSCALE: 2^-14 up to 2^5 (2^15 scaled)
-constexpr uint32_t WROW_MIN = (127 - 14) << 7, WROW_MAX = (127 + 5) << 7;
-
-__device__ __forceinline__ bool wide_ok(uint32_t m) { return m == 0 || (m >= WROW_MIN && m <= WROW_MAX); }
-
-// 2^sa for a row whose largest magnitude is amax, and 2^-sa
-__device__ __forceinline__ float row_scale(float amax, float *inv) {
-    const int e = (int)((__float_as_uint(amax) >> 23) & 255u);
-    // both powers are normal numbers; rows with inf or NaN as they are
-    const int sa = e == 255 ? 0 : (141 - e > 126 ? 126 : 141 - e);
-    *inv = __uint_as_float((uint32_t)(127 - sa) << 23);
-    return __uint_as_float((uint32_t)(127 + sa) << 23);
+// Terms of elements k .. k + 7 of row m (K of them): from x, one 16-byte word a term.
+__device__ __forceinline__ void store_terms8(const PfTerms &o, int m, int k, int K, const float (&x)[8]) {
+    u32x4_t t[X_TERMS];
+    split8(x, t);
+    uint16_t *p = o.at(m, k, K);
+#pragma unroll
+    for (int i = 0; i < X_TERMS; ++i)
+        *reinterpret_cast<u32x4_t *>(p + i * o.step()) = t[i];
 }
 
-// The terms of eight consecutive scaled values, each packed as 8 halves.
-__device__ __forceinline__ void split_f16x8(const float (&x)[8], u32x4_t &hi, u32x4_t &lo) {
-    f16x8_t h, l;
+// The same of four elements (k a multiple of 4).
+__device__ __forceinline__ void store_terms4(const PfTerms &o, int m, int k, int K, f32x4_t x) {
+    uint16_t h[4][X_TERMS];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        h[u] = (_Float16)x[u];
-        l[u] = (_Float16)(x[u] - (float)h[u]);
-    }
-    hi = __builtin_bit_cast(u32x4_t, h);
-    lo = __builtin_bit_cast(u32x4_t, l);
+    for (int u = 0; u < 4; ++u)
+        split3(x[u], h[u]);
+    uint16_t *p = o.at(m, k, K);
+#pragma unroll
+    for (int i = 0; i < X_TERMS; ++i)
+        *reinterpret_cast<u32x2_t *>(p + i * o.step()) =
+            u32x2_t{(uint32_t)h[0][i] | ((uint32_t)h[1][i] << 16), (uint32_t)h[2][i] | ((uint32_t)h[3][i] << 16)};
 }
 
 // Row i of 16-row weight tile t of a QKV product: eight elements of the first
@@ -171,11 +142,9 @@ __device__ __forceinline__ void store_qkv4(const PfRope &a, int t, int i, int m,
 // 32-k stages through LDS.  Every 16 x 32 MFMA operand block is 1 KB of LDS
 // with lane l's 16 bytes at 16 l, so a fragment read is one contiguous 1 KB
 // read.  All operands go from global memory straight into LDS
-// (global_load_lds_dwordx4: lane l's 16 bytes to 16 l), P stages ahead: the
-// activation terms as they are, the weights as bfloat16 into a block of the
-// wave that loads them, which turns them into float16 one stage before they
-// are multiplied.  The barrier is a bare s_barrier: a release fence before it
-// would also wait for the loads of the coming stages.
+// (global_load_lds_dwordx4: lane l's 16 bytes to 16 l), P stages ahead in
+// P + 1 stage buffers.  The barrier is a bare s_barrier: a release fence before
+// it would also wait for the loads of the coming stages.
 
 // s_waitcnt immediate (gfx9 layout: vmcnt bits 3:0 and 15:14, expcnt 6:4,
 // lgkmcnt 11:8) that waits for vmcnt n and leaves the other counters alone
@@ -196,22 +165,15 @@ __device__ __forceinline__ void load_to_lds16(const uint16_t *g, uint16_t *l) {
 
 template <int EPI, int BN, int BM, int NWN, int NWM, int P, int WPS>
 __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
-    constexpr int T = PF_TERMS, NW = NWN * NWM;
+    constexpr int T = X_TERMS, NW = NWN * NWM;
     constexpr int WN = BN / NWN, WM = BM / NWM;          // a wave's share
     constexpr int NT = WN / 16, MT = WM / 16;            // 16 x 16 output tiles per wave
-    constexpr int NBW = BN / 16, NBA = T * BM / 16;      // weight and activation blocks per stage
-    constexpr int WPW = (NBW + NW - 1) / NW, APW = (NBA + NW - 1) / NW;  // load instructions per wave and stage
+    constexpr int NBW = BN / 16, NB = NBW + T * BM / 16; // blocks per stage: weights, then activation terms
+    constexpr int PW = (NB + NW - 1) / NW;               // load instructions per wave and stage
     static_assert(NT * 16 == WN && MT * 16 == WM, "tile split");
     static_assert(EPI == EPI_STORE || EPI == EPI_PARTIAL || EPI == EPI_SWIGLU || EPI == EPI_QKV, "epilogue");
     constexpr bool SWI = EPI == EPI_SWIGLU, QKV = EPI == EPI_QKV;
-    // float16 weights, activation terms, bfloat16 weights (a block per wave and load)
-    constexpr int LW = 2 * NBW * 512, LA = (P + 1) * NBA * 512, LR = P * WPW * NW * 512;
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[LW + LA + LR];
-    uint16_t *const lw = lds, *const la = lds + LW, *const lr = lds + LW + LA;
-    // after the main loop: 1 / scale of each weight row, and row maxima
-    float *const wsc = reinterpret_cast<float *>(lds);
-    uint32_t *const ymax = reinterpret_cast<uint32_t *>(lds) + BN;
-    static_assert(LW * 2 >= (BN + BM + 1) * 4, "epilogue scratch");
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[(P + 1) * NB * 512];
 
     constexpr int BC = SWI ? BN / 2 : BN;                // output columns per tile
     const int M = a.M, N = a.N, K = a.K, F = N / 2;
@@ -230,7 +192,7 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
     const int GM = TM < 4 ? TM : 4;
     const int grp_i = L / (GM * TN), first = grp_i * GM, gm = min(TM - first, GM);
     const int in = L - grp_i * GM * TN;
-    const int m0 = (first + in % gm) * BM, tn = in / gm, n0 = tn * BC;  // SWI: n0 is the first f
+    const int m0 = (first + in % gm) * BM, n0 = in / gm * BC;  // SWI: n0 is the first f
     // the split's stages (possibly none: its partial tile is then zeros)
     const int S_all = (K + 31) / 32, S_per = (S_all + a.splits - 1) / a.splits;
     const int s_begin = split * S_per, S = max(0, min(S_all - s_begin, S_per));
@@ -240,76 +202,66 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
 
     // Weight block b holds rows n0 + 16 b .., with SWI eight gate rows
     // f = n0 + 8 b .. and then the up rows of the same f, with QKV eight rows of
-    // the first half of a head and then their rotary partners; lane l loads row
-    // l % 16, k chunk l / 16 (rows past the end read the last one: never
-    // stored).  The lane keeps the largest magnitude of what it loads.
-    const uint16_t *wsrc[WPW];
-    uint32_t wmax[WPW];
-    float wscale[WPW], winv[WPW];
+    // the first half of a head and then their rotary partners; block NBW + c term
+    // c / (BM / 16) of activation rows m0 + 16 (c % (BM / 16)) ...  Lane l loads
+    // row l % 16, k chunk l / 16 (rows past the end read the last one: never
+    // stored; where the blocks do not come out even, waves share the last one).
+    const uint16_t *src[PW];
 #pragma unroll
-    for (int i = 0; i < WPW; ++i) {
-        const int b = min(wave + NW * i, NBW - 1);
-        int row;
-        if constexpr (SWI)
-            row = (col < 8 ? 0 : F) + min(n0 + 8 * b + (col & 7), F - 1);
-        else if constexpr (QKV)
-            row = qkv_row(min(n0 / 16 + b, N / 16 - 1), col, a.rope.head_dim);
-        else
-            row = min(n0 + 16 * b + col, N - 1);
-        wsrc[i] = a.W + (int64_t)row * K;
-        wmax[i] = 0;
-        wscale[i] = WSCALE;
-        winv[i] = 1.0f / WSCALE;
-    }
-    const uint16_t *asrc[APW];
-#pragma unroll
-    for (int i = 0; i < APW; ++i) {
-        const int c = min(wave + NW * i, NBA - 1), t = c / (BM / 16), rg = c % (BM / 16);
-        asrc[i] = a.A + t * a.a_term + (int64_t)min(m0 + 16 * rg + col, M - 1) * a.lda + 8 * grp;
+    for (int i = 0; i < PW; ++i) {
+        const int b = min(wave + NW * i, NB - 1);
+        if (b < NBW) {
+            int row;
+            if constexpr (SWI)
+                row = (col < 8 ? 0 : F) + min(n0 + 8 * b + (col & 7), F - 1);
+            else if constexpr (QKV)
+                row = qkv_row(min(n0 / 16 + b, N / 16 - 1), col, a.rope.head_dim);
+            else
+                row = min(n0 + 16 * b + col, N - 1);
+            src[i] = a.W + (int64_t)row * K + 8 * grp;
+        } else {
+            const int c = b - NBW, t = c / (BM / 16), rg = c % (BM / 16);
+            src[i] = a.A + t * a.a_term + (int64_t)min(m0 + 16 * rg + col, M - 1) * K + 8 * grp;
+        }
     }
     // stages past the end load the last one again (into buffers no one reads),
     // so every wave has the same number of loads in flight
-    auto aload = [&](int stage) {
-        uint16_t *dst = la + (stage % (P + 1)) * NBA * 512;
+    auto issue = [&](int stage, int buf) {
         const int k0 = (s_begin + min(stage, S - 1)) * 32;
+        uint16_t *dst = lds + buf * NB * 512;
+        if (k0 + 32 <= K) {
 #pragma unroll
-        for (int i = 0; i < APW; ++i)
-            load_to_lds16(asrc[i] + k0, dst + min(wave + NW * i, NBA - 1) * 512);
-    };
-    auto wload = [&](int stage) {
-        uint16_t *dst = lr + (stage % P) * WPW * NW * 512;
-        const int k = (s_begin + min(stage, S - 1)) * 32 + 8 * grp;
+            for (int i = 0; i < PW; ++i)
+                load_to_lds16(src[i] + k0, dst + min(wave + NW * i, NB - 1) * 512);
+        } else {  // zeros past K
 #pragma unroll
-        for (int i = 0; i < WPW; ++i)
-            load_to_lds16(wsrc[i] + min(k, K - 8), dst + (wave + NW * i) * 512);
-    };
-    // this wave's weights of a stage: zero past K, largest magnitude, float16
-    auto wconvert = [&](int stage) {
-        const uint16_t *src = lr + (stage % P) * WPW * NW * 512;
-        uint16_t *dst = lw + (stage & 1) * NBW * 512;
-        const bool ok = (s_begin + stage) * 32 + 8 * grp < K;
-#pragma unroll
-        for (int i = 0; i < WPW; ++i) {
-            if (NBW % NW != 0 && wave + NW * i >= NBW)  // uniform over the wave
-                break;
-            const int o = (wave + NW * i) * 512 + lane * 8;
-            const u32x4_t w = *reinterpret_cast<const u32x4_t *>(src + o);
-            u32x4_t h;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t v = ok ? w[j] : 0u;
-                wmax[i] = pk_max_u16(wmax[i], v & 0x7fff7fffu);
-                h[j] = __builtin_bit_cast(
-                    uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(v << 16) * wscale[i],
-                                                         __uint_as_float(v & 0xffff0000u) * wscale[i]));
-            }
-            *reinterpret_cast<u32x4_t *>(dst + o) = h;
+            for (int i = 0; i < PW; ++i)
+                load_to_lds16(k0 + 8 * grp < K ? src[i] + k0 : a.zero, dst + min(wave + NW * i, NB - 1) * 512);
         }
     };
 
     f32x4_t acc[NT][MT];
-    auto fread = [&](int stage, u32x4_t(&wf)[NT], u32x4_t(&af)[MT][T]) {
-        const uint16_t *ws = lw + (stage & 1) * NBW * 512, *as = la + (stage % (P + 1)) * NBA * 512;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+            acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    if (S > 0) {
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            issue(p, p);
+    }
+    for (int s = 0, buf = 0; s < S; ++s) {
+        // This wave's blocks of stage s have landed: at most the loads issued
+        // after them are in flight.  Then everyone's have, and every read of
+        // stage s - 1, whose buffer the next loads fill, has returned.
+        __builtin_amdgcn_s_waitcnt(wait_vmcnt((P - 1) * PW));
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (P > 1 || s + 1 < S)
+            issue(s + P, buf == 0 ? P : buf - 1);
+        const uint16_t *ws = lds + buf * NB * 512, *as = ws + NBW * 512;
+        buf = buf == P ? 0 : buf + 1;
+        u32x4_t wf[NT], af[MT][T];
 #pragma unroll
         for (int i = 0; i < NT; ++i)
             wf[i] = *reinterpret_cast<const u32x4_t *>(&ws[(wn * NT + i) * 512 + lane * 8]);
@@ -318,147 +270,29 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
 #pragma unroll
             for (int t = 0; t < T; ++t)
                 af[j][t] = *reinterpret_cast<const u32x4_t *>(&as[(t * (BM / 16) + wm * MT + j) * 512 + lane * 8]);
-    };
-    auto multiply = [&](const u32x4_t(&wf)[NT], const u32x4_t(&af)[MT][T]) {
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
             for (int i = 0; i < NT; ++i)
 #pragma unroll
                 for (int j = 0; j < MT; ++j)
-                    acc[i][j] = mfma16h(wf[i], af[j][t], acc[i][j]);
-    };
-
-    for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int j = 0; j < MT; ++j)
-                acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        if (S > 0) {
-            wload(0);
-            __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
-            wconvert(0);
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                aload(p);
-                wload(p + 1);
-            }
-            for (int s = 0; s < S; ++s) {
-                // This wave's activations of stage s and weights of stage s + 1
-                // have landed: at most the loads issued after them are in
-                // flight.  Then everyone's activations have, and the float16
-                // weights are there; every read of stage s - 1 has returned.
-                __builtin_amdgcn_s_waitcnt(wait_vmcnt((P - 1) * (APW + WPW)));
-                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                aload(s + P);
-                u32x4_t wf[NT], af[MT][T];
-                fread(s, wf, af);
-                wconvert(s + 1);
-                wload(s + 1 + P);  // into the block just converted
-                multiply(wf, af);
-            }
-        }
-        __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
-        __syncthreads();  // every wave is done with the stage buffers
-        if (pass)
-            break;
-        // weight rows outside the window of WSCALE: again with their own scales
-        uint32_t *flag = ymax + BM;
-        if (tid == 0)
-            *flag = 0;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < WPW; ++i) {
-            uint32_t m = max(wmax[i] & 0xffffu, wmax[i] >> 16);
-            m = max(m, (uint32_t)__shfl_xor((int)m, 16, 64));
-            m = max(m, (uint32_t)__shfl_xor((int)m, 32, 64));
-            wmax[i] = m;
-            if (!wide_ok(m))
-                *flag = 1;
-        }
-        __syncthreads();
-        const bool again = *flag;
-        __syncthreads();
-        if (!again)
-            break;
-#pragma unroll
-        for (int i = 0; i < WPW; ++i)
-            wscale[i] = row_scale(__uint_as_float(wmax[i] << 16), &winv[i]);
+                    acc[i][j] = mfma16(wf[i], af[j][t], acc[i][j]);
     }
-#pragma unroll
-    for (int i = 0; i < WPW; ++i)
-        if (grp == 0 && wave + NW * i < NBW)
-            wsc[(wave + NW * i) * 16 + col] = winv[i];
-    if constexpr (SWI)
-        for (int i = tid; i < BM; i += 64 * NW)
-            ymax[i] = 0;
-    __syncthreads();
+    __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));  // no load into LDS outlives the work-group
 
-    // lane holds (C 2^..)^T[n0 + wn WN + 16 i + 4 grp + v][m0 + wm WM + 16 j + col]
+    // lane holds C^T[n0 + wn WN + 16 i + 4 grp + v][m0 + wm WM + 16 j + col]
     // (EPI_PARTIAL: of the split's partial sum, part[split][m][n])
-    float rs[MT];
-#pragma unroll
-    for (int j = 0; j < MT; ++j)
-        rs[j] = a.rs[min(m0 + wm * WM + 16 * j + col, M - 1)];
-    if constexpr (SWI) {
-        // Block rows 0-7 are gate, 8-15 up: lanes 0-31 hold gate, lanes 32-63
-        // up of the same eight f.  Swapping the lane halves of two tiles
-        // leaves gate and up of the first tile in lanes 0-31 and of the
-        // second in lanes 32-63.
-        float mx[MT];
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-            mx[j] = 0.0f;
+    if constexpr (SWI || QKV) {
+        // Block rows 0-7 and 8-15 are a pair's two rows (gate and up; a rotary
+        // pair): lanes 0-31 hold the first, lanes 32-63 the second of the same
+        // eight pairs.  Swapping the lane halves of two tiles leaves both rows
+        // of the first tile's pairs in lanes 0-31 and of the second's in lanes
+        // 32-63.
 #pragma unroll
         for (int i = 0; i < NT; i += 2) {
             const int i2 = i + 1 < NT ? i + 1 : i;
-            const int ti = lane < 32 ? i : i2;
-            const int fl = wn * NT * 8 + 8 * ti + 4 * (grp & 1), f = n0 + fl;
+            const int bl = wn * NT + (lane < 32 ? i : i2);
             const bool own = lane < 32 || i2 != i;
-            f32x4_t sg, su;
-            const int rb = (wn * NT + ti) * 16 + 4 * (grp & 1);
-            sg = *reinterpret_cast<const f32x4_t *>(&wsc[rb]);
-            su = *reinterpret_cast<const f32x4_t *>(&wsc[rb + 8]);
-#pragma unroll
-            for (int j = 0; j < MT; ++j) {
-                const int m = m0 + wm * WM + 16 * j + col;
-                f32x4_t y;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][j][v]),
-                                                                    __float_as_uint(acc[i2][j][v]), false, false);
-                    const float g = __uint_as_float(r[0]) * (rs[j] * sg[v]);
-                    const float up = __uint_as_float(r[1]) * (rs[j] * su[v]);
-                    y[v] = g / (1.0f + expf(-g)) * up;
-                }
-                if (m >= M || f >= F || !own)
-                    continue;
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    mx[j] = fmaxf(mx[j], fabsf(y[v]));
-                *reinterpret_cast<f32x4_t *>(a.C + (int64_t)m * F + f) = y;  // F % 8 == 0
-            }
-        }
-        // the tile's largest |y| of every row into slot tn of ymax
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-            atomicMax(&ymax[wm * WM + 16 * j + col], __float_as_uint(mx[j]));
-        __syncthreads();
-        for (int i = tid; i < BM; i += 64 * NW)
-            if (m0 + i < M)
-                a.amax[(int64_t)(m0 + i) * a.amax_ld + tn] = __uint_as_float(ymax[i]);
-        return;
-    }
-    if constexpr (QKV) {
-        // the same swap leaves a row's element p and its partner p + half
-#pragma unroll
-        for (int i = 0; i < NT; i += 2) {
-            const int i2 = i + 1 < NT ? i + 1 : i, ti = lane < 32 ? i : i2;
-            const bool own = lane < 32 || i2 != i;
-            const int bl = wn * NT + ti, rb = bl * 16 + 4 * (grp & 1);
-            const f32x4_t s0 = *reinterpret_cast<const f32x4_t *>(&wsc[rb]);
-            const f32x4_t s1 = *reinterpret_cast<const f32x4_t *>(&wsc[rb + 8]);
 #pragma unroll
             for (int j = 0; j < MT; ++j) {
                 const int m = m0 + wm * WM + 16 * j + col;
@@ -467,35 +301,44 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
                 for (int v = 0; v < 4; ++v) {
                     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][j][v]),
                                                                     __float_as_uint(acc[i2][j][v]), false, false);
-                    y0[v] = __uint_as_float(r[0]) * (rs[j] * s0[v]);
-                    y1[v] = __uint_as_float(r[1]) * (rs[j] * s1[v]);
+                    y0[v] = __uint_as_float(r[0]);
+                    y1[v] = __uint_as_float(r[1]);
                 }
-                if (m < M && n0 + 16 * bl < N && own)
+                if (m >= M || !own)
+                    continue;
+                if constexpr (SWI) {
+                    const int f = n0 + 8 * bl + 4 * (grp & 1);
+                    if (f >= F)  // F % 8 == 0
+                        continue;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        y0[v] = y0[v] / (1.0f + expf(-y0[v])) * y1[v];
+                    store_terms4(a.out, m, f, F, y0);
+                } else if (n0 + 16 * bl < N) {
                     store_qkv4(a.rope, n0 / 16 + bl, 4 * (grp & 1), m, y0, y1, a.C, a.ldc);
+                }
             }
         }
-        return;
-    }
-    float *C = EPI == EPI_PARTIAL ? a.part + (int64_t)split * M * a.ldc : a.C;
-    const bool vec = (a.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
+    } else {
+        float *C = EPI == EPI_PARTIAL ? a.part + (int64_t)split * M * a.ldc : a.C;
+        const bool vec = (a.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-        const int nl = wn * WN + 16 * i + 4 * grp, n = n0 + nl;
-        const f32x4_t sw = *reinterpret_cast<const f32x4_t *>(&wsc[nl]);
+        for (int i = 0; i < NT; ++i) {
+            const int n = n0 + wn * WN + 16 * i + 4 * grp;
 #pragma unroll
-        for (int j = 0; j < MT; ++j) {
-            const int m = m0 + wm * WM + 16 * j + col;
-            if (m >= M || n >= N)
-                continue;
-            f32x4_t v = acc[i][j] * (sw * rs[j]);
-            float *c = C + (int64_t)m * a.ldc + n;
-            if (vec && n + 3 < N) {
-                *reinterpret_cast<f32x4_t *>(c) = v;
-            } else {
+            for (int j = 0; j < MT; ++j) {
+                const int m = m0 + wm * WM + 16 * j + col;
+                if (m >= M || n >= N)
+                    continue;
+                float *c = C + (int64_t)m * a.ldc + n;
+                if (vec && n + 3 < N) {
+                    *reinterpret_cast<f32x4_t *>(c) = acc[i][j];
+                } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (n + u < N)
-                        c[u] = v[u];
+                    for (int u = 0; u < 4; ++u)
+                        if (n + u < N)
+                            c[u] = acc[i][j][u];
+                }
             }
         }
     }
@@ -508,10 +351,10 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
 // k-step and meet in LDS at the end, so nothing is shared and no wave waits
 // for another inside the loop (the tile kernel above spends 0.4 us per 32-k
 // stage on its barrier chain at these sizes, whatever the tile).  A wave loads
-// its weights coalesced (eight lanes per 128-byte row slice), transposes them
-// through a private LDS tile whose 16-byte chunks are XOR-swizzled by row,
-// and turns the fragments into float16.  The activation terms come in fragment
-// order (thin_off), each operand one contiguous 1 KB load.
+// its weights coalesced (eight lanes per 128-byte row slice) and transposes
+// them through a private LDS tile whose 16-byte chunks are XOR-swizzled by row.
+// The activation terms come in fragment order (thin_off), each operand one
+// contiguous 1 KB load.
 
 template <int EPI>
 __device__ __forceinline__ int thin_row(int t, int i, const PfThinArgs &a) {
@@ -527,15 +370,12 @@ __device__ __forceinline__ int thin_row(int t, int i, const PfThinArgs &a) {
 
 template <int EPI, int MB, int NW, int TN>
 __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
-    constexpr int T = PF_TERMS;
-    constexpr int WL = TN * 16 * 64;          // halves of a wave's staging tile
+    constexpr int T = X_TERMS;
+    constexpr int WL = TN * 16 * 64;          // elements of a wave's staging tile
     constexpr int RC = MB * 16 + 1;           // pitch of the reduction rows
     constexpr size_t SMEM_W = (size_t)NW * WL * 2, SMEM_R = (size_t)NW * 16 * RC * 4;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_W > SMEM_R ? SMEM_W : SMEM_R];
-    __shared__ uint32_t rmax[TN * 16];
-    __shared__ float wsc[TN * 16];
     __shared__ float fin[EPI == EPI_QKV || EPI == EPI_SWIGLU ? 16 * RC : 1];
-    __shared__ uint32_t ymax[EPI == EPI_SWIGLU ? MB * 16 : 1];
     const int S = EPI == EPI_PARTIAL ? a.splits : 1;
     const int grp = blockIdx.x / S, sp = blockIdx.x - grp * S;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -556,8 +396,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
     const int ks0 = (int)(((int64_t)KS_all * sp) / S), ks1 = (int)(((int64_t)KS_all * (sp + 1)) / S);
 
     f32x4_t acc[TN][MB];
-    float wscale[TN];
-    uint32_t wmax[TN];
     u32x4_t wv[TN][2], xv[2][MB][T];
     // (a uniform base and a 32-bit offset per lane)
     auto load_w = [&](int q) {
@@ -580,100 +418,55 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
     };
 #pragma unroll
     for (int j = 0; j < TN; ++j)
-        wscale[j] = WSCALE;
-    for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            wmax[j] = 0;
-#pragma unroll
-            for (int b = 0; b < MB; ++b)
-                acc[j][b] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-        int q = ks0 + wave;
-        if (q < ks1) {
-            load_w(q);
-            load_x(q, 0);
-            load_x(q, 1);
-        }
-        // One k-step, requesting the next one's operands if there is one.  The
-        // last is peeled: where the loads are under a branch, the compiler
-        // waits at the join for what may have been issued, that is for
-        // everything in flight (13B, 4 layers, 33 rows: 915 -> 895 us a
-        // forward; 64 rows 1063 -> 1017).
-        auto kstep = [&](int q, auto more) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int ii = 0; ii < 2; ++ii) {
-                    const int row = 8 * ii + lrow;
-                    *reinterpret_cast<u32x4_t *>(wl + j * 1024 + row * 64 + ((lch ^ (row & 7)) << 3)) = wv[j][ii];
-                }
-            if constexpr (decltype(more)::value)
-                load_w(q + NW);
-            // the staging tile is private to this wave, whose LDS accesses run
-            // in program order; the fences only keep the compiler from
-            // reordering them
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(wl + j * 1024 + r16 * 64 +
-                                                                         (((4 * i + kg) ^ (r16 & 7)) << 3));
-                    u32x4_t wf;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        wmax[j] = pk_max_u16(wmax[j], v[u] & 0x7fff7fffu);
-                        wf[u] = __builtin_bit_cast(
-                            uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(v[u] << 16) * wscale[j],
-                                                                 __uint_as_float(v[u] & 0xffff0000u) * wscale[j]));
-                    }
-#pragma unroll
-                    for (int t = 0; t < T; ++t)
-#pragma unroll
-                        for (int b = 0; b < MB; ++b)
-                            acc[j][b] = mfma16h(wf, xv[i][b][t], acc[j][b]);
-                }
-                // one set of registers per half step: its next activations
-                // (cache hits) are requested once its MFMAs have read these
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (decltype(more)::value)
-                    load_x(q + NW, i);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        };
-        for (; q + NW < ks1; q += NW)
-            kstep(q, std::true_type{});
-        if (q < ks1)
-            kstep(q, std::false_type{});
-        if (pass)
-            break;
-        // largest magnitude of every weight row over the waves
-        if (tid < TN * 16)
-            rmax[tid] = 0;
-        __syncthreads();
+        for (int b = 0; b < MB; ++b)
+            acc[j][b] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    int q = ks0 + wave;
+    if (q < ks1) {
+        load_w(q);
+        load_x(q, 0);
+        load_x(q, 1);
+    }
+    // One k-step, requesting the next one's operands if there is one.  The
+    // last is peeled: where the loads are under a branch, the compiler waits at
+    // the join for what may have been issued, that is for everything in flight.
+    auto kstep = [&](int q, auto more) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-            atomicMax(&rmax[16 * j + r16], max(wmax[j] & 0xffffu, wmax[j] >> 16));
-        __syncthreads();
-        const bool again = __syncthreads_or(tid < TN * 16 && !wide_ok(rmax[tid]));
-        if (tid < TN * 16) {
-            float inv = 1.0f / WSCALE;
-            if (again)
-                (void)row_scale(__uint_as_float(rmax[tid] << 16), &inv);
-            wsc[tid] = inv;
-        }
-        if (!again)
-            break;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            float inv;
-            wscale[j] = row_scale(__uint_as_float(rmax[16 * j + r16] << 16), &inv);
+            for (int ii = 0; ii < 2; ++ii) {
+                const int row = 8 * ii + lrow;
+                *reinterpret_cast<u32x4_t *>(wl + j * 1024 + row * 64 + ((lch ^ (row & 7)) << 3)) = wv[j][ii];
+            }
+        if constexpr (decltype(more)::value)
+            load_w(q + NW);
+        // the staging tile is private to this wave, whose LDS accesses run in
+        // program order; the fences only keep the compiler from reordering them
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const u32x4_t wf =
+                    *reinterpret_cast<const u32x4_t *>(wl + j * 1024 + r16 * 64 + (((4 * i + kg) ^ (r16 & 7)) << 3));
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int b = 0; b < MB; ++b)
+                        acc[j][b] = mfma16(wf, xv[i][b][t], acc[j][b]);
+            }
+            // one set of registers per half step: its next activations (cache
+            // hits) are requested once its MFMAs have read these
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (decltype(more)::value)
+                load_x(q + NW, i);
         }
-    }
-    if constexpr (EPI == EPI_SWIGLU)
-        if (tid < MB * 16)
-            ymax[tid] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    for (; q + NW < ks1; q += NW)
+        kstep(q, std::true_type{});
+    if (q < ks1)
+        kstep(q, std::false_type{});
 
     // acc: lane holds rows 4 kg + v of tile j, activation row 16 b + r16.
     // Tile by tile the waves' sums meet in LDS and are added in wave order.
@@ -697,7 +490,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
 #pragma unroll
             for (int w = 1; w < NW; ++w)
                 v += red[(w * 16 + ni) * RC + m];
-            v = v * wsc[16 * j + ni] * a.rs[m];
             if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
                 fin[ni * RC + m] = v;
             } else {
@@ -707,15 +499,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
                     C[(int64_t)m * a.ldc + n] = v;
             }
         }
-        if constexpr (EPI == EPI_SWIGLU) {
-            __syncthreads();
-            for (int o = tid; o < 8 * M; o += 64 * NW) {
-                const int i = o & 7, m = o >> 3, f = t * 8 + i;
-                const float g = fin[i * RC + m], y = g / (1.0f + expf(-g)) * fin[(i + 8) * RC + m];
-                a.C[(int64_t)m * a.ldc + f] = y;  // F is a multiple of 8
-                atomicMax(&ymax[m], __float_as_uint(fabsf(y)));
-            }
-        } else if constexpr (EPI == EPI_QKV) {
+        if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
             __syncthreads();
             for (int o = tid; o < 2 * M; o += 64 * NW) {
                 const int i = 4 * (o & 1), m = o >> 1;
@@ -725,14 +509,16 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
                     y0[v] = fin[(i + v) * RC + m];
                     y1[v] = fin[(i + v + 8) * RC + m];
                 }
-                store_qkv4(a.rope, t, i, m, y0, y1, a.C, a.ldc);
+                if constexpr (EPI == EPI_QKV) {
+                    store_qkv4(a.rope, t, i, m, y0, y1, a.C, a.ldc);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        y0[v] = y0[v] / (1.0f + expf(-y0[v])) * y1[v];
+                    store_terms4(a.out, m, t * 8 + i, a.N >> 1, y0);  // F is a multiple of 8
+                }
             }
         }
-    }
-    if constexpr (EPI == EPI_SWIGLU) {
-        __syncthreads();
-        if (tid < M)
-            a.amax[(int64_t)tid * a.amax_ld + grp] = __uint_as_float(ymax[tid]);
     }
 }
 
@@ -749,7 +535,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pf_thin(PfThinArgs a) {
 constexpr int PA_KB = 32;
 
 template <int DH>
-__global__ __launch_bounds__(256) void k_pf_attn(PfAttnArgs a) {
+__global__ __launch_bounds__(256) void k_pf_attn(PfAttnArgs a, PfTerms out) {
     constexpr int T = X_TERMS;
     constexpr int ES = DH / 32;     // 32-wide slices of head_dim (score MFMAs)
     constexpr int ET = DH / 16;     // 16-wide tiles of head_dim (value MFMAs)
@@ -890,22 +676,12 @@ __global__ __launch_bounds__(256) void k_pf_attn(PfAttnArgs a) {
     }
 
     // lane holds O^T[16 et + 4 grp + v][query col]
+    if (!qok)
+        return;
     const float inv = 1.0f / l_run;
-    float mx = 0.0f;
 #pragma unroll
-    for (int et = 0; et < ET; ++et) {
-        oacc[et] *= inv;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            mx = fmaxf(mx, fabsf(oacc[et][v]));
-        if (qok)
-            *reinterpret_cast<f32x4_t *>(a.out + (int64_t)rq * a.ldo + (int64_t)head * DH + 16 * et + 4 * grp) =
-                oacc[et];
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    if (qok && grp == 0)
-        a.amax[(int64_t)rq * a.amax_ld + head] = mx;
+    for (int et = 0; et < ET; ++et)
+        store_terms4(out, rq, head * DH + 16 * et + 4 * grp, a.n_heads * DH, oacc[et] * inv);
 }
 
 // ---------------------------------------------------------------------------
@@ -935,25 +711,6 @@ __global__ __launch_bounds__(256) void k_pf_embed(const uint16_t *E, int d, cons
 // there are few rows, smaller work-groups where rows fill the chip.
 constexpr int PF_FEW_ROWS = 256;
 
-// The terms of row m, x[0..K) (K a multiple of 8; x(k) gives elements k .. k + 7
-// times the row's scale): row-major, zero up to the next multiple of 32
-// (blocks 0), or in fragment order.
-template <int NT, typename F>
-__device__ __forceinline__ void store_terms(int m, int K, uint16_t *out, int64_t out_term, int blocks, F x) {
-    const int ldk = pf_pitch(K);
-    for (int k = 8 * threadIdx.x; k < ldk; k += 8 * NT) {
-        u32x4_t h = {0u, 0u, 0u, 0u}, l = h;
-        if (k < K) {
-            float u[8];
-            x(k, u);
-            split_f16x8(u, h, l);
-        }
-        uint16_t *o = out + (blocks ? thin_off(0, m, k, blocks) : (int64_t)m * ldk + k);
-        *reinterpret_cast<u32x4_t *>(o) = h;
-        *reinterpret_cast<u32x4_t *>(o + (blocks ? (int64_t)blocks << 9 : out_term)) = l;
-    }
-}
-
 __device__ __forceinline__ void load8f(const float *p, float (&x)[8]) {
     const f32x4_t a = reinterpret_cast<const f32x4_t *>(p)[0], b = reinterpret_cast<const f32x4_t *>(p)[1];
 #pragma unroll
@@ -963,22 +720,21 @@ __device__ __forceinline__ void load8f(const float *p, float (&x)[8]) {
     }
 }
 
-// g * h / rms(h) of every row as float16 terms, with the row's scale.  With
-// splits > 0 the partials of a split residual update are added into h first,
-// in split order: h[m] += part[0][m] + part[1][m] + ...
+// g * h / rms(h) of every row as terms.  With splits > 0 the partials of a
+// residual update are added into h first, in split order:
+// h[m] += part[0][m] + part[1][m] + ...
 template <int NT>
 __global__ __launch_bounds__(NT) void k_pf_norm_split(float *h, const float *part, int splits, int64_t stride, int K,
-                                                       const uint16_t *gain, float eps, uint16_t *out, int64_t out_term,
-                                                       int blocks, float *rs) {
-    __shared__ float red[2][NT / 64];
+                                                       const uint16_t *gain, float eps, PfTerms out) {
+    __shared__ float red[NT / 64];
     const int m = blockIdx.x, tid = threadIdx.x;
     float *x = h + (int64_t)m * K;
     const float *p = part + (int64_t)m * K;
-    float ss = 0.0f, mx = 0.0f;
+    float ss = 0.0f;
     // 16-byte loads (K is a multiple of 8): with 4-byte loads this pass over
     // the row and three partial planes took 40 us per 13B call
     for (int k = 8 * tid; k < K; k += 8 * NT) {
-        float v[8], g[8];
+        float v[8];
         load8f(x + k, v);
         if (splits) {
             float w[8];
@@ -996,71 +752,29 @@ __global__ __launch_bounds__(NT) void k_pf_norm_split(float *h, const float *par
             reinterpret_cast<f32x4_t *>(x + k)[0] = f32x4_t{v[0], v[1], v[2], v[3]};
             reinterpret_cast<f32x4_t *>(x + k)[1] = f32x4_t{v[4], v[5], v[6], v[7]};
         }
-        load8bf(gain + k, g);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < 8; ++j)
             ss = fmaf(v[j], v[j], ss);
-            mx = fmaxf(mx, fabsf(g[j] * v[j]));
-        }
     }
     ss = wave_sum_all(ss);
-    mx = wave_max_all(mx);
-    if ((tid & 63) == 0) {
-        red[0][tid >> 6] = ss;
-        red[1][tid >> 6] = mx;
-    }
+    if ((tid & 63) == 0)
+        red[tid >> 6] = ss;
     __syncthreads();
-    ss = mx = 0.0f;
+    ss = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        ss += red[0][w];
-        mx = fmaxf(mx, red[1][w]);
-    }
+    for (int w = 0; w < NT / 64; ++w)
+        ss += red[w];
     const float inv = 1.0f / sqrtf(ss / (float)K + eps);
-    const float amax = mx * inv;
-    float rinv;
-    const float sc = row_scale(amax, &rinv);
-    if (tid == 0)
-        rs[m] = rinv;
     // (re-reads what this thread wrote or read above)
-    store_terms<NT>(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
+    for (int k = 8 * tid; k < K; k += 8 * NT) {
         float v[8], g[8];
         load8f(x + k, v);
         load8bf(gain + k, g);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            u[j] = g[j] * (v[j] * inv) * sc;
-    });
-}
-
-// The terms of every row of x [M][K] (the attention output or the MLP
-// activation), whose largest magnitude is the largest of its amax slots.
-template <int NT>
-__global__ __launch_bounds__(NT) void k_pf_split(const float *x, int K, const float *amax, int slots, int amax_ld,
-                                                  uint16_t *out, int64_t out_term, int blocks, float *rs) {
-    __shared__ float red[NT / 64];
-    const int m = blockIdx.x, tid = threadIdx.x;
-    float mx = 0.0f;
-    for (int i = tid; i < slots; i += NT)
-        mx = fmaxf(mx, amax[(int64_t)m * amax_ld + i]);
-    mx = wave_max_all(mx);
-    if ((tid & 63) == 0)
-        red[tid >> 6] = mx;
-    __syncthreads();
-    mx = 0.0f;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w)
-        mx = fmaxf(mx, red[w]);
-    float rinv;
-    const float sc = row_scale(mx, &rinv);
-    if (tid == 0)
-        rs[m] = rinv;
-    store_terms<NT>(m, K, out, out_term, blocks, [&](int k, float(&u)[8]) {
-        load8f(x + (int64_t)m * K + k, u);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            u[j] *= sc;
-    });
+            v[j] = g[j] * (v[j] * inv);
+        store_terms8(out, m, k, K, v);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1286,15 +1000,11 @@ __global__ __launch_bounds__(256, 2) void k_pf_attn128(PfAttnArgs a) {
 }
 
 // The chunks of k_pf_attn128 combined in order and normalised, one work-group
-// per row, as float16 terms with the row's scale.  LDS: the row (hd floats) and
-// the chunks' weights [H][chunks].
+// per row, as terms.  LDS: the chunks' weights [H][chunks].
 template <int NT>
-__global__ __launch_bounds__(NT) void k_pf_attn_terms(PfAttnArgs a, uint16_t *out, int64_t out_term, int blocks,
-                                                       float *rs) {
-    extern __shared__ __attribute__((aligned(16))) float sm[];
-    __shared__ float red[NT / 64];
+__global__ __launch_bounds__(NT) void k_pf_attn_terms(PfAttnArgs a, PfTerms out) {
+    extern __shared__ __attribute__((aligned(16))) float wt[];
     const int m = blockIdx.x, tid = threadIdx.x, H = a.n_heads, hd = H * 128;
-    float *row = sm, *wt = sm + hd;
     // chunks some row of this row's work-group saw keys of
     const int kend = a.start + min((m / PA2_ROWS + 1) * PA2_ROWS, a.M);
     const int nc = min(a.chunks, (kend + a.chunk_keys - 1) / a.chunk_keys);
@@ -1313,35 +1023,18 @@ __global__ __launch_bounds__(NT) void k_pf_attn_terms(PfAttnArgs a, uint16_t *ou
             wt[h * nc + c] *= inv;
     }
     __syncthreads();
-    float mx = 0.0f;
-    for (int k = 4 * tid; k < hd; k += 4 * NT) {
+    for (int k = 8 * tid; k < hd; k += 8 * NT) {
         const float *w = wt + (k >> 7) * nc, *p = a.out + (int64_t)m * a.ldo + k;
-        f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int c = 0; c < nc; ++c)
-            v += w[c] * *reinterpret_cast<const f32x4_t *>(p + (int64_t)c * a.M * a.ldo);
-        *reinterpret_cast<f32x4_t *>(row + k) = v;
+        float v[8] = {};
+        for (int c = 0; c < nc; ++c) {
+            float x[8];
+            load8f(p + (int64_t)c * a.M * a.ldo, x);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            mx = fmaxf(mx, fabsf(v[j]));
+            for (int j = 0; j < 8; ++j)
+                v[j] += w[c] * x[j];
+        }
+        store_terms8(out, m, k, hd, v);
     }
-    mx = wave_max_all(mx);
-    if ((tid & 63) == 0)
-        red[tid >> 6] = mx;
-    __syncthreads();
-    mx = 0.0f;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w)
-        mx = fmaxf(mx, red[w]);
-    float rinv;
-    const float sc = row_scale(mx, &rinv);
-    if (tid == 0)
-        rs[m] = rinv;
-    store_terms<NT>(m, hd, out, out_term, blocks, [&](int k, float(&u)[8]) {
-        load8f(row + k, u);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            u[j] *= sc;
-    });
 }
 
 }  // namespace
@@ -1356,17 +1049,8 @@ hipError_t launch_pf_norm_split(float *h, const float *part, int splits, int K, 
     if (K % 8 || (t.blocks && K % 32) || splits < 0 || splits > PF_MAX_SPLITS)
         return hipErrorInvalidValue;
     auto kern = M <= PF_FEW_ROWS ? k_pf_norm_split<1024> : k_pf_norm_split<256>;
-    hipLaunchKernelGGL(kern, dim3(M), dim3(M <= PF_FEW_ROWS ? 1024 : 256), 0, s, h, part, splits, (int64_t)M * K, K, gain, eps, t.x,
-                       t.term, t.blocks, t.rs);
-    return hipGetLastError();
-}
-
-hipError_t launch_pf_split(const float *x, int K, int M, const float *amax, int slots, int amax_ld, const PfTerms &t,
-                           hipStream_t s) {
-    if (K % 8 || (t.blocks && K % 32))
-        return hipErrorInvalidValue;
-    auto kern = M <= PF_FEW_ROWS ? k_pf_split<1024> : k_pf_split<256>;
-    hipLaunchKernelGGL(kern, dim3(M), dim3(M <= PF_FEW_ROWS ? 1024 : 256), 0, s, x, K, amax, slots, amax_ld, t.x, t.term, t.blocks, t.rs);
+    hipLaunchKernelGGL(kern, dim3(M), dim3(M <= PF_FEW_ROWS ? 1024 : 256), 0, s, h, part, splits, (int64_t)M * K, K,
+                       gain, eps, t);
     return hipGetLastError();
 }
 
@@ -1379,7 +1063,7 @@ hipError_t launch_tile(const PfGemmArgs &a, int epi, hipStream_t s) {
     const dim3 grid(8 * ((tiles + 7) / 8)), block(64 * NWN * NWM);
     if (epi == EPI_STORE)
         hipLaunchKernelGGL((k_pf_gemm<EPI_STORE, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
-    else if (epi == EPI_PARTIAL)
+    else if (epi == EPI_RESID)
         hipLaunchKernelGGL((k_pf_gemm<EPI_PARTIAL, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
     else if (epi == EPI_SWIGLU)
         hipLaunchKernelGGL((k_pf_gemm<EPI_SWIGLU, BN, BM, NWN, NWM, P, WPS>), grid, block, 0, s, a);
@@ -1438,78 +1122,93 @@ namespace {
 
 // The tiles of k_pf_gemm: weight rows, activation rows, and the time of one
 // 32-k stage of a work-group (ns, one work-group per CU with the chip full;
-// 13B shapes, random operands).  The larger tiles read fewer operand bytes
-// per product: 256 x 256 multiplies 2.3 times as fast per CU as 128 x 64.
+// 13B and 7B shapes, random operands, weights not in cache).  The larger tiles
+// read fewer operand bytes per product: 256 x 256 multiplies 1.9 times as fast
+// per CU as 128 x 64.  Tiles of 224 save an eighth of the columns and 2 to 4%
+// of the time, as the power limit sets the clock: they are for layers they
+// fill the rounds of better (13B gate/up, 1000 rows: 496 of 512 work-group
+// slots and 752 us, 432 and 770 us with 256).
 struct PfTile {
     int bn, bm, ns;
 };
-constexpr PfTile PF_TILES[] = {{256, 256, 1820}, {256, 128, 1120}, {128, 128, 820}, {128, 64, 550}};
+constexpr PfTile PF_TILES[PF_TILE_COUNT] = {
+    {256, 256, 2500}, {224, 256, 2400}, {256, 128, 1340}, {128, 128, 960}, {128, 64, 600}};
+
+}  // namespace
 
 // The tile and the split of the reduction with the least time by that table:
 // rounds of one work-group per CU, times the stages of a split, plus the
 // writing and reading of the partial sums at 5 TB/s.
-void pick_tile(const PfGemmArgs &a, int epi, int *tile, int *splits) {
-    const int stages = (a.K + 31) / 32;
+int pf_gemm_tile(int M, int N, int K, int epi, int *splits) {
+    const int stages = (K + 31) / 32;
     // partial planes: PF_MAX_SPLITS of them, and in all 4 x PF_ROWS rows
-    const int most = epi == EPI_RESID ? std::min(PF_MAX_SPLITS, PF_PART_ROWS / a.M) : 1;
+    const int most = epi == EPI_RESID ? std::min(PF_MAX_SPLITS, PF_PART_ROWS / M) : 1;
     double best = 0.0;
-    *tile = -1;
-    for (int i = 0; i < 4; ++i) {
+    int tile = -1;
+    for (int i = 0; i < PF_TILE_COUNT; ++i) {
         const PfTile &t = PF_TILES[i];
-        const int bc = epi == EPI_SWIGLU ? t.bn / 2 : t.bn, nc = epi == EPI_SWIGLU ? a.N / 2 : a.N;
-        const int64_t tiles = (int64_t)((nc + bc - 1) / bc) * ((a.M + t.bm - 1) / t.bm);
+        const int bc = epi == EPI_SWIGLU ? t.bn / 2 : t.bn, nc = epi == EPI_SWIGLU ? N / 2 : N;
+        const int64_t tiles = (int64_t)((nc + bc - 1) / bc) * ((M + t.bm - 1) / t.bm);
         for (int s = 1; s <= most && (s == 1 || stages >= 8 * s); ++s) {
             const double rounds = (double)((tiles * s + 255) / 256);
-            const double ns = rounds * ((stages + s - 1) / s) * t.ns + (epi == EPI_RESID ? s * 8.0e-3 / 5 * a.M * a.N : 0.0);
-            if (*tile < 0 || ns < best) {
+            const double ns =
+                rounds * ((stages + s - 1) / s) * t.ns + (epi == EPI_RESID ? s * 8.0e-3 / 5 * M * N : 0.0);
+            if (tile < 0 || ns < best) {
                 best = ns;
-                *tile = i;
+                tile = i;
                 *splits = s;
             }
         }
     }
+    return tile;
 }
 
-}  // namespace
-
-hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out) {
-    if (a.M < 1 || a.N < 1 || a.K < 8 || a.K % 8 || a.lda != pf_pitch(a.K) || a.M > PF_ROWS || !a.rs)
+hipError_t launch_pf_gemm_tile(const PfGemmArgs &a, int epi, int tile, hipStream_t s) {
+    if (a.M < 1 || a.N < 1 || a.K < 8 || a.K % 8 || a.M > PF_ROWS || !a.zero || a.splits < 1 ||
+        a.splits > (epi == EPI_RESID ? PF_MAX_SPLITS : 1) || a.splits * a.M > PF_PART_ROWS)
         return hipErrorInvalidValue;
-    if (epi == EPI_SWIGLU ? (a.N % 16 || !a.amax || !out) : epi == EPI_RESID ? (!a.part || !out)
+    if (epi == EPI_SWIGLU ? (a.N % 16 || !a.out.x || a.out.blocks) : epi == EPI_RESID ? !a.part
         : epi == EPI_QKV ? (a.rope.head_dim % 16 || a.N % 16) : epi != EPI_STORE)
         return hipErrorInvalidValue;
-    PfGemmArgs b = a;
-    int tile = 0;
-    pick_tile(a, epi, &tile, &b.splits);
-    if (epi == EPI_RESID)
-        *out = b.splits;
-    if (epi == EPI_SWIGLU)
-        *out = (a.N + PF_TILES[tile].bn - 1) / PF_TILES[tile].bn;
-    const int e = epi == EPI_RESID ? EPI_PARTIAL : epi;
+    // Waves, and stages in flight: as many as LDS takes for one work-group per
+    // CU, but two of them for 128 x 64 (13B, 1023 rows, QKV: 256 x 128 two
+    // stages ahead 439 us, one and two work-groups per CU 473; 128 x 64 in four
+    // waves 757, in eight 900).
     switch (tile) {
     case 0:
-        // 16 waves of 64 x 64; 8 of 64 x 128 read fewer fragments from LDS and
-        // were faster alone (13B QKV, 1023 rows: 331 against 296 us), not in
-        // the forward (1000 rows over 8000 keys: 7.59 against 7.64 ms)
-        return launch_tile<256, 256, 4, 4, 2, 4>(b, e, s);
+        return launch_tile<256, 256, 4, 4, 1, 4>(a, epi, s);
     case 1:
-        return launch_tile<256, 128, 4, 2, 2, 2>(b, e, s);
+        return launch_tile<224, 256, 2, 8, 1, 4>(a, epi, s);
     case 2:
-        return launch_tile<128, 128, 4, 2, 2, 2>(b, e, s);
+        return launch_tile<256, 128, 4, 2, 2, 2>(a, epi, s);
+    case 3:
+        return launch_tile<128, 128, 4, 2, 2, 2>(a, epi, s);
+    case 4:
+        return launch_tile<128, 64, 2, 2, 3, 2>(a, epi, s);
     default:
-        return launch_tile<128, 64, 4, 2, 3, 2>(b, e, s);
+        return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out) {
+    if (a.M < 1 || a.N < 1 || a.K < 8 || a.M > PF_ROWS || (epi == EPI_RESID && !out))
+        return hipErrorInvalidValue;
+    PfGemmArgs b = a;
+    const int tile = pf_gemm_tile(a.M, a.N, a.K, epi, &b.splits);
+    if (epi == EPI_RESID)
+        *out = b.splits;
+    return launch_pf_gemm_tile(b, epi, tile, s);
 }
 
 bool pf_thin_ok(int M, int64_t N, int K) { return M <= PF_THIN_ROWS && K % 64 == 0 && N * K < ((int64_t)1 << 31); }
 
 hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out) {
     PfThinArgs a = a0;
-    if (a.M < 1 || a.N < 1 || !pf_thin_ok(a.M, a.N, a.K) || !a.rs)
+    if (a.M < 1 || a.N < 1 || !pf_thin_ok(a.M, a.N, a.K))
         return hipErrorInvalidValue;
     a.splits = 1;
     if (epi == EPI_SWIGLU) {
-        if (a.N % 16 || !a.amax || !out)
+        if (a.N % 16 || !a.out.x)
             return hipErrorInvalidValue;
         a.n_tiles = a.N / 16;
     } else if (epi == EPI_QKV) {
@@ -1520,11 +1219,10 @@ hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out
         a.n_tiles = (a.N + 15) / 16;
     }
     // Tiles per work-group: four, or three where that takes an eighth off the
-    // tiles of the busiest CU (us, 33 rows: 7B gate/up, 6 for 8, 57.1 -> 49.1,
-    // QKV, 3 for 4, 33.2 -> 29.4; 70B QKV 54.5 -> 48.3; not 15 for 16, 70B
-    // gate/up 215 and 222: every group loads all activations).  Up to 32 rows
-    // seven where that is one group per CU (13B gate/up, 20 rows: 59.5 -> 53.4;
-    // at 33 rows, without registers for them, 70 -> 79).
+    // tiles of the busiest CU (us, 33 rows: 7B gate/up, 6 for 8, 60.6 -> 51.4,
+    // QKV, 3 for 4, 32.6 -> 30.0; not 13B gate/up, 9 for 8, 75.3 and 91.7).
+    // Up to 32 rows seven where that is one group per CU (13B gate/up, 20 rows:
+    // 67.0 -> 55.2; at 33 rows there are no registers for them).
     int tn = 4;
     if (epi != EPI_RESID) {
         tn = 8 * mfma_busiest(3, a.n_tiles) <= 7 * mfma_busiest(4, a.n_tiles) ? 3 : 4;
@@ -1532,27 +1230,20 @@ hipError_t launch_pf_thin(const PfThinArgs &a0, int epi, hipStream_t s, int *out
             tn = 7;
     }
     const int groups = (a.n_tiles + tn - 1) / tn;
-    if (epi == EPI_SWIGLU)
-        *out = groups;
     if (epi == EPI_RESID) {
         if (!out)
             return hipErrorInvalidValue;
         // output projections: as many splits of the reduction as fill the CUs
-        // with one work-group of eight waves (13B, 33 rows, 80 groups: O 22.3,
-        // 17.9 and 26.5 us with 2, 3 and 4 splits; down 46.4, 35.5 and 51.1)
+        // with one work-group (33 rows: 13B, 80 groups, O 21.2, 17.2 and 21.6 us
+        // with 2, 3 and 4 splits, down 48.1, 38.2 and 49.0; 7B, 64 groups, O 13.5,
+        // 11.7 and 15.4 with 3, 4 and 5)
         a.splits = std::max(1, std::min({PF_MAX_SPLITS, 256 / groups, a.K / 512}));
         *out = a.splits;
         epi = EPI_PARTIAL;
     }
-    // Eight waves where one work-group per CU takes the layer, four where two
-    // fit on many CUs (33 rows: 13B QKV, 240 groups, 41.2 against 43.6 us;
-    // gate/up, 432 groups, 75.0 against 70.9).
-    const bool one = groups * a.splits <= MFMA_CUS;
-    if (tn == 3)
-        return one ? launch_thin_nw<8, 3>(a, epi, s) : launch_thin_nw<4, 3>(a, epi, s);
-    if (tn == 7)
-        return launch_thin_nw<8, 7>(a, epi, s);
-    return one ? launch_thin_nw<8, 4>(a, epi, s) : launch_thin_nw<4, 4>(a, epi, s);
+    // (four waves: eight of them lose up to 5% at the same number of tiles)
+    return tn == 3 ? launch_thin_nw<4, 3>(a, epi, s)
+           : tn == 4 ? launch_thin_nw<4, 4>(a, epi, s) : launch_thin_nw<8, 7>(a, epi, s);
 }
 
 // Chunks of the keys per row block: enough work-groups for PA_UNITS of them,
@@ -1566,7 +1257,7 @@ hipError_t launch_pf_attention(const PfAttnArgs &a0, const PfTerms &t, hipStream
     const int hd = a.n_heads * a.head_dim;
     if (a.head_dim == 128 && hd <= 8192) {
         const int units = ((a.M + PA2_ROWS - 1) / PA2_ROWS) * a.n_heads, keys = a.start + a.M;
-        const int most = std::min({PF_PART_ROWS / a.M, keys / 256, (16384 - hd) / a.n_heads});
+        const int most = std::min({PF_PART_ROWS / a.M, keys / 256, 16384 / a.n_heads});
         a.chunks = std::max(1, std::min(most, (PA_UNITS + units - 1) / units));
         a.chunk_keys = ((keys + a.chunks - 1) / a.chunks + PA2_KB - 1) / PA2_KB * PA2_KB;
         a.chunks = (keys + a.chunk_keys - 1) / a.chunk_keys;
@@ -1575,28 +1266,25 @@ hipError_t launch_pf_attention(const PfAttnArgs &a0, const PfTerms &t, hipStream
         if (e != hipSuccess)
             return e;
         auto kern = a.M <= PF_FEW_ROWS ? k_pf_attn_terms<1024> : k_pf_attn_terms<256>;
-        hipLaunchKernelGGL(kern, dim3(a.M), dim3(a.M <= PF_FEW_ROWS ? 1024 : 256), (size_t)(hd + a.n_heads * a.chunks) * sizeof(float),
-                           s, a, t.x, t.term, t.blocks, t.rs);
+        hipLaunchKernelGGL(kern, dim3(a.M), dim3(a.M <= PF_FEW_ROWS ? 1024 : 256),
+                           (size_t)a.n_heads * a.chunks * sizeof(float), s, a, t);
         return hipGetLastError();
     }
     const dim3 grid(((a.M + 63) / 64) * a.n_heads), block(256);
     switch (a.head_dim) {
     case 32:
-        hipLaunchKernelGGL(k_pf_attn<32>, grid, block, 0, s, a);
+        hipLaunchKernelGGL(k_pf_attn<32>, grid, block, 0, s, a, t);
         break;
     case 64:
-        hipLaunchKernelGGL(k_pf_attn<64>, grid, block, 0, s, a);
+        hipLaunchKernelGGL(k_pf_attn<64>, grid, block, 0, s, a, t);
         break;
     case 128:
-        hipLaunchKernelGGL(k_pf_attn<128>, grid, block, 0, s, a);
+        hipLaunchKernelGGL(k_pf_attn<128>, grid, block, 0, s, a, t);
         break;
     default:
         return hipErrorInvalidValue;
     }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    return launch_pf_split(a.out, hd, a.M, a.amax, a.n_heads, a.amax_ld, t, s);
+    return hipGetLastError();
 }
 
 }  // namespace sdk

@@ -130,16 +130,14 @@ struct sd_model {
     float2 *rope = nullptr;
     int rope_cap = 0;
     // large-M forward (bfloat16 models), PF_ROWS rows each: residual stream,
-    // MLP activation, rotated queries, partial sums of residual updates (and
-    // the attention's chunks), and the GEMM inputs as PF_TERMS terms with their rows' scales
-    // and the maxima those come from
+    // rotated queries, partial sums of residual updates (and the attention's
+    // chunks), and the GEMM inputs as X_TERMS terms: normed rows and attention
+    // output (pf_x), MLP activation (pf_y)
     bool pf_ok = false;
-    float *pf_h = nullptr, *pf_c = nullptr, *pf_q = nullptr, *pf_part = nullptr;
-    uint16_t *pf_x = nullptr;
-    int64_t pf_term = 0;
-    float *pf_rs = nullptr, *pf_amax = nullptr;
+    float *pf_h = nullptr, *pf_q = nullptr, *pf_part = nullptr;
+    uint16_t *pf_x = nullptr, *pf_y = nullptr, *pf_zero = nullptr;
+    int64_t pf_term = 0, pf_y_term = 0;
     float2 *pf_ml = nullptr;  // attention: (max, sum) per chunk of the keys, row and head
-    int pf_amax_ld = 0;
     DevState *st = nullptr;
     Mailbox *mb_host = nullptr;
     Mailbox *mb_dev = nullptr;
@@ -757,45 +755,40 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
     // up to 64 rows on the thin GEMMs, if every layer fits them
     const bool thin = pf_thin_ok(M, std::max({(int64_t)nq, (int64_t)2 * F, (int64_t)c.vocab}), d) &&
                       pf_thin_ok(M, d, hd) && pf_thin_ok(M, d, F);
-    const PfTerms terms{m->pf_x, m->pf_rs, m->pf_term, thin ? pf_thin_blocks(M) : 0};
+    const int blocks = thin ? pf_thin_blocks(M) : 0;
+    const PfTerms terms{m->pf_x, m->pf_term, blocks}, act{m->pf_y, m->pf_y_term, blocks};
     // A residual update leaves its partial sums in pf_part; the next norm adds
     // them into the residual stream (fold = their count, 0: none).
     int fold = 0;
     PfRope rope{m->rope, nullptr, nullptr, head_stride, start, H, KVH, dh};
-    auto gemm = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, int *out) {
+    auto product = [&](const void *W, int N, int K, const PfTerms &in, float *C, int64_t ldc, int epi) {
+        if (thin) {
+            PfThinArgs g{};
+            g.W = static_cast<const uint16_t *>(W);
+            g.X = in.x;
+            g.C = epi == EPI_RESID ? m->pf_part : C;
+            g.ldc = ldc;
+            g.M = M;
+            g.N = N;
+            g.K = K;
+            g.out = act;
+            g.rope = rope;
+            return launch(launch_pf_thin(g, epi, s, &fold), "prefill GEMM");
+        }
         PfGemmArgs g{};
         g.W = static_cast<const uint16_t *>(W);
-        g.A = terms.x;
-        g.rs = terms.rs;
-        g.a_term = terms.term;
+        g.A = in.x;
+        g.a_term = in.term;
+        g.zero = m->pf_zero;
         g.C = C;
         g.ldc = ldc;
         g.M = M;
         g.N = N;
         g.K = K;
-        g.lda = pf_pitch(K);
         g.part = m->pf_part;
-        g.amax = m->pf_amax;
-        g.amax_ld = m->pf_amax_ld;
+        g.out = act;
         g.rope = rope;
-        return launch(launch_pf_gemm(g, epi, s, out), "prefill GEMM");
-    };
-    auto product = [&](const void *W, int N, int K, float *C, int64_t ldc, int epi, int *out) {
-        if (!thin)
-            return gemm(W, N, K, C, ldc, epi, out);
-        PfThinArgs g{};
-        g.W = static_cast<const uint16_t *>(W);
-        g.X = terms.x;
-        g.rs = terms.rs;
-        g.C = epi == EPI_RESID ? m->pf_part : C;
-        g.ldc = ldc;
-        g.M = M;
-        g.N = N;
-        g.K = K;
-        g.amax = m->pf_amax;
-        g.amax_ld = m->pf_amax_ld;
-        g.rope = rope;
-        return launch(launch_pf_thin(g, epi, s, out), "prefill GEMM");
+        return launch(launch_pf_gemm(g, epi, s, &fold), "prefill GEMM");
     };
     auto norm = [&](const void *gain) {
         const int f = fold;
@@ -812,7 +805,6 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
         return SD_OK;
     SD_TRY(launch(launch_pf_embed(static_cast<const uint16_t *>(m->tok_emb), d, dev_tokens, M, m->pf_h, s),
                   "prefill embedding"));
-    int slots = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         if (!(skip && skip[2 * l])) {
             uint16_t *kbase = reinterpret_cast<uint16_t *>(kv) + (size_t)(2 * l) * KVH * head_stride;
@@ -820,7 +812,7 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
             SD_TRY(norm(m->attn_norm[l]));
             rope.kcache = kbase;
             rope.vcache = vbase;
-            SD_TRY(product(m->w_qkv[l], nq, d, m->pf_q, hd, EPI_QKV, nullptr));
+            SD_TRY(product(m->w_qkv[l], nq, d, terms, m->pf_q, hd, EPI_QKV));
             if (!logits && l == last_attn)
                 return SD_OK;
             PfAttnArgs at{};
@@ -832,25 +824,22 @@ sd_status enqueue_forward_large(sd_model *m, void *kv, int32_t cap, const uint8_
             at.out = m->pf_part;
             at.ldo = hd;
             at.ml = m->pf_ml;
-            at.amax = m->pf_amax;
-            at.amax_ld = m->pf_amax_ld;
             at.M = M;
             at.start = start;
             at.n_heads = H;
             at.n_kv_heads = KVH;
             at.head_dim = dh;
             SD_TRY(launch(launch_pf_attention(at, terms, s), "prefill attention"));
-            SD_TRY(product(m->w_o[l], d, hd, nullptr, d, EPI_RESID, &fold));
+            SD_TRY(product(m->w_o[l], d, hd, terms, nullptr, d, EPI_RESID));
         }
         if (!(skip && skip[2 * l + 1])) {
             SD_TRY(norm(m->mlp_norm[l]));
-            SD_TRY(product(m->w_gate_up[l], 2 * F, d, m->pf_c, F, EPI_SWIGLU, &slots));
-            SD_TRY(launch(launch_pf_split(m->pf_c, F, M, m->pf_amax, slots, m->pf_amax_ld, terms, s), "prefill terms"));
-            SD_TRY(product(m->w_down[l], d, F, nullptr, d, EPI_RESID, &fold));
+            SD_TRY(product(m->w_gate_up[l], 2 * F, d, terms, nullptr, 0, EPI_SWIGLU));
+            SD_TRY(product(m->w_down[l], d, F, act, nullptr, d, EPI_RESID));
         }
     }
     SD_TRY(norm(m->final_norm));
-    return product(m->lm_head, c.vocab, d, logits, c.vocab, EPI_STORE, nullptr);
+    return product(m->lm_head, c.vocab, d, terms, logits, c.vocab, EPI_STORE);
 }
 
 // Prefill: full-model forward of tokens [0, n) already on the device, no
@@ -1448,12 +1437,11 @@ void destroy_model(sd_model *m) {
     dev_free(m->ws.attn_ml);
     dev_free(m->rope);
     dev_free(m->pf_h);
-    dev_free(m->pf_c);
     dev_free(m->pf_q);
     dev_free(m->pf_part);
     dev_free(m->pf_x);
-    dev_free(m->pf_rs);
-    dev_free(m->pf_amax);
+    dev_free(m->pf_y);
+    dev_free(m->pf_zero);
     dev_free(m->pf_ml);
     dev_free(m->ws.ctl);
     dev_free(m->st);
@@ -1544,17 +1532,16 @@ sd_status create_model(const sd_config *cfg, const sd_weights *w, void *stream, 
     m->pf_ok = m->bf16 && (c.head_dim == 32 || c.head_dim == 64 || c.head_dim == 128);
     if (m->pf_ok) {
         const int64_t hd = (int64_t)c.n_heads * c.head_dim;
-        m->pf_term = (int64_t)PF_ROWS * pf_pitch((int)std::max<int64_t>({c.d_model, hd, c.ffn_dim}));
-        m->pf_amax_ld = std::max(c.n_heads, pf_swiglu_slots(c.ffn_dim));
+        m->pf_term = (int64_t)PF_ROWS * std::max<int64_t>(c.d_model, hd);
+        m->pf_y_term = (int64_t)PF_ROWS * c.ffn_dim;
         chain(dev_alloc(&m->pf_h, (size_t)PF_ROWS * c.d_model));
-        chain(dev_alloc(&m->pf_c, (size_t)PF_ROWS * c.ffn_dim));
         chain(dev_alloc(&m->pf_q, (size_t)PF_ROWS * hd));
         // partial sums of residual updates, and the attention chunks' outputs
         chain(dev_alloc(&m->pf_part, (size_t)PF_PART_ROWS * std::max<int64_t>(c.d_model, hd)));
         chain(dev_alloc(&m->pf_ml, (size_t)PF_PART_ROWS * c.n_heads));
-        chain(dev_alloc(&m->pf_x, (size_t)PF_TERMS * m->pf_term));
-        chain(dev_alloc(&m->pf_rs, (size_t)PF_ROWS));
-        chain(dev_alloc(&m->pf_amax, (size_t)PF_ROWS * m->pf_amax_ld));
+        chain(dev_alloc(&m->pf_x, (size_t)X_TERMS * m->pf_term));
+        chain(dev_alloc(&m->pf_y, (size_t)X_TERMS * m->pf_y_term));
+        chain(dev_alloc(&m->pf_zero, 8));
     }
     if (st != SD_OK) {
         destroy_model(m);
@@ -1582,6 +1569,7 @@ sd_status create_model(const sd_config *cfg, const sd_weights *w, void *stream, 
         hipMemsetAsync(ws.mbuf, 0, sizeof(float) * (size_t)MAX_ROWS * c.ffn_dim, m->stream) != hipSuccess ||
         hipMemsetAsync(ws.o, 0, sizeof(float) * (size_t)MAX_ROWS * c.n_heads * c.head_dim, m->stream) !=
             hipSuccess ||
+        (m->pf_ok && hipMemsetAsync(m->pf_zero, 0, 16, m->stream) != hipSuccess) ||
         hipStreamSynchronize(m->stream) != hipSuccess) {
         destroy_model(m);
         return fail(SD_ERR_DEVICE, "workspace initialisation failed");

@@ -273,15 +273,34 @@ struct AttnArgs {
 // ---------------------------------------------------------------------------
 // Large-M forward (prompt prefill, long forwards): up to PF_ROWS rows at
 // positions [start, start + M), bfloat16 weights and KV.  Activations that
-// feed a matrix-core GEMM are held as PF_TERMS float16 planes of the row times
-// a power of two (kernels_prefill.hip), row-major: [PF_TERMS][PF_ROWS][ld] with
-// ld the row length rounded up to 32 (zeros past the end), and rs[row], the
-// inverse of the row's power of two.
+// feed a matrix-core GEMM are held as X_TERMS bf16 terms (PfTerms).
 constexpr int PF_ROWS = 1024;
-constexpr int PF_TERMS = 2;
 constexpr int PF_MAX_SPLITS = 8;  // k-splits of a residual-update GEMM, and the rows of all its partial planes
 constexpr int PF_PART_ROWS = 4 * PF_ROWS;
-__host__ __device__ constexpr int pf_pitch(int K) { return (K + 31) & ~31; }
+
+// Fragment order of a GEMM input for few rows (k_pf_thin): term t of element k
+// of row m is at thin_off(t, m, k, blocks), blocks = pf_thin_blocks(M), rows
+// past M undefined.
+__host__ __device__ inline int64_t thin_off(int t, int m, int k, int blocks) {
+    return ((((int64_t)(k >> 5) * X_TERMS + t) * blocks + (m >> 4)) << 9) +
+           ((m & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
+constexpr int PF_THIN_ROWS = 64;
+// Blocks of 16 rows of a thin GEMM's input.
+constexpr int pf_thin_blocks(int M) { return M <= 32 ? 2 : (M + 15) / 16; }
+
+// A GEMM input [rows][K] as terms: row-major planes `term` elements apart
+// (blocks 0), or fragment order over `blocks` blocks of 16 rows.
+struct PfTerms {
+    uint16_t *x;
+    int64_t term;
+    int32_t blocks;
+    // term 0 of elements k .. k + 7 (k a multiple of 8), and from a term to the next
+    __device__ uint16_t *at(int m, int k, int K) const {
+        return x + (blocks ? thin_off(0, m, k, blocks) : (int64_t)m * K + k);
+    }
+    __device__ int64_t step() const { return blocks ? (int64_t)blocks << 9 : term; }
+};
 
 // What a QKV product's epilogue needs: the rotary table, and K and V rows
 // start .. start + M - 1 of this layer's cache.
@@ -292,42 +311,31 @@ struct PfRope {
     int32_t start, n_heads, n_kv_heads, head_dim;
 };
 
-// C[m][n] = sum over the terms t of rs[m] A_t[m][0..K) . W[n][0..K).
+// C[m][n] = sum over the terms t of A_t[m][0..K) . W[n][0..K).
 struct PfGemmArgs {
     const uint16_t *W;  // [N][K] bf16
-    const uint16_t *A;  // [PF_TERMS][.][lda] float16 terms, M rows used
-    const float *rs;    // [M]
+    const uint16_t *A;  // [X_TERMS][.][K] bf16 terms, M rows used
     int64_t a_term;     // elements between terms
+    const uint16_t *zero;  // 16 bytes of zeros
     float *C;           // [M][ldc]
     int64_t ldc;
-    int32_t M, N, K, lda;
+    int32_t M, N, K;
     float *part;        // EPI_RESID: [splits][M][ldc], the partial sums (at most PF_PART_ROWS rows)
     int32_t splits;     // set by the launcher
-    // EPI_SWIGLU (W = [gate; up], N = 2 F): silu(gate) * up into C [M][F], and
-    // in amax[m][0 .. slots) (pitch amax_ld) maxima of |C[m]| over column ranges
-    float *amax;
-    int32_t amax_ld;
+    PfTerms out;        // EPI_SWIGLU (W = [gate; up], N = 2 F): silu(gate) * up [M][F]; not A (others still read it)
     PfRope rope;        // EPI_QKV: q into C [M][ldc], k and v into the cache
 };
 
-// The same products for 17 to PF_THIN_ROWS rows (K a multiple of 64).  The
-// activation terms come in fragment order: term t of element k of row m is at
-// thin_off(t, m, k, blocks), blocks = ceil(M / 16), rows past M undefined.
-constexpr int PF_THIN_ROWS = 64;
-__host__ __device__ inline int64_t thin_off(int t, int m, int k, int blocks) {
-    return ((((int64_t)(k >> 5) * PF_TERMS + t) * blocks + (m >> 4)) << 9) +
-           ((m & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
-}
+// The same products for 17 to PF_THIN_ROWS rows (K a multiple of 64), the
+// activation terms in fragment order.
 struct PfThinArgs {
     const uint16_t *W;  // [N][K] bf16
-    const uint16_t *X;  // float16 terms in fragment order
-    const float *rs;    // [M]
-    float *C;           // STORE [M][ldc]; PARTIAL [splits][M][ldc]; SWIGLU [M][ldc] (N = 2 F); QKV: q [M][ldc]
+    const uint16_t *X;  // bf16 terms in fragment order
+    float *C;           // STORE [M][ldc]; PARTIAL [splits][M][ldc]; QKV: q [M][ldc]
     int64_t ldc;
     int32_t M, N, K;
     int32_t splits, n_tiles;  // n_tiles: 16-row weight tiles
-    float *amax;              // SWIGLU: maxima of |C[m]| over the work-groups' columns
-    int32_t amax_ld;
+    PfTerms out;              // SWIGLU (N = 2 F), not X
     PfRope rope;              // QKV
 };
 
@@ -339,47 +347,33 @@ struct PfAttnArgs {
     const uint16_t *kcache, *vcache;  // this layer: [n_kv_heads][cap][head_dim]
     int64_t kv_head_stride;
     // scratch: float32 outputs of the chunks of the keys (PF_PART_ROWS rows) and
-    // their (max, sum) per head; maxima of the rows [M][amax_ld]
+    // their (max, sum) per head
     float *out;      // [chunks][M][ldo]
     int64_t ldo;
     float2 *ml;      // [chunks][M][n_heads]
-    float *amax;
-    int32_t amax_ld;
     int32_t M, start, n_heads, n_kv_heads, head_dim;
     int32_t chunks, chunk_keys;  // set by the launcher
 };
 
 hipError_t launch_pf_embed(const uint16_t *emb, int d, const int32_t *tokens, int M, float *h, hipStream_t s);
-// Where a GEMM input's terms go: row-major planes `term` elements apart
-// (blocks 0), or fragment order over `blocks` blocks of 16 rows (thin_off).
-struct PfTerms {
-    uint16_t *x;
-    float *rs;
-    int64_t term;
-    int32_t blocks;
-};
 // g * h / rms(h) of every row (g: gain [K] bf16) as terms; with splits > 0
 // after adding split-K partials into h: h[m] += part[0][m] + part[1][m] + ...
 // ([splits][M][K], in split order).
 hipError_t launch_pf_norm_split(float *h, const float *part, int splits, int K, int M, const uint16_t *gain, float eps,
                                 const PfTerms &t, hipStream_t s);
-// x [M][K] as terms, given maxima of each row in amax[m][0 .. slots).
-hipError_t launch_pf_split(const float *x, int K, int M, const float *amax, int slots, int amax_ld, const PfTerms &t,
-                           hipStream_t s);
 // C = A W^T (EPI_STORE), the partial sums of a residual update into a.part
 // (EPI_RESID; *out receives their number, for launch_pf_norm_split), the SwiGLU
-// of a gate/up product (EPI_SWIGLU; *out receives the number of amax slots), or
-// the rotated q and the cache rows of a QKV product (EPI_QKV).
+// of a gate/up product as terms (EPI_SWIGLU), or the rotated q and the cache
+// rows of a QKV product (EPI_QKV).
 hipError_t launch_pf_gemm(const PfGemmArgs &a, int epi, hipStream_t s, int *out = nullptr);
-// The same with the rules of PfThinArgs: EPI_STORE, EPI_RESID (partial sums
-// into C, *out their number), EPI_SWIGLU (*out the amax slots) or EPI_QKV.
+// Its two parts: the tile (0 .. PF_TILE_COUNT - 1) and the splits of the
+// reduction for a shape, and the launch with a given tile and a.splits.
+constexpr int PF_TILE_COUNT = 5;
+int pf_gemm_tile(int M, int N, int K, int epi, int *splits);
+hipError_t launch_pf_gemm_tile(const PfGemmArgs &a, int epi, int tile, hipStream_t s);
+// The same with the rules of PfThinArgs (EPI_RESID: partial sums into C).
 bool pf_thin_ok(int M, int64_t N, int K);
 hipError_t launch_pf_thin(const PfThinArgs &a, int epi, hipStream_t s, int *out = nullptr);
-// Blocks of 16 rows of a thin GEMM's input.
-constexpr int pf_thin_blocks(int M) { return M <= 32 ? 2 : (M + 15) / 16; }
-// amax slots a gate/up product of ffn columns writes at most (24 columns each:
-// three tiles of k_pf_thin).
-constexpr int pf_swiglu_slots(int ffn) { return (ffn + 23) / 24; }
 hipError_t launch_pf_attention(const PfAttnArgs &a, const PfTerms &t, hipStream_t s);
 
 // Kernel paths of the linear layers.

@@ -1,26 +1,26 @@
 """GPU parity of the large-M GEMMs at the edges of their tiles and of the
-float16 window of their operands.
+range of their operands.
 
 - MLP and head products of one-layer models (attention skipped, so nothing is
   rounded to bfloat16 on the way): 17 to 64 rows on the thin GEMM and more on
   the tile GEMM, at every boundary of 16-row blocks, 64- and 128-row tiles; a
   shape whose reductions are no multiple of 64 or 32 takes the tile GEMM at
   every row count.
-- Weight rows far outside the float16 window of the GEMMs' common scale (they
-  run again with a scale per row), and an MLP activation 2^12 times the others
-  that its down weights undo, beside one 2^-35 times the others.
+- Weight rows far from the others' magnitude, and an MLP activation 2^12 times
+  the others that its down weights undo, beside one 2^-35 times the others.
+- Powers of two on MLP channels that the down weights undo: the logits are, bit
+  for bit, those of the model without them.
 - MLP activations of every row near the ends of float32's range, the down
   weights undoing the factor.
 - The rotary embedding and KV append in the thin QKV product, after a prefix
   and after a decode step over the keys it wrote.
 
-Tolerance of the products: every output is a chain of three products of at
-most 2048 terms, accumulated in float32 in at most 2 (terms) x 64 (steps of 32)
+Tolerance of the products: every output is a chain of three products of at most
+2048 terms, accumulated in float32 in at most 3 (terms) x 64 (steps of 32)
 matrix instructions and 8 partial sums, each rounding to 2^-24 of the running
-sum, and the two float16 terms hold an activation to 2^-22.  The sum of their
-worst cases, 3 x (136 x 2^-24 + 2^-22) = 2.5e-5 of the norm of the row, bounds
-the difference to 5e-5 of the row's logit deviation times the factor the
-oracle's own logit rows are scaled by.
+sum.  The sum of their worst cases, 3 x 200 x 2^-24 = 3.6e-5 of the norm of the
+row, bounds the difference to 5e-5 of the row's logit deviation times the factor
+the oracle's own logit rows are scaled by.
 """
 
 import numpy as np
@@ -46,7 +46,7 @@ MLP_REL = 5e-5
 THIN = S.ModelConfig("terms_thin", 1, 256, 4, 2, 64, 1344, 777, "bf16")
 RAGGED = S.ModelConfig("terms_ragged", 1, 136, 3, 1, 32, 200, 777, "bf16")
 LONG_K = S.ModelConfig("terms_long_k", 1, 512, 4, 2, 64, 2048, 400, "bf16")
-# head rows scaled far below and above the rest; gate / up / down rows that undo each other
+# head rows scaled far below and above the rest
 HEAD_ROWS = {5: -30, 6: -30, 200: 9, 399: -60}
 _models = {}
 
@@ -124,3 +124,35 @@ def test_thin_rotary_and_kv_append(name, rows):
         out = torch.empty((hi - lo, cfg.vocab), dtype=torch.float32, device="cuda")
         dm.forward(toks[lo:hi], gc, logits=out)
         A._tight(ref, out.cpu().numpy(), f"{name} rows {lo}..{hi}")
+
+
+# MLP channel -> exponent of a power of two on its up row, undone on its down column
+CHANNELS = {
+    # every down row has a largest magnitude near 2^-10 and elements down to 2^-35, the activations the reverse
+    "spread": {k: 6 + k % 20 for k in range(THIN.ffn_dim)},
+    # one MLP activation 2^24 and one 2^30 times the others
+    "outliers": {3: 24, 40: 30},
+}
+
+
+@pytest.mark.parametrize("rows", [17, 33, 64, 100, 300])
+@pytest.mark.parametrize("what", list(CHANNELS))
+def test_powers_of_two_change_no_bit(what, rows):
+    """The three terms hold an activation exactly and weights are multiplied as they are, so a power of two on a
+    weight goes through every product and sum unchanged: the logits are those of the plain model, bit for bit."""
+    _, _, plain = _pair(THIN, False)
+    if (THIN.name, what) not in _models:
+        w = S.make_weights(THIN, 11)
+        F, gu, down = THIN.ffn_dim, w["layers.0.w_gate_up"], w["layers.0.w_down"]
+        for k, e in CHANNELS[what].items():
+            gu[F + k] = S.scale_tensor(gu[F + k], 2.0 ** e, "bf16")
+            down[:, k] = S.scale_tensor(np.ascontiguousarray(down[:, k]), 2.0 ** -e, "bf16")
+        _models[(THIN.name, what)] = U.device_model(THIN, w)
+    toks, skip = S.prompt(THIN, rows, seed=rows), np.array([1, 0], np.uint8)
+    got = []
+    for dm in (plain, _models[(THIN.name, what)]):
+        out = torch.full((rows, THIN.vocab), float("nan"), dtype=torch.float32, device="cuda")
+        dm.forward(toks, dm.cache(rows), skip=skip, logits=out)
+        got.append(out.cpu().numpy().astype(np.float64))
+    worst = np.abs(got[0] - got[1]).max() / got[0].std()
+    assert np.array_equal(got[0], got[1]), f"{what}, {rows} rows: {worst} of the deviation"

@@ -11,9 +11,7 @@ Tolerance: the products of the activations' three bfloat16 terms are exact, so
 only float32 sums round: at most 14000 terms in 3 x 437 matrix instructions and
 8 + 4 partial sums of 2^-24 of the running sum each, in a chain of three
 products; 3 x 1323 x 2^-24 = 2.4e-4 of the row's logit deviation bounds the
-difference, and the sums' rounding is far from its worst case: 1e-4.  Prompts
-have two float16 terms: two thirds of the instructions, and 2^-22 of each
-activation.
+difference, and the sums' rounding is far from its worst case: 1e-4.
 """
 
 import numpy as np
