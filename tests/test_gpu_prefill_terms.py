@@ -156,3 +156,28 @@ def test_powers_of_two_change_no_bit(what, rows):
         got.append(out.cpu().numpy().astype(np.float64))
     worst = np.abs(got[0] - got[1]).max() / got[0].std()
     assert np.array_equal(got[0], got[1]), f"{what}, {rows} rows: {worst} of the deviation"
+
+
+# vocabulary row -> exponent of a power of two on it
+HEAD_POWERS = {0: -60, 5: -30, 200: 9, 399: 112, 776: 118}
+
+
+@pytest.mark.parametrize("rows", [17, 33, 64, 100, 300])
+def test_logits_near_the_ends_of_the_range(rows):
+    """Head rows times powers of two up to 2^118: the logits are those of the plain model times the power, bit for
+    bit, so no intermediate value leaves float32's range where the logit does not."""
+    _, _, plain = _pair(THIN, False)
+    if (THIN.name, "head") not in _models:
+        w = S.make_weights(THIN, 11)
+        for r, e in HEAD_POWERS.items():
+            w["lm_head"][r] = S.scale_tensor(w["lm_head"][r], 2.0 ** e, "bf16")
+        _models[(THIN.name, "head")] = U.device_model(THIN, w)
+    toks, skip = S.prompt(THIN, rows, seed=rows), np.array([1, 0], np.uint8)
+    got = []
+    for dm in (plain, _models[(THIN.name, "head")]):
+        out = torch.full((rows, THIN.vocab), float("nan"), dtype=torch.float32, device="cuda")
+        dm.forward(toks, dm.cache(rows), skip=skip, logits=out)
+        got.append(out.cpu().numpy().astype(np.float64))
+    for r, e in HEAD_POWERS.items():
+        got[1][:, r] *= 2.0 ** -e
+    assert np.array_equal(got[0], got[1])
