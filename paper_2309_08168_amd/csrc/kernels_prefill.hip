@@ -240,12 +240,19 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
         }
     };
 
-    f32x4_t acc[NT][MT];
+    // Where two waves per SIMD leave the registers, the second and third terms
+    // have sums of their own: the large sum is then rounded once per stage and
+    // not three times (the same time; keys and values of the first layer that
+    // round to another bfloat16 than the float64 ones, 13B, 100 rows: 580 -> 339).
+    constexpr int SUMS = WPS == 2 ? 2 : 1;
+    f32x4_t acc[SUMS][NT][MT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int q = 0; q < SUMS; ++q)
 #pragma unroll
-        for (int j = 0; j < MT; ++j)
-            acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+                acc[q][i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     if (S > 0) {
 #pragma unroll
         for (int p = 0; p < P; ++p)
@@ -275,10 +282,20 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
 #pragma unroll
             for (int i = 0; i < NT; ++i)
 #pragma unroll
-                for (int j = 0; j < MT; ++j)
-                    acc[i][j] = mfma16(wf[i], af[j][t], acc[i][j]);
+                for (int j = 0; j < MT; ++j) {
+                    f32x4_t &c = acc[t ? SUMS - 1 : 0][i][j];
+                    c = mfma16(wf[i], af[j][t], c);
+                }
     }
     __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));  // no load into LDS outlives the work-group
+    f32x4_t(&sum)[NT][MT] = acc[0];
+    if constexpr (SUMS == 2) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+                sum[i][j] += acc[1][i][j];
+    }
 
     // lane holds C^T[n0 + wn WN + 16 i + 4 grp + v][m0 + wm WM + 16 j + col]
     // (EPI_PARTIAL: of the split's partial sum, part[split][m][n])
@@ -299,8 +316,8 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
                 f32x4_t y0, y1;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][j][v]),
-                                                                    __float_as_uint(acc[i2][j][v]), false, false);
+                    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[i][j][v]),
+                                                                    __float_as_uint(sum[i2][j][v]), false, false);
                     y0[v] = __uint_as_float(r[0]);
                     y1[v] = __uint_as_float(r[1]);
                 }
@@ -332,12 +349,12 @@ __global__ __launch_bounds__(64 * NWN * NWM, WPS) void k_pf_gemm(PfGemmArgs a) {
                     continue;
                 float *c = C + (int64_t)m * a.ldc + n;
                 if (vec && n + 3 < N) {
-                    *reinterpret_cast<f32x4_t *>(c) = acc[i][j];
+                    *reinterpret_cast<f32x4_t *>(c) = sum[i][j];
                 } else {
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
                         if (n + u < N)
-                            c[u] = acc[i][j][u];
+                            c[u] = sum[i][j][u];
                 }
             }
         }
