@@ -1305,3 +1305,35 @@ hipError_t launch_pf_attention(const PfAttnArgs &a0, const PfTerms &t, hipStream
 }
 
 }  // namespace sdk
+
+// For the tests: what pf_gemm_tile picks for a shape (weight rows and
+// activation rows of the tile), and one product on a given tile.
+extern "C" int32_t sdk_prefill_tile(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t *bn, int32_t *bm,
+                                    int32_t *splits) {
+    const int tile = sdk::pf_gemm_tile(M, N, K, epi, splits);
+    *bn = sdk::PF_TILES[tile].bn;
+    *bm = sdk::PF_TILES[tile].bm;
+    return tile;
+}
+
+extern "C" int32_t sdk_prefill_gemm(int32_t tile, int32_t epi, int32_t splits, int32_t M, int32_t N, int32_t K,
+                                    const uint16_t *W, const uint16_t *A, int64_t a_term, const uint16_t *zero,
+                                    float *C, int64_t ldc, uint16_t *out, int64_t out_term, const float2 *table,
+                                    uint16_t *kcache, uint16_t *vcache, int64_t kv_head_stride, int32_t start,
+                                    int32_t n_heads, int32_t n_kv_heads, int32_t head_dim, hipStream_t s) {
+    sdk::PfGemmArgs g{};
+    g.W = W;
+    g.A = A;
+    g.a_term = a_term;
+    g.zero = zero;
+    g.C = C;
+    g.ldc = ldc;
+    g.M = M;
+    g.N = N;
+    g.K = K;
+    g.part = C;
+    g.splits = splits;
+    g.out = sdk::PfTerms{out, out_term, 0};
+    g.rope = sdk::PfRope{table, kcache, vcache, kv_head_stride, start, n_heads, n_kv_heads, head_dim};
+    return (int32_t)sdk::launch_pf_gemm_tile(g, epi, tile, s);
+}

@@ -5,9 +5,13 @@ the prompt prefill, and long sd_forward calls) against the oracle.
   whose shapes leave ragged tails everywhere, and one whose narrow GEMMs
   split their reduction over work-groups: K of 136 and 200 (not a
   multiple of the 32-k stage), output widths of 160 and 400 (not a multiple
-  of the 256-row tile), a vocabulary of 777 (odd leading dimension, scalar
+  of any tile), a vocabulary of 777 (odd leading dimension, scalar
   stores), grouped-query attention with head_dim 32, 64 and 128, and row
   counts across several 64- and 128-row tiles with a ragged last tile.
+- The 256 x 256 tiles in every product: gate/up, split output and down
+  projections, QKV and head (which tile a shape takes is checked in
+  test_prefill_tiles_host.py, every tile with every product in
+  test_gpu_prefill_tiles.py).
 - A forward of 1100 rows runs as two chunks (1024 + 76).
 - A masked forward (sublayers bypassed) equals the oracle's.
 - Attention-dominated one-layer models at the tight tolerance of the
@@ -35,23 +39,26 @@ def _need_gpu():
 
 
 ODD_BF16 = S.ModelConfig("odd_bf16", 2, 136, 3, 1, 32, 200, 777, "bf16")
-# wide enough that the residual-update GEMMs split their reduction (2 ways
-# for the output projection, 4 for the down projection)
+# narrow outputs: the residual-update GEMMs split their reduction
 WIDE_BF16 = S.ModelConfig("wide_bf16", 1, 1024, 8, 8, 128, 2048, 512, "bf16")
-# two layers whose output and down projections split their reduction (2
-# and 4 ways): each split's partials are added into the residual stream by
-# the norm that follows, whichever sublayer that is
+# two layers whose output and down projections leave partial sums, which the
+# norm that follows adds into the residual stream, whichever sublayer that is
 WIDE2_BF16 = S.ModelConfig("wide2_bf16", 2, 1024, 8, 8, 128, 2048, 512, "bf16")
-# a gate/up GEMM wide enough (14400 columns: 57 tiles of 256, the last one
-# 64 wide) that forwards of 513 rows or more take the direct-to-LDS kernel
+# a gate/up GEMM of 14400 columns: 65 tiles of 224 x 256 per 256 rows at 600
+# rows, 57 of 256 x 256 (the last one 64 wide) at 1000
 FFN_WIDE_BF16 = S.ModelConfig("ffn_wide_bf16", 1, 256, 4, 4, 64, 7200, 512, "bf16")
 MODELS = {"mini_bf16": U.MINI_BF16, "odd_bf16": ODD_BF16, "gqa8_dh128": A.CONFIGS["gqa8_dh128"],
           "wide_bf16": WIDE_BF16}
-# output and down projections of 10 column tiles of 256: at 1000 rows (4 row
-# tiles) they split their reduction 4 ways on the 256 x 256 kernel (160
-# work-groups)
+# output and down projections of 10 x 8 tiles of 256 x 128 at 1000 rows, their
+# reductions split three ways
 D2560_BF16 = S.ModelConfig("d2560_bf16", 1, 2560, 20, 20, 128, 2048, 512, "bf16")
-EXTRA = {"ffn_wide_bf16": FFN_WIDE_BF16, "wide2_bf16": WIDE2_BF16, "d2560_bf16": D2560_BF16}
+# a down projection of 20 x 4 tiles of 256 x 256 at 1000 rows, split three ways
+SPLIT_WIDE_BF16 = S.ModelConfig("split_wide_bf16", 1, 5120, 8, 8, 128, 4096, 512, "bf16")
+# QKV and head of 64 x 4 tiles of 256 x 256 at 1000 rows (and H head_dim past
+# what the attention kernel of head_dim 128 takes)
+ALL_WIDE_BF16 = S.ModelConfig("all_wide_bf16", 1, 256, 96, 16, 128, 7200, 16381, "bf16")
+EXTRA = {"ffn_wide_bf16": FFN_WIDE_BF16, "wide2_bf16": WIDE2_BF16, "d2560_bf16": D2560_BF16,
+         "split_wide_bf16": SPLIT_WIDE_BF16, "all_wide_bf16": ALL_WIDE_BF16}
 _models = {}
 
 
@@ -82,8 +89,8 @@ def test_long_forward_from_zero(name, rows):
 
 @pytest.mark.parametrize("rows", [600, 1000, 1024])
 def test_forward_on_the_wide_gemm(rows):
-    """gate/up of 3 or 4 x 57 tiles of 256 x 256 (a ragged last row tile at
-    600 and 1000 rows, a 64-column last column tile): the direct-to-LDS GEMM."""
+    """gate/up on 224 x 256 tiles at 600 rows and 256 x 256 at 1000 and 1024
+    (a ragged last row tile at 600 and 1000, a ragged last column tile)."""
     cfg, w, om, dm = _pair("ffn_wide_bf16")
     toks = S.prompt(cfg, rows, seed=rows + 5)
     ref = om.score(toks)["logits"]
@@ -94,9 +101,9 @@ def test_forward_on_the_wide_gemm(rows):
 
 @pytest.mark.parametrize("rows", [600, 1000])
 def test_wide_gemm_forward_is_deterministic(rows):
-    """Three forwards on the SwiGLU-fused gate/up GEMM (224- and 256-wide
-    tiles) give bit-identical logits: no work-group writes its output where
-    another still reads its input."""
+    """Three forwards on the SwiGLU-fused gate/up GEMM (224 x 256 tiles at 600
+    rows, 256 x 256 at 1000) give bit-identical logits: no work-group writes
+    its output where another still reads its input."""
     cfg, w, om, dm = _pair("ffn_wide_bf16")
     toks = S.prompt(cfg, rows, seed=rows + 13)
     first = _logits(dm, toks, dm.cache(rows))
@@ -130,9 +137,9 @@ def test_forward_of_two_chunks():
 
 @pytest.mark.parametrize("mask", ["none", "1", "2", "3"])
 def test_split_partials_fold_into_the_next_norm(mask):
-    """Split output and down projections on a two-layer model: unmasked the
-    partials go into the next MLP or attention norm and the final norm; with
-    layer 0's MLP skipped (1) the output projection's go into layer 1's
+    """The partial sums of the output and down projections on a two-layer
+    model: unmasked they go into the next MLP or attention norm and the final
+    norm; with layer 0's MLP skipped (1) the output projection's go into layer 1's
     attention norm, with layer 1's attention skipped (2) the down
     projection's into layer 1's MLP norm, with layer 1's MLP skipped (3)
     into the final norm."""
@@ -146,8 +153,8 @@ def test_split_partials_fold_into_the_next_norm(mask):
 
 
 def test_split_reduction_on_the_wide_gemm():
-    """The output and down projections of a d 2560 model over 1000 rows: 40
-    tiles of 256 x 256, each reduction split 4 ways, the partials folded
+    """The output and down projections of a d 2560 model over 1000 rows: 80
+    tiles of 256 x 128, each reduction split three ways, the partials folded
     into the MLP norm and the final norm."""
     cfg, w, om, dm = _pair("d2560_bf16")
     toks = S.prompt(cfg, 1000, seed=41)
@@ -157,10 +164,22 @@ def test_split_reduction_on_the_wide_gemm():
     print(f"d2560_bf16 1000 rows: max |d| / tol {r:.3f}")
 
 
+@pytest.mark.parametrize("name", ["split_wide_bf16", "all_wide_bf16"])
+def test_256_tiles_in_every_product(name):
+    """1000 rows: a down projection on 256 x 256 tiles split three ways; QKV,
+    gate/up and head on 256 x 256 tiles."""
+    cfg, w, om, dm = _pair(name)
+    toks = S.prompt(cfg, 1000, seed=43)
+    ref = om.score(toks)["logits"]
+    got = _logits(dm, toks, dm.cache(1000))
+    r = U.check_logits(cfg, got, ref, f"{name} 1000 rows")
+    print(f"{name} 1000 rows: max |d| / tol {r:.3f}")
+
+
 def test_generate_after_a_split_prefill():
     """The prompt prefill of a model with split residual updates and no
-    logits: the last down projection's partials are added by a plain sum, and
-    layer 1's keys and values depend on every fold before them."""
+    logits ends with layer 1's keys and values, which depend on every fold
+    before them."""
     cfg, w, om, dm = _pair("wide2_bf16")
     pr = S.prompt(cfg, 200, seed=23)
     z = S.skip_mask(cfg, "1", seed=0)

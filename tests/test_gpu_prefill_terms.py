@@ -3,9 +3,9 @@ range of their operands.
 
 - MLP and head products of one-layer models (attention skipped, so nothing is
   rounded to bfloat16 on the way): 17 to 64 rows on the thin GEMM and more on
-  the tile GEMM, at every boundary of 16-row blocks, 64- and 128-row tiles; a
-  shape whose reductions are no multiple of 64 or 32 takes the tile GEMM at
-  every row count.
+  the tile GEMM (128 x 64 at these sizes), at every boundary of 16-row blocks
+  and 64-row tiles; a shape whose reductions are no multiple of 64 or 32 takes
+  the tile GEMM at every row count.
 - Weight rows far from the others' magnitude, and an MLP activation 2^12 times
   the others that its down weights undo, beside one 2^-35 times the others.
 - Powers of two on MLP channels that the down weights undo: the logits are, bit
