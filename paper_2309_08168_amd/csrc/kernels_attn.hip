@@ -825,19 +825,20 @@ __global__ __launch_bounds__(HW * 64) void k_attn_head(AttnArgs a) {
         const float mn = fmaxf(mr, mx);
         if (mn != -INFINITY) {
             const float so = expf(mr - mn);
-            float l = lr * so;
-#pragma unroll
-            for (int e = 0; e < ED; ++e)
-                o[e] *= so;
+            // the block's sums first: one rounding of the running sums per block
+            float l = 0.0f, y[ED];
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 const float p = expf(s[jj] - mn);
                 l += p;
 #pragma unroll
                 for (int e = 0; e < ED; ++e)
-                    o[e] = fmaf(p, vc[jj].at(e), o[e]);
+                    y[e] = jj ? fmaf(p, vc[jj].at(e), y[e]) : p * vc[jj].at(e);
             }
-            lr = l;
+            lr = fmaf(lr, so, l);
+#pragma unroll
+            for (int e = 0; e < ED; ++e)
+                o[e] = fmaf(o[e], so, y[e]);
             mr = mn;
         }
 #pragma unroll
