@@ -13,10 +13,13 @@
 //     gate/up product's applies the SwiGLU);
 //   - k_pf_thin: the same products for up to 64 rows, bound by the weight
 //     stream;
-//   - k_pf_attn: causal attention, one wave per 16 query rows of a head,
-//     scores and the weighted sum of values on matrix cores with an online
-//     softmax over 32-key blocks, the longest row blocks dispatched first and
-//     spread evenly over the XCDs;
+//   - k_pf_attn128 and k_pf_attn_terms: causal attention for head_dim 128, 128
+//     query rows of a head sharing 64-key stages through LDS, split over chunks
+//     of the keys, and the chunks combined;
+//   - k_pf_attn: causal attention for head_dim 32 and 64, one wave per 16 query
+//     rows of a head, 32-key blocks;
+//     both with scores and the weighted sum of values on matrix cores, an online
+//     softmax, and the longest row blocks dispatched first;
 //   - small row kernels between them: embedding, and RMSNorm into terms (adding
 //     a residual update's partials first).
 #include "sd_internal.h"
@@ -1275,6 +1278,10 @@ hipError_t launch_pf_attention(const PfAttnArgs &a0, const PfTerms &t, hipStream
     if (a.M < 1 || a.n_heads < 1 || a.n_kv_heads < 1 || a.n_heads % a.n_kv_heads)
         return hipErrorInvalidValue;
     const int hd = a.n_heads * a.head_dim;
+    // head_dim 128 with more than 64 heads (none of the shapes here) runs on
+    // k_pf_attn: us of 64 heads on this kernel and 66 on that one, 1000 rows over
+    // 4000 keys 437 and 812, 600 from position 0 44 and 45, 200 from position 0 22
+    // and 17.
     if (a.head_dim == 128 && hd <= 8192) {
         const int units = ((a.M + PA2_ROWS - 1) / PA2_ROWS) * a.n_heads, keys = a.start + a.M;
         const int most = std::min({PF_PART_ROWS / a.M, keys / 256, 16384 / a.n_heads});

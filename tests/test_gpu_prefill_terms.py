@@ -93,7 +93,7 @@ def test_products_at_tile_edges(cfg, rows):
 
 @pytest.mark.parametrize("rows", [33, 64, 100, 300])
 @pytest.mark.parametrize("cfg", [THIN, LONG_K], ids=lambda c: c.name)
-def test_rows_outside_the_float16_window(cfg, rows):
+def test_rows_of_other_magnitudes(cfg, rows):
     _check(cfg, rows, True)
 
 
