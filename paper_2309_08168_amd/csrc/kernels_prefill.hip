@@ -1320,6 +1320,8 @@ hipError_t launch_pf_attention(const PfAttnArgs &a0, const PfTerms &t, hipStream
 // activation rows of the tile), and one product on a given tile.
 extern "C" int32_t sdk_prefill_tile(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t *bn, int32_t *bm,
                                     int32_t *splits) {
+    if (M < 1 || M > sdk::PF_ROWS || N < 1 || K < 8)
+        return -1;
     const int tile = sdk::pf_gemm_tile(M, N, K, epi, splits);
     *bn = sdk::PF_TILES[tile].bn;
     *bm = sdk::PF_TILES[tile].bm;

@@ -77,3 +77,9 @@ def test_splits_stay_within_the_scratch(rows):
             assert 1 <= splits <= (8 if epi == RESID else 1)
             assert splits * rows <= 4096
             assert splits == 1 or -(-K // 32) >= 8 * splits
+
+
+@pytest.mark.parametrize("M,N,K", [(0, 64, 64), (1025, 64, 64), (17, 0, 64), (17, 64, 0)])
+def test_shapes_out_of_range_are_refused(M, N, K):
+    out = [ctypes.byref(ctypes.c_int32()) for _ in range(3)]
+    assert binding.load().sdk_prefill_tile(M, N, K, RESID, *out) == -1
